@@ -2,12 +2,10 @@
 // H_hat = (S_hat X)^T S_hat X (Sec. 3) is applied through its triangular
 // factor R (R^T R = H_hat; QR route of the implementation-details appendix).
 //
-//  gemm        C = alpha op(A) op(B) + beta C, 64x64 tiles, 4x4 per thread
-//  cholesky    one block, blocked upper Cholesky: for each 32-row panel the
-//              rows are first updated with all earlier rows of R (a GEMM
-//              staged through LDS), then factored in LDS
-//  tri_inv_t   L = R^{-T}: one wave per row of L (back substitution of
-//              R x = e_j, x kept in LDS)
+//  gram        G = alpha A^T A, the upper tiles on the FP64 matrix cores
+//  cholesky    R^T R = G together with Z = R^{-T}, one launch per 32 columns
+//  gemm        Q = alpha A Z^T (a CholeskyQR pass) and small d x d products
+// and M = (R^T R)^{-1} = Z^T Z, once more the Gram kernel.
 #include <algorithm>
 
 #include "kernels.hpp"
@@ -15,8 +13,7 @@
 namespace slse {
 namespace {
 
-constexpr int kTile = 64;
-constexpr int kKStep = 16;
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 // value of `v` held by lane `lane` (uniform), broadcast to the wave
 __device__ __forceinline__ double readlane_f64(double v, int lane) {
@@ -26,589 +23,489 @@ __device__ __forceinline__ double readlane_f64(double v, int lane) {
   return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
 }
 
-// One 64 x 64 output tile of C = alpha op(A) op(B) + beta C over k in
-// [kb0, kend); with `part` the raw sums go to split slot `zpart` instead.
-// (the pointer types are generic, or global ones from a batched kernel's
-// job descriptors)
-template <typename CP, typename MP>
-__device__ __forceinline__ void gemm_tile(int64_t M, int64_t N, double alpha, CP __restrict__ A,
-                                          int64_t lda, int transA, CP __restrict__ B, int64_t ldb,
-                                          int transB, double beta, MP __restrict__ C, int64_t ldc,
-                                          MP __restrict__ part, int zpart, int64_t i0,
-                                          int64_t j0, int64_t kb0, int64_t kend) {
-  __shared__ double As[kKStep][kTile + 1];
-  __shared__ double Bs[kKStep][kTile + 1];
-  const int tx = threadIdx.x % 16;
-  const int ty = threadIdx.x / 16;
-  double acc[4][4] = {};
-  // Each thread copies kL entries of A and of B per k step.  Their loads are
-  // unconditional (entries outside the matrices read a clamped, valid address
-  // and are replaced by zero when written to LDS) and the next step's are
-  // issued before the current step's products, so they are all in flight
-  // together and overlap the arithmetic.
-  constexpr int kL = kKStep * kTile / 256;
+// ---------------------------------------------------------------------------
+// FP64 products on the matrix cores (v_mfma_f64_16x16x4_f64: lane l holds
+// A[l % 16][l / 16] and B[l / 16][l % 16]; accumulator r of lane l is
+// C[4 r + l / 16][l % 16]).  A block of four waves computes an
+// S x S tile (S = 32 MT), each wave MT x MT MFMA tiles, in steps of 32 k staged
+// through LDS; the next step's loads are in flight during the products.
+// Matrix products of the factor are small (d <= 1024), so what bounds them
+// is latency: S = 32 where a product has few tiles, S = 64 where the tiles and
+// the row splits fill the chip anyway (twice the products per LDS read).
+// ---------------------------------------------------------------------------
+constexpr int kKS = 32;  // k per step
+
+template <int MT>
+struct GemmLds {
+  // row strides: 2 x stride = 8 and 32 banks mod 64, so that the 16 x 4 lanes
+  // of an operand read fall into distinct banks
+  double a[kKS][32 * MT + 16];
+  double b[kKS][32 * MT + 16];
+};
+
+// acc += op(A)[i0 .., k] op(B)[k, j0 ..] over k in [kb0, kend).
+// TRA: A is stored k-major (A[k][i]), else i-major; TRB: B is stored j-major
+// (B[j][k]), else k-major.
+template <int MT, bool TRA, bool TRB, typename AP, typename BP>
+__device__ __forceinline__ void mfma_tile(GemmLds<MT>& lds, AP __restrict__ A, int64_t lda,
+                                          BP __restrict__ B, int64_t ldb, int64_t M, int64_t N,
+                                          int64_t i0, int64_t j0, int64_t kb0, int64_t kend,
+                                          f64x4 (&acc)[MT][MT]) {
+  constexpr int S = 32 * MT;
+  constexpr int kL = kKS * S / 256;  // entries of A and of B per thread per step
+  const int t = threadIdx.x;
+  const int lane = t & 63, wave = t >> 6;
+  const int wr = (wave >> 1) * 16 * MT, wc = (wave & 1) * 16 * MT;
   double va[kL], vb[kL];
   unsigned oka = 0, okb = 0;
+  // loads outside the matrices read a clamped, valid address and become zero
+  // on their way to LDS, so none sits behind a branch
   auto fetch = [&](int64_t k0) {
     oka = okb = 0;
 #pragma unroll
     for (int u = 0; u < kL; ++u) {
-      const int e = threadIdx.x + 256 * u;
-      int kk, ii;
-      if (transA) {  // A stored K x M: contiguous along i
-        kk = e / kTile;
-        ii = e % kTile;
-      } else {  // A stored M x K: contiguous along k
-        ii = e / kKStep;
-        kk = e % kKStep;
-      }
-      const int64_t gi = i0 + ii, gk = k0 + kk;
+      const int e = t + 256 * u;
+      const int ia = TRA ? e % S : e / kKS, ka = TRA ? e / S : e % kKS;
+      const int64_t gi = i0 + ia, gk = k0 + ka;
       oka |= (unsigned)(gi < M && gk < kend) << u;
       const int64_t ci = min(gi, M - 1), ck = min(gk, kend - 1);
-      va[u] = transA ? A[ck * lda + ci] : A[ci * lda + ck];
-      int kb, jj;
-      if (transB) {  // B stored N x K
-        jj = e / kKStep;
-        kb = e % kKStep;
-      } else {
-        kb = e / kTile;
-        jj = e % kTile;
-      }
-      const int64_t gj = j0 + jj, gkb = k0 + kb;
-      okb |= (unsigned)(gj < N && gkb < kend) << u;
-      const int64_t cj = min(gj, N - 1), ckb = min(gkb, kend - 1);
-      vb[u] = transB ? B[cj * ldb + ckb] : B[ckb * ldb + cj];
+      va[u] = (double)(TRA ? A[ck * lda + ci] : A[ci * lda + ck]);
+      const int jb = TRB ? e / kKS : e % S, kb = TRB ? e % kKS : e / S;
+      const int64_t gj = j0 + jb, gq = k0 + kb;
+      okb |= (unsigned)(gj < N && gq < kend) << u;
+      const int64_t cj = min(gj, N - 1), cq = min(gq, kend - 1);
+      vb[u] = (double)(TRB ? B[cj * ldb + cq] : B[cq * ldb + cj]);
     }
   };
   if (kb0 < kend) fetch(kb0);
-  for (int64_t k0 = kb0; k0 < kend; k0 += kKStep) {
+  for (int64_t k0 = kb0; k0 < kend; k0 += kKS) {
 #pragma unroll
     for (int u = 0; u < kL; ++u) {
-      const int e = threadIdx.x + 256 * u;
-      if (transA)
-        As[e / kTile][e % kTile] = ((oka >> u) & 1) ? va[u] : 0.0;
-      else
-        As[e % kKStep][e / kKStep] = ((oka >> u) & 1) ? va[u] : 0.0;
-      if (transB)
-        Bs[e % kKStep][e / kKStep] = ((okb >> u) & 1) ? vb[u] : 0.0;
-      else
-        Bs[e / kTile][e % kTile] = ((okb >> u) & 1) ? vb[u] : 0.0;
+      const int e = t + 256 * u;
+      const int ia = TRA ? e % S : e / kKS, ka = TRA ? e / S : e % kKS;
+      lds.a[ka][ia] = ((oka >> u) & 1) ? va[u] : 0.0;
+      const int jb = TRB ? e / kKS : e % S, kb = TRB ? e % kKS : e / S;
+      lds.b[kb][jb] = ((okb >> u) & 1) ? vb[u] : 0.0;
     }
     __syncthreads();
-    if (k0 + kKStep < kend) fetch(k0 + kKStep);
+    if (k0 + kKS < kend) fetch(k0 + kKS);
 #pragma unroll
-    for (int kk = 0; kk < kKStep; ++kk) {
-      double a[4], b[4];
+    for (int ks = 0; ks < kKS; ks += 4) {
+      double a[MT], b[MT];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        a[u] = As[kk][ty + 16 * u];
-        b[u] = Bs[kk][tx + 16 * u];
+      for (int u = 0; u < MT; ++u) {
+        a[u] = lds.a[ks + (lane >> 4)][wr + 16 * u + (lane & 15)];
+        b[u] = lds.b[ks + (lane >> 4)][wc + 16 * u + (lane & 15)];
       }
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
+      for (int u = 0; u < MT; ++u)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) acc[u][v] = fma(a[u], b[v], acc[u][v]);
+        for (int v = 0; v < MT; ++v)
+          acc[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[v], acc[u][v], 0, 0, 0);
     }
     __syncthreads();
   }
-#pragma unroll
-  for (int u = 0; u < 4; ++u)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int64_t gi = i0 + ty + 16 * u, gj = j0 + tx + 16 * v;
-      if (gi < M && gj < N) {
-        if (part) {
-          part[((int64_t)zpart * M + gi) * N + gj] = acc[u][v];
-        } else {
-          double c = alpha * acc[u][v];
-          if (beta != 0.0) c += beta * C[gi * ldc + gj];
-          C[gi * ldc + gj] = c;
-        }
-      }
-    }
 }
 
-__global__ __launch_bounds__(256) void gemm_kernel(int64_t M, int64_t N, int64_t K, double alpha,
-                                                   const double* __restrict__ A, int64_t lda,
-                                                   int transA, const double* __restrict__ B,
-                                                   int64_t ldb, int transB, double beta,
-                                                   double* __restrict__ C, int64_t ldc,
+// f(row, column, value) for every entry of this thread's accumulators
+template <int MT, typename F>
+__device__ __forceinline__ void for_acc(const f64x4 (&acc)[MT][MT], F&& f) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int wr = (wave >> 1) * 16 * MT, wc = (wave & 1) * 16 * MT;
+#pragma unroll
+  for (int u = 0; u < MT; ++u)
+#pragma unroll
+    for (int v = 0; v < MT; ++v)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        f(wr + 16 * u + 4 * r + (lane >> 4), wc + 16 * v + (lane & 15), acc[u][v][r]);
+}
+
+template <int MT>
+__device__ __forceinline__ void clear_acc(f64x4 (&acc)[MT][MT]) {
+#pragma unroll
+  for (int u = 0; u < MT; ++u)
+#pragma unroll
+    for (int v = 0; v < MT; ++v) acc[u][v] = f64x4{0.0, 0.0, 0.0, 0.0};
+}
+
+// row and column tile of upper tile number `t` (column by column: (0,0),
+// (0,1), (1,1), (0,2), ..)
+__device__ __forceinline__ void upper_tile(int t, int& ti, int& tj) {
+  tj = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
+  while (tj * (tj + 1) / 2 > t) --tj;
+  while ((tj + 1) * (tj + 2) / 2 <= t) ++tj;
+  ti = t - tj * (tj + 1) / 2;
+}
+
+// One upper tile of G = alpha A^T A over the rows [kb0, kend): written to both
+// triangles of G, or raw to split slot `zpart` of `part` when there are several.
+template <int MT, typename AP, typename GP, typename PP>
+__device__ __forceinline__ void gram_tile(int d, double alpha, AP __restrict__ A, int64_t lda,
+                                          GP __restrict__ G, int64_t ldg, PP __restrict__ part,
+                                          int zpart, int tile, int64_t kb0, int64_t kend) {
+  __shared__ GemmLds<MT> lds;
+  int ti, tj;
+  upper_tile(tile, ti, tj);
+  const int i0 = ti * 32 * MT, j0 = tj * 32 * MT;
+  f64x4 acc[MT][MT];
+  clear_acc(acc);
+  mfma_tile<MT, true, false>(lds, A, lda, A, lda, d, d, i0, j0, kb0, kend, acc);
+  for_acc(acc, [&](int r, int c, double v) {
+    const int i = i0 + r, j = j0 + c;
+    if (i >= d || j >= d) return;
+    if (part) {
+      part[((int64_t)zpart * d + i) * d + j] = v;
+    } else {
+      G[(int64_t)i * ldg + j] = alpha * v;
+      if (ti != tj) G[(int64_t)j * ldg + i] = alpha * v;
+    }
+  });
+}
+
+template <int MT, typename T>
+__global__ __launch_bounds__(256) void gram_kernel(int d, int64_t rows, double alpha,
+                                                   const T* __restrict__ A, int64_t lda,
+                                                   double* __restrict__ G, int64_t ldg,
                                                    double* __restrict__ part, int64_t kper) {
-  const int64_t kb0 = (int64_t)blockIdx.z * kper;
-  gemm_tile(M, N, alpha, A, lda, transA, B, ldb, transB, beta, C, ldc, part, (int)blockIdx.z,
-            (int64_t)blockIdx.y * kTile, (int64_t)blockIdx.x * kTile, kb0, min(K, kb0 + kper));
+  const int64_t kb0 = (int64_t)blockIdx.y * kper;
+  gram_tile<MT>(d, alpha, A, lda, G, ldg, part, (int)blockIdx.y, (int)blockIdx.x, kb0,
+                min(rows, kb0 + kper));
 }
 
-// Batched products of the factor jobs (blockIdx.z = job):
-//   which = 0: G = Ad^T Ad    which = 1: M = L L^T
-// G = Ad^T Ad of every job (blockIdx.z = job x splits + split): with splits > 1
-// each split sums its share of the rows into the job's partial slot
-__global__ __launch_bounds__(256) void factor_gemm_batched_kernel(const FactorJob* __restrict__ jobs,
-                                                                  int splits) {
-  const int z = blockIdx.z / splits, sp = blockIdx.z % splits;
-  const FactorJob jb = jobs[z];
-  const int64_t d = jb.d;
-  const int64_t i0 = (int64_t)blockIdx.y * kTile, j0 = (int64_t)blockIdx.x * kTile;
-  if (i0 >= d || j0 >= d) return;
-  const int64_t kper = round_up(ceil_div(jb.rows, (int64_t)splits), kKStep);
-  const int64_t kb0 = sp * kper;
-  gemm_tile(d, d, 1.0, gptr((const double*)jb.Ad), d, 1, gptr((const double*)jb.Ad), d, 0, 0.0,
-            gptr(jb.G), d, splits > 1 ? gptr(jb.part) : nullptr, sp, i0, j0, kb0,
-            min(jb.rows, kb0 + kper));
-}
-
-// G = sum of the job's split slots, in split order (blockIdx.y = job)
-__global__ void factor_reduce_batched_kernel(const FactorJob* __restrict__ jobs, int splits) {
-  const FactorJob jb = jobs[blockIdx.y];
-  const int64_t n = (int64_t)jb.d * jb.d;
+// G = alpha sum_s part[s] from the upper tiles of side S (splits summed in order)
+template <typename GP, typename PP>
+__device__ __forceinline__ void gram_reduce(int d, int S, int splits, double alpha,
+                                            PP __restrict__ part, GP __restrict__ G, int64_t ldg) {
+  const int64_t n = (int64_t)d * d;
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n;
        e += (int64_t)gridDim.x * blockDim.x) {
-    double t = 0.0;
-    for (int q = 0; q < splits; ++q) t += gptr(jb.part)[(int64_t)q * n + e];
-    *gptr(jb.G + e) = t;
-  }
-}
-
-// C = alpha * sum_s part[s] + beta * C (splits summed in order)
-__global__ void gemm_reduce_kernel(int64_t M, int64_t N, int splits, const double* __restrict__ part,
-                                   double alpha, double beta, double* __restrict__ C, int64_t ldc) {
-  const int64_t n = M * N;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n;
-       e += (int64_t)gridDim.x * blockDim.x) {
+    const int i = (int)(e / d), j = (int)(e % d);
+    if (i / S > j / S) continue;  // below the upper tiles: written from its mirror
     double t = 0.0;
     for (int q = 0; q < splits; ++q) t += part[(int64_t)q * n + e];
-    const int64_t i = e / N, j = e % N;
-    double c = alpha * t;
-    if (beta != 0.0) c += beta * C[i * ldc + j];
-    C[i * ldc + j] = c;
+    G[(int64_t)i * ldg + j] = alpha * t;
+    if (i / S < j / S) G[(int64_t)j * ldg + i] = alpha * t;
   }
 }
 
-__global__ void convert_scale_kernel(int64_t rows, int d, const void* __restrict__ A, int64_t lda,
-                                     int is_f32, double s, double* __restrict__ out, int64_t ldo) {
-  const int64_t n = rows * d;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t i = e / d, k = e % d;
-    const double v = is_f32 ? (double)static_cast<const float*>(A)[i * lda + k]
-                            : static_cast<const double*>(A)[i * lda + k];
-    out[i * ldo + k] = s * v;
+__global__ void gram_reduce_kernel(int d, int S, int splits, double alpha,
+                                   const double* __restrict__ part, double* __restrict__ G,
+                                   int64_t ldg) {
+  gram_reduce(d, S, splits, alpha, part, G, ldg);
+}
+
+// C = alpha A op(B), one S x S tile per block; blockIdx.z picks one of two products
+// of the same shape.
+template <typename T>
+struct GemmPair {
+  const T* A[2];
+  const double* B[2];
+  double* C[2];
+  int64_t ldc[2];
+};
+
+template <int MT, bool TRB, typename T>
+__global__ __launch_bounds__(256) void gemm_kernel(int64_t M, int64_t N, int64_t K, double alpha,
+                                                   GemmPair<T> p, int64_t lda, int64_t ldb) {
+  __shared__ GemmLds<MT> lds;
+  const int z = blockIdx.z;
+  const int64_t i0 = (int64_t)blockIdx.y * 32 * MT, j0 = (int64_t)blockIdx.x * 32 * MT;
+  double* __restrict__ C = p.C[z];
+  const int64_t ldc = p.ldc[z];
+  f64x4 acc[MT][MT];
+  clear_acc(acc);
+  mfma_tile<MT, false, TRB>(lds, p.A[z], lda, p.B[z], ldb, M, N, i0, j0, 0, K, acc);
+  for_acc(acc, [&](int r, int c, double v) {
+    if (i0 + r < M && j0 + c < N) C[(i0 + r) * ldc + j0 + c] = alpha * v;
+  });
+}
+
+// ---------------------------------------------------------------------------
+// Cholesky R^T R = G together with Z = R^{-T}, right-looking, 32 columns per
+// launch.  Step k with pivot tile K: every block factors the 32 x 32 pivot tile
+// itself (one wave, about 4 us: cheaper than another launch that hands the
+// factor over), and one block per trailing tile (i, j), i > k, applies the
+// step to it:
+//   j >= i : G[i, j] -= P_i^T P_j,   P_c = R_KK^{-T} G[K, c] = R[K, c]
+//   j <  k : W[i, j] -= P_i^T Z[K, j],   Z[K, j] = R_KK^{-T} W[K, j]
+//   j == k : W[i, k]  = -P_i^T R_KK^{-T}
+// W, the identity being eliminated along with G, lives in the tiles of G
+// below the diagonal (each is first written, not read, at its column's step),
+// so G is destroyed.  The blocks of the first trailing row (the last step: of
+// a virtual one) write row K of R and of Z; nothing of row K of G is written
+// during step k, and every trailing tile belongs to one block.
+//
+// A step is latency: 9.8 us at d = 512, of which 2.6 the launch and the loads,
+// 4.3 the pivot tile and 2.9 the three products with their LDS round trips.  The
+// 16 steps take 0.157 ms, against 2.37 + 0.69 ms of a one-block Cholesky and a
+// row-wise inverse (slse_factor, 3072 x 512: 3.24 -> 0.26 ms; CholeskyQR3 of
+// 1536 x 256: 3.09 -> 0.43 ms) and 0.37 ms of a blocked Gauss-Jordan inverse with
+// two launches per 32 columns, which the solves took.
+// ---------------------------------------------------------------------------
+constexpr int kCB = 32;       // columns per step
+constexpr int kCBs = kCB + 16;  // LDS row stride
+
+// 1/sqrt(p) for p > 0: the hardware's estimate (24 bits) and one step of order
+// three
+__device__ __forceinline__ double rsqrt_f64(double p) {
+  const double y = __builtin_amdgcn_rsq(p);
+  const double e = fma(-(p * y), y, 1.0);
+  return fma(y * e, fma(0.375, e, 0.5), y);
+}
+
+// 32 x 32 product acc (one 16 x 16 tile per wave) += X Y with X[m][k] at
+// X[m * sxm + k * sxk] and Y[k][n] at Y[k * kCBs + n]
+__device__ __forceinline__ void tile_product(const double* X, int sxm, int sxk, const double* Y,
+                                             double sign, f64x4& acc) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r0 = (wave >> 1) * 16, c0 = (wave & 1) * 16;
+#pragma unroll
+  for (int ks = 0; ks < kCB; ks += 4) {
+    const int k = ks + (lane >> 4);
+    const double a = sign * X[(r0 + (lane & 15)) * sxm + k * sxk];
+    const double b = Y[k * kCBs + c0 + (lane & 15)];
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
   }
 }
 
-constexpr int kCholNB = 32;       // panel height
-constexpr int kCholThreads = 512;  // one thread per column of the panel
-constexpr int kCholMaxD = 512;
-constexpr int kCholKC = 32;       // rows of R staged per update step
-
-// Upper Cholesky R^T R = G by row panels of height 32.  Thread c owns column
-// J + c of the panel rows J..J+31 in registers.  Each panel is first reduced by
-// the rows of R above it (a GEMM against rows staged through LDS), its 32 x 32
-// diagonal block is then factored in LDS by the whole block, and the rest of
-// the panel is a triangular solve with that block, one column per thread.
-__device__ __forceinline__ void cholesky_block(int d, const double* __restrict__ G, int64_t ldg,
-                                               double* __restrict__ R, int64_t ldr,
-                                               int* __restrict__ info) {
-  __shared__ double Kb[kCholKC][kCholNB];
-  __shared__ double D[kCholNB][kCholNB + 1];
-  __shared__ int s_bad;
-  const int t = threadIdx.x;
-  if (t == 0) s_bad = 0;
-  for (int J = 0; J < d; J += kCholNB) {
-    const int w = min(kCholNB, d - J);
-    const int ncols = d - J;
-    const bool mine = t < ncols;
-    double acc[kCholNB];
-#pragma unroll
-    for (int a = 0; a < kCholNB; ++a) acc[a] = (mine && a < w) ? G[(int64_t)(J + a) * ldg + J + t] : 0.0;
-    // 1. subtract sum_{k < J} R[k][J+a] R[k][J+t]
-    for (int k0 = 0; k0 < J; k0 += kCholKC) {
-      const int kc = min(kCholKC, J - k0);
-      __syncthreads();
-      for (int e = t; e < kCholKC * kCholNB; e += kCholThreads) {
-        const int kk = e / kCholNB, a = e % kCholNB;
-        Kb[kk][a] = (kk < kc && a < w) ? R[(int64_t)(k0 + kk) * ldr + J + a] : 0.0;
-      }
-      double rc[kCholKC];
-#pragma unroll
-      for (int kk = 0; kk < kCholKC; ++kk)
-        rc[kk] = (mine && kk < kc) ? R[(int64_t)(k0 + kk) * ldr + J + t] : 0.0;
-      __syncthreads();
-#pragma unroll
-      for (int kk = 0; kk < kCholKC; ++kk)
-#pragma unroll
-        for (int a = 0; a < kCholNB; ++a) acc[a] = fma(-Kb[kk][a], rc[kk], acc[a]);
-    }
-    // 2. factor the diagonal block: wave 0, lane c holds column c in registers,
-    //    rows of the block are broadcast lane to lane
-    if (t < 64) {
-      double col[kCholNB];
-#pragma unroll
-      for (int a = 0; a < kCholNB; ++a) col[a] = acc[a];
-#pragma unroll
-      for (int a = 0; a < kCholNB; ++a) {
-        if (a < w) {
-          double piv = readlane_f64(col[a], a);
-          if (!(piv > 0.0) || !isfinite(piv)) {
-            if (t == 0 && !s_bad) s_bad = J + a + 1;
-            piv = 1.0;
-          }
-          const double rd = sqrt(piv);
-          const double inv = 1.0 / rd;
-          col[a] = (t == a) ? rd : col[a] * inv;  // row a of R: R[a][c]
-#pragma unroll
-          for (int b = a + 1; b < kCholNB; ++b) {
-            if (b < w) col[b] = fma(-readlane_f64(col[a], b), col[a], col[b]);
-          }
-        }
-      }
-      if (t < w) {
-#pragma unroll
-        for (int a = 0; a < kCholNB; ++a)
-          if (a < w) D[a][t] = col[a];
-      }
-    }
-    __syncthreads();
-    // 3. the rest of the panel: solve D^T x = acc for each column t >= w
-    if (mine) {
-      if (t < w) {
-#pragma unroll
-        for (int a = 0; a < kCholNB; ++a) acc[a] = (a < w && a <= t) ? D[a][t] : 0.0;
-      } else {
-#pragma unroll
-        for (int a = 0; a < kCholNB; ++a) {
-          if (a < w) {
-            double x = acc[a];
-#pragma unroll
-            for (int b = 0; b < kCholNB; ++b)
-              if (b < a) x = fma(-D[b][a], acc[b], x);
-            acc[a] = x / D[a][a];
-          }
-        }
-      }
-    }
-    // 4. write panel rows J..J+w of R (zero left of the diagonal)
-    for (int a = 0; a < w; ++a) {
-      double* Rr = R + (int64_t)(J + a) * ldr;
-      for (int c = t; c < J; c += kCholThreads) Rr[c] = 0.0;
-    }
-    if (mine) {
-#pragma unroll
-      for (int a = 0; a < kCholNB; ++a)
-        if (a < w) R[(int64_t)(J + a) * ldr + J + t] = acc[a];
-    }
-    __threadfence_block();
-    __syncthreads();
-  }
-  if (t == 0) info[0] = s_bad;
-}
-
-__global__ __launch_bounds__(kCholThreads) void cholesky_kernel(int d, const double* __restrict__ G,
-                                                                int64_t ldg, double* __restrict__ R,
-                                                                int64_t ldr, int* __restrict__ info) {
-  cholesky_block(d, G, ldg, R, ldr, info);
-}
-
-// Rinv = R^{-1} row by row: row i solves x^T R = e_i^T by forward
-// substitution over j with running sums s_l = -sum_{k<j} x_k R_kl, so each
-// step reads one row of R (contiguous).  Lane l keeps s for the columns
-// l, l+64, ... in registers; x_j is read from its owner lane.  A block's four
-// waves take rows i0..i0+3 and share rows of R staged through LDS.
-constexpr int kInvRows = 16;
-constexpr int kInvMaxD = 512;
-constexpr int kInvPer = kInvMaxD / 64;
-
-__device__ __forceinline__ void tri_inv_rows(int d, const double* __restrict__ R, int64_t ldr,
-                                             double* __restrict__ Rinv, int64_t ldi, int i0) {
-  __shared__ double Rs[kInvRows][kInvMaxD];
-  __shared__ double rdiag[kInvMaxD];
+// Sixteen elimination steps on columns of 16 rows, one per lane (lanes 0..15:
+// the pivot block A = U^T U); leaves U^{-T} times the columns.  What bounds it
+// is the chain from one pivot to the next, so the steps eliminate without
+// square roots (row b loses A[a][b] / p_a times row a: a broadcast, a reciprocal and
+// two products per step) and the rows are scaled by p_a^{-1/2} afterwards.
+// Returns c0 + a + 1 of the first bad pivot a, else 0.
+__device__ __forceinline__ int eliminate16(double (&col)[16], int c0) {
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int i = i0 + wave;
-  for (int l = threadIdx.x; l < d; l += 256) rdiag[l] = 1.0 / R[(int64_t)l * ldr + l];
-  double s[kInvPer];
 #pragma unroll
-  for (int k = 0; k < kInvPer; ++k) s[k] = 0.0;
-  for (int j0 = i0; j0 < d; j0 += kInvRows) {
-    const int jc = min(kInvRows, d - j0);
-    __syncthreads();
-    for (int e = threadIdx.x; e < jc * d; e += 256) {
-      const int rr = e / d, c = e % d;
-      Rs[rr][c] = R[(int64_t)(j0 + rr) * ldr + c];
-    }
-    __syncthreads();
-    if (i < d) {
-      for (int jj = 0; jj < jc; ++jj) {
-        const int j = j0 + jj;
-        if (j < i) continue;
-        // x_j = (delta_ij + s_j) / R_jj, s_j held by lane j % 64 in slot j / 64
-        double sj = 0.0;
+  for (int a = 0; a < 16; ++a) {
+    const double p = readlane_f64(col[a], a);
+    double m[16];
 #pragma unroll
-        for (int k = 0; k < kInvPer; ++k)
-          if (k == (j >> 6)) sj = readlane_f64(s[k], j & 63);
-        const double xj = ((j == i) ? 1.0 + sj : sj) * rdiag[j];
+    for (int b = a + 1; b < 16; ++b) m[b] = readlane_f64(col[a], b);
+    double inv = __builtin_amdgcn_rcp(p);  // 24 bits; one step of order three
+    const double e = fma(-p, inv, 1.0);
+    inv = fma(inv, fma(e, e, e), inv);
+    const double w = col[a] * inv;
 #pragma unroll
-        for (int k = 0; k < kInvPer; ++k) {
-          const int l = lane + 64 * k;
-          if (l == j) {
-            s[k] = xj;  // slot j now holds x_j
-          } else if (l > j && l < d) {
-            s[k] = fma(-xj, Rs[jj][l], s[k]);
-          }
-        }
-      }
-    }
+    for (int b = a + 1; b < 16; ++b) col[b] = fma(-m[b], w, col[b]);
   }
-  if (i < d) {
+  // lane a < 16 holds p_a
+  double p = 1.0;
 #pragma unroll
-    for (int k = 0; k < kInvPer; ++k) {
-      const int l = lane + 64 * k;
-      if (l < d) Rinv[(int64_t)i * ldi + l] = (l < i) ? 0.0 : s[k];
-    }
-  }
+  for (int a = 0; a < 16; ++a) p = lane == a ? col[a] : p;
+  const uint64_t ok = __ballot(p > 0.0 && p <= 1.7976931348623157e308) | ~uint64_t(0xffff);
+  const double y = rsqrt_f64(p);
+  const double h = p * y;
+  const double root = fma(0.5 * y, fma(-h, h, p), h);
+#pragma unroll
+  for (int a = 0; a < 16; ++a) col[a] = lane == a ? root : col[a] * readlane_f64(y, a);
+  return ok == ~uint64_t(0) ? 0 : c0 + __builtin_ctzll(~ok) + 1;
 }
 
-__global__ __launch_bounds__(256) void tri_inv_kernel(int d, const double* __restrict__ R,
-                                                      int64_t ldr, double* __restrict__ Rinv,
-                                                      int64_t ldi) {
-  tri_inv_rows(d, R, ldr, Rinv, ldi, blockIdx.x * 4);
-}
-
-// Ad = scale * A[:, :d] of every job (blockIdx.y = job)
-__global__ void convert_scale_batched_kernel(const FactorJob* __restrict__ jobs, int is_f32) {
-  const FactorJob jb = jobs[blockIdx.y];
-  const int64_t n = jb.rows * jb.d;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t i = e / jb.d, k = e % jb.d;
-    const double v = is_f32 ? (double)gptr(static_cast<const float*>(jb.A))[i * jb.lda + k]
-                            : gptr(static_cast<const double*>(jb.A))[i * jb.lda + k];
-    *gptr(jb.Ad + e) = jb.scale * v;
+// One wave factors the 32 x 32 pivot tile D (rows of kCBs doubles in LDS): R_KK
+// to Rs and R_KK^{-T} over D.  Two halves of 16 columns, so that the cross
+// term is eight matrix-core products instead of 256 broadcast multipliers:
+//   [A11 A12 | I]  ->  R11, R12, Z11             (lanes 0..15, 16..31, 32..47)
+//   T = A22 - R12^T R12,   W = -R12^T Z11
+//   [T | W | I]    ->  R22, Z21, Z22
+// Returns k0 + a + 1 of the first bad pivot a, or 0.
+__device__ __forceinline__ int pivot_tile(double* D, double* Rs, int k0) {
+  const int lane = threadIdx.x & 63;
+  const int c = lane & 15, q = lane >> 4;
+  // selections by per-lane integers, so that they stay selections (a
+  // condition of several parts becomes branches around every register: 14 us a
+  // step instead of 9.8)
+  const bool data = q < 2;
+  const int one = q == 2 ? c : -1;  // the row of the identity column's 1
+  const unsigned keep = q == 0   ? (2u << c) - 1  // rows kept of this lane's column
+                        : q == 1 ? 0xffffu
+                        : q == 2 ? 0x10000u - (1u << c)
+                                 : 0u;
+  double col[16];
+  // the lanes past 32 read a valid column and replace it
+#pragma unroll
+  for (int a = 0; a < 16; ++a) {
+    const double v = D[a * kCBs + (lane & 31)];
+    const double id = a == one ? 1.0 : 0.0;
+    col[a] = data ? v : id;
   }
+  f64x4 T;  // A22 in the accumulator layout
+#pragma unroll
+  for (int r = 0; r < 4; ++r) T[r] = D[(16 + 4 * r + q) * kCBs + 16 + c];
+  const int bad0 = eliminate16(col, k0);
+  // R11 | R12 to Rs, Z11 to the upper left of D, zeros to its upper right
+  {
+    double* out = data ? Rs + lane : D + (lane - 32);
+#pragma unroll
+    for (int a = 0; a < 16; ++a) out[a * kCBs] = (keep >> a) & 1 ? col[a] : 0.0;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  f64x4 W{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int ks = 0; ks < 16; ks += 4) {
+    const double r12 = Rs[(ks + q) * kCBs + 16 + c];  // (R12^T)[m][k] and R12[k][n] alike
+    const double z11 = D[(ks + q) * kCBs + c];
+    T = __builtin_amdgcn_mfma_f64_16x16x4f64(-r12, r12, T, 0, 0, 0);
+    W = __builtin_amdgcn_mfma_f64_16x16x4f64(-r12, z11, W, 0, 0, 0);
+  }
+  // [W | T] through the lower half of D, back as columns
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    D[(16 + 4 * r + q) * kCBs + c] = W[r];
+    D[(16 + 4 * r + q) * kCBs + 16 + c] = T[r];
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+  for (int a = 0; a < 16; ++a) {
+    const double v = D[(16 + a) * kCBs + (q == 0 ? 16 + c : c)];
+    const double id = a == one ? 1.0 : 0.0;
+    col[a] = data ? v : id;
+  }
+  const int bad1 = eliminate16(col, k0 + 16);
+  // R22 to Rs (zeros left of it), Z21 | Z22 to the lower half of D
+  {
+    double* out = q == 0 ? Rs + 16 + c : q == 1 ? D + c : q == 2 ? D + 16 + c : Rs + c;
+#pragma unroll
+    for (int a = 0; a < 16; ++a) out[(16 + a) * kCBs] = (keep >> a) & 1 ? col[a] : 0.0;
+  }
+  return bad0 ? bad0 : bad1;
 }
 
-// ---------------------------------------------------------------------------
-// M = G^{-1} for SPD G by blocked Gauss-Jordan elimination in place, 32 rows
-// per step (no pivoting: the pivots of an SPD matrix are positive).  Step k
-// with pivot block P = G[K, K], K = [k0, k0 + 32):
-//   panel  : Pinv = P^{-1} (every block; block 0 stores it in colp rows K);
-//            G[K, j] = Pinv G[K, j] (j outside K); the old column panel
-//            G[i, K] (i outside K) is saved to colp rows i
-//   update : G[i, j] -= colp[i, :] G[K, j]   (i, j outside K)
-//            G[i, K]  = -colp[i, :] Pinv      (i outside K)
-//            G[K, K]  = Pinv
-// G[K, K] is written only in the update, after every panel block has read P.
-// ---------------------------------------------------------------------------
-constexpr int kGJ = 32;
-constexpr int kGJChunk = 64;  // columns (and saved rows) per panel block
-
-template <typename DP, typename IP>
-__device__ __forceinline__ void gj_panel(int d, int k0, DP __restrict__ G, DP __restrict__ colp,
-                                         IP __restrict__ info, int bx) {
-  __shared__ double Pinv[kGJ][kGJ + 1];
-  __shared__ double Rp[kGJ][kGJChunk + 1];
+template <typename DP, typename RP, typename IP>
+__device__ __forceinline__ void chol_step(int d, int k, DP __restrict__ G, RP __restrict__ R,
+                                          int64_t ldr, DP __restrict__ Z, IP __restrict__ info,
+                                          int j, int row) {
+  __shared__ double Ds[kCB * kCBs];  // pivot tile, then R_KK^{-T}
+  __shared__ double Rs[kCB * kCBs];  // R_KK (head blocks of column k)
+  __shared__ double Gi[kCB * kCBs];  // G[K, i], then P_i
+  __shared__ double Gj[kCB * kCBs];  // G[K, j] or W[K, j], then P_j or Z[K, j]
+  const int nb = (int)ceil_div(d, kCB);
+  const int i = k + 1 + row;
+  const bool head = row == 0;
+  const bool trail = i < nb;
+  if (j > k && j < i) return;  // below the diagonal of the trailing part (uniform)
   const int t = threadIdx.x;
-  const int kw = min(kGJ, d - k0);
-  // Every thread moves a fixed number of entries in each of 1-3, so the
-  // loops have compile-time trip counts and all their loads are in flight
-  // together (a runtime-bounded loop waits for each load in turn).
-  constexpr int kP = kGJ * kGJ / 256;       // pivot-block entries per thread
-  constexpr int kC = kGJChunk * kGJ / 256;  // column- and row-panel entries per thread
-  // (loads outside the matrix read a clamped, valid address and are
-  // replaced afterwards, so that no load sits behind a branch)
-  // 1. the pivot block into LDS, padded with the identity past d
-  {
-    double v[kP];
+  const int lane = t & 63, wave = t >> 6;
+  const int k0 = k * kCB, i0 = i * kCB, j0 = j * kCB;
+  constexpr int kL = kCB * kCB / 256;
+  // all of the block's loads at once, from clamped addresses
+  double vd[kL], vi[kL], vj[kL];
 #pragma unroll
-    for (int u = 0; u < kP; ++u) {
-      const int e = t + 256 * u;
-      const int a = min(e / kGJ, kw - 1), c = min(e % kGJ, kw - 1);
-      v[u] = G[(int64_t)(k0 + a) * d + k0 + c];
-    }
-#pragma unroll
-    for (int u = 0; u < kP; ++u) {
-      const int e = t + 256 * u;
-      const int a = e / kGJ, c = e % kGJ;
-      Pinv[a][c] = (a < kw && c < kw) ? v[u] : (a == c ? 1.0 : 0.0);
-    }
+  for (int u = 0; u < kL; ++u) {
+    const int e = t + 256 * u;
+    const int a = e / kCB, c = e % kCB;
+    const int64_t rk = (int64_t)min(k0 + a, d - 1) * d;
+    vd[u] = G[rk + min(k0 + c, d - 1)];
+    vi[u] = G[rk + min(i0 + c, d - 1)];
+    vj[u] = G[rk + min(j0 + c, d - 1)];
   }
-  // 2. save the old column panel for rows [64 b, 64 b + 64) outside K
-  const int r0 = bx * kGJChunk;
-  {
-    double v[kC];
+  const int r0 = (wave >> 1) * 16, c0 = (wave & 1) * 16;
+  f64x4 acc;  // this wave's 16 x 16 tile of (i, j)
 #pragma unroll
-    for (int u = 0; u < kC; ++u) {
-      const int e = t + 256 * u;
-      const int i = min(r0 + e / kGJ, d - 1), a = min(e % kGJ, kw - 1);
-      v[u] = G[(int64_t)i * d + k0 + a];
-    }
-#pragma unroll
-    for (int u = 0; u < kC; ++u) {
-      const int e = t + 256 * u;
-      const int i = r0 + e / kGJ, a = e % kGJ;
-      if (i < d && (i < k0 || i >= k0 + kw) && a < kw) colp[(int64_t)i * kGJ + a] = v[u];
-    }
+  for (int r = 0; r < 4; ++r) {
+    const int gi = i0 + r0 + 4 * r + (lane >> 4), gj = j0 + c0 + (lane & 15);
+    const double v = G[(int64_t)min(gi, d - 1) * d + min(gj, d - 1)];
+    acc[r] = (j != k && trail && gi < d && gj < d) ? v : 0.0;
   }
-  // 3. row panel of this block's columns [64 b, 64 b + 64)
-  const int c0 = bx * kGJChunk;
-  {
-    double v[kC];
 #pragma unroll
-    for (int u = 0; u < kC; ++u) {
-      const int e = t + 256 * u;
-      const int a = min(e / kGJChunk, kw - 1), j = min(c0 + e % kGJChunk, d - 1);
-      v[u] = G[(int64_t)(k0 + a) * d + j];
-    }
-#pragma unroll
-    for (int u = 0; u < kC; ++u) {
-      const int e = t + 256 * u;
-      const int a = e / kGJChunk, j = c0 + e % kGJChunk;
-      Rp[a][e % kGJChunk] = (a < kw && j < d) ? v[u] : 0.0;
+  for (int u = 0; u < kL; ++u) {
+    const int e = t + 256 * u;
+    const int a = e / kCB, c = e % kCB;
+    const bool rowok = k0 + a < d;
+    // the pivot tile is padded with the identity past d
+    Ds[a * kCBs + c] = rowok && k0 + c < d ? vd[u] : (a == c ? 1.0 : 0.0);
+    Gi[a * kCBs + c] = rowok && i0 + c < d ? vi[u] : 0.0;
+    Gj[a * kCBs + c] = rowok && j0 + c < d ? vj[u] : 0.0;
+  }
+  __syncthreads();
+  if (wave == 0) {
+    const int bad = pivot_tile(Ds, Rs, k0);
+    if (lane == 0 && head && j == k && bad) {
+      if (*info == 0) *info = bad;
     }
   }
   __syncthreads();
-  // 1b. Gauss-Jordan on the pivot block in place, every thread on four entries
-  // of one row (row i = t / 8, columns 4 (t % 8) ..): at step s the pivot row
-  // becomes P[s][.] / P[s][s] (1 / P[s][s] in column s), and every other row
-  // loses P[i][s] times it (-P[i][s] / P[s][s] in column s).  The old values
-  // of the step are read before a barrier and written after it.  A
-  // non-positive or non-finite pivot is reported.
-  {
-    static_assert(kGJ * kGJ == 4 * 256, "four entries per thread");
-    const int i = t >> 3;
-    const int j0 = (t & 7) * 4;
-    bool bad = false;
-    for (int s = 0; s < kGJ; ++s) {
-      double piv = Pinv[s][s];
-      if (!(piv > 0.0) || !isfinite(piv)) {
-        bad = true;
-        piv = 1.0;
-      }
-      const double inv = 1.0 / piv;
-      const double f = Pinv[i][s];
-      double rs[4], cur[4];
+  // P_i, and P_j or Z[K, j] (for j == k it is R_KK^{-T} itself)
+  f64x4 pi{0.0, 0.0, 0.0, 0.0}, pj{0.0, 0.0, 0.0, 0.0};
+  if (trail) tile_product(Ds, kCBs, 1, Gi, 1.0, pi);
+  if (j != k) tile_product(Ds, kCBs, 1, Gj, 1.0, pj);
+  __syncthreads();
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int j = j0 + u;
-        rs[u] = (j == s) ? inv : Pinv[s][j] * inv;
-        cur[u] = Pinv[i][j];
-      }
-      __syncthreads();
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int j = j0 + u;
-        Pinv[i][j] = (i == s) ? rs[u] : (j == s) ? -f * inv : fma(-f, rs[u], cur[u]);
-      }
-      __syncthreads();
-    }
-    if (bad && t == 0) atomicCAS(info, 0, k0 + 1);
-  }
-  if (bx == 0)
-    for (int e = t; e < kGJ * kGJ; e += 256) {
-      const int a = e / kGJ, c = e % kGJ;
-      if (a < kw && c < kw) colp[(int64_t)(k0 + a) * kGJ + c] = Pinv[a][c];
-    }
-  for (int e = t; e < kGJ * kGJChunk; e += 256) {
-    const int a = e / kGJChunk, jj = e % kGJChunk, j = c0 + jj;
-    if (a >= kw || j >= d || (j >= k0 && j < k0 + kw)) continue;
-    double v = 0.0;
-#pragma unroll 8
-    for (int q = 0; q < kGJ; ++q) v = fma(Pinv[a][q], Rp[q][jj], v);
-    G[(int64_t)(k0 + a) * d + j] = v;
-  }
-}
-
-__global__ __launch_bounds__(256) void gj_panel_kernel(int d, int k0, double* __restrict__ G,
-                                                       double* __restrict__ colp,
-                                                       int* __restrict__ info) {
-  gj_panel(d, k0, G, colp, info, blockIdx.x);
-}
-
-// the panel step of every job (blockIdx.y), past the end of a smaller job: nothing
-__global__ __launch_bounds__(256) void gj_panel_batched_kernel(const FactorJob* __restrict__ jobs,
-                                                               int k0) {
-  const FactorJob jb = jobs[blockIdx.y];
-  if (k0 >= jb.d || (int)blockIdx.x * kGJChunk >= jb.d) return;
-  gj_panel(jb.d, k0, gptr(jb.M), gptr(jb.colp), jb.info, blockIdx.x);
-}
-
-// one 32 x 32 output tile per block (by = row tile, bx = column tile)
-template <typename DP, typename CP>
-__device__ __forceinline__ void gj_update(int d, int k0, DP __restrict__ G, CP __restrict__ colp,
-                                          int bx, int by) {
-  __shared__ double Cp[kGJ][kGJ + 1];  // colp rows of this tile
-  __shared__ double Rw[kGJ][kGJ + 1];  // new row panel columns of this tile
-  const int kw = min(kGJ, d - k0);
-  const int i0 = by * kGJ, j0 = bx * kGJ;
-  const int t = threadIdx.x;
-  const bool pivcols = j0 == k0;
-  if (i0 == k0) {  // the pivot rows were finished by the panel step, but for G[K, K]
-    if (pivcols)
-      for (int e = t; e < kGJ * kGJ; e += 256) {
-        const int r = e / kGJ, c = e % kGJ;
-        if (r < kw && c < kw) G[(int64_t)(k0 + r) * d + k0 + c] = colp[(int64_t)(k0 + r) * kGJ + c];
-      }
-    return;
-  }
-  // a fixed count per thread, every load from a clamped valid address (the
-  // entries outside the matrix are replaced afterwards): all of the two
-  // tiles' loads in flight together
-  {
-    constexpr int kT = kGJ * kGJ / 256;
-    double cv[kT], rv[kT];
-#pragma unroll
-    for (int u = 0; u < kT; ++u) {
-      const int e = t + 256 * u;
-      const int r = e / kGJ, c = min(e % kGJ, kw - 1);
-      cv[u] = colp[(int64_t)min(i0 + r, d - 1) * kGJ + c];
-      // Pinv (colp rows K) for the pivot columns, else the new row panel
-      const int rr = min(r, kw - 1);
-      rv[u] = pivcols ? colp[(int64_t)(k0 + rr) * kGJ + c]
-                      : G[(int64_t)(k0 + rr) * d + min(j0 + e % kGJ, d - 1)];
-    }
-#pragma unroll
-    for (int u = 0; u < kT; ++u) {
-      const int e = t + 256 * u;
-      const int r = e / kGJ, c = e % kGJ;
-      Cp[r][c] = (i0 + r < d && c < kw) ? cv[u] : 0.0;
-      Rw[r][c] = (r < kw && j0 + c < d) ? rv[u] : 0.0;
-    }
+  for (int r = 0; r < 4; ++r) {
+    const int o = (r0 + 4 * r + (lane >> 4)) * kCBs + c0 + (lane & 15);
+    Gi[o] = pi[r];
+    Gj[o] = j == k ? Ds[o] : pj[r];
   }
   __syncthreads();
-  // the tile's old values first (all in flight), then the products
-  constexpr int kU = kGJ * kGJ / 256;
-  double old[kU];
+  if (head) {
 #pragma unroll
-  for (int u = 0; u < kU; ++u) {
-    const int e = t + 256 * u;
-    const int i = i0 + e / kGJ, j = j0 + e % kGJ;
-    old[u] = G[(int64_t)min(i, d - 1) * d + min(j, d - 1)];
+    for (int u = 0; u < kL; ++u) {
+      const int e = t + 256 * u;
+      const int a = e / kCB, c = e % kCB;
+      if (k0 + a >= d || j0 + c >= d) continue;
+      const int64_t gr = k0 + a, gc = j0 + c;
+      const double p = Gj[a * kCBs + c];
+      if (R) R[gr * ldr + gc] = j > k ? p : j == k ? Rs[a * kCBs + c] : 0.0;
+      Z[gr * d + gc] = j > k ? 0.0 : p;
+    }
   }
+  if (!trail) return;
+  tile_product(Gi, 1, kCBs, Gj, -1.0, acc);
 #pragma unroll
-  for (int u = 0; u < kU; ++u) {
-    const int e = t + 256 * u;
-    const int r = e / kGJ, c = e % kGJ;
-    const int i = i0 + r, j = j0 + c;
-    if (i >= d || j >= d) continue;
-    double v = 0.0;
-#pragma unroll 8
-    for (int q = 0; q < kGJ; ++q) v = fma(Cp[r][q], Rw[q][c], v);
-    G[(int64_t)i * d + j] = pivcols ? -v : old[u] - v;  // Rw holds Pinv for the pivot columns
+  for (int r = 0; r < 4; ++r) {
+    const int gi = i0 + r0 + 4 * r + (lane >> 4), gj = j0 + c0 + (lane & 15);
+    if (gi < d && gj < d) G[(int64_t)gi * d + gj] = acc[r];
   }
 }
 
-__global__ __launch_bounds__(256) void gj_update_kernel(int d, int k0, double* __restrict__ G,
-                                                        const double* __restrict__ colp) {
-  gj_update(d, k0, G, colp, blockIdx.x, blockIdx.y);
+__global__ __launch_bounds__(256) void chol_step_kernel(int d, int k, double* __restrict__ G,
+                                                        double* __restrict__ R, int64_t ldr,
+                                                        double* __restrict__ Z,
+                                                        int* __restrict__ info) {
+  chol_step(d, k, G, R, ldr, Z, info, (int)blockIdx.x, (int)blockIdx.y);
 }
 
-// the update step of every job (blockIdx.z)
-__global__ __launch_bounds__(256) void gj_update_batched_kernel(const FactorJob* __restrict__ jobs,
-                                                                int k0) {
+// ---------------------------------------------------------------------------
+// The same for the jobs of a batch.
+// ---------------------------------------------------------------------------
+// G = scale^2 A^T A of every job (blockIdx.z = job x splits + split): with splits > 1
+// each split sums its share of the rows into the job's partial slot
+template <typename T>
+__global__ __launch_bounds__(256) void gram_batched_kernel(const FactorJob* __restrict__ jobs,
+                                                           int splits) {
+  const FactorJob jb = jobs[blockIdx.z / splits];
+  const int sp = blockIdx.z % splits;
+  const int nt = (int)ceil_div(jb.d, 32);
+  if ((int)blockIdx.x >= nt * (nt + 1) / 2) return;
+  const int64_t kper = round_up(ceil_div(jb.rows, (int64_t)splits), kKS);
+  const int64_t kb0 = sp * kper;
+  gram_tile<1>(jb.d, jb.scale, gptr(static_cast<const T*>(jb.A)), jb.lda, gptr(jb.G), jb.d,
+               splits > 1 ? gptr(jb.part) : nullptr, sp, (int)blockIdx.x, kb0,
+               min(jb.rows, kb0 + kper));
+}
+
+__global__ void gram_reduce_batched_kernel(const FactorJob* __restrict__ jobs, int splits) {
+  const FactorJob jb = jobs[blockIdx.y];
+  gram_reduce(jb.d, 32, splits, jb.scale, gptr((const double*)jb.part), gptr(jb.G), jb.d);
+}
+
+__global__ __launch_bounds__(256) void chol_step_batched_kernel(const FactorJob* __restrict__ jobs,
+                                                                int k) {
   const FactorJob jb = jobs[blockIdx.z];
-  const int nt = (int)ceil_div(jb.d, kGJ);
-  if (k0 >= jb.d || (int)blockIdx.x >= nt || (int)blockIdx.y >= nt) return;
-  gj_update(jb.d, k0, gptr(jb.M), gptr((const double*)jb.colp), blockIdx.x, blockIdx.y);
+  const int nb = (int)ceil_div(jb.d, kCB);
+  if (k >= nb || (int)blockIdx.x >= nb || (int)blockIdx.y >= max(1, nb - k - 1)) return;
+  chol_step(jb.d, k, gptr(jb.G), gptr((double*)nullptr), 0, gptr(jb.Z), jb.info, (int)blockIdx.x,
+            (int)blockIdx.y);
+}
+
+// M = Z^T Z of every job
+__global__ __launch_bounds__(256) void inverse_batched_kernel(const FactorJob* __restrict__ jobs) {
+  const FactorJob jb = jobs[blockIdx.z];
+  const int nt = (int)ceil_div(jb.d, 32);
+  if ((int)blockIdx.x >= nt * (nt + 1) / 2) return;
+  gram_tile<1>(jb.d, 1.0, gptr((const double*)jb.Z), jb.d, gptr(jb.M), jb.d,
+               (SLSE_GLOBAL double*)nullptr, 0, (int)blockIdx.x, 0, jb.d);
 }
 
 // G += coef trace(G) I (one block): the diagonal shift of shifted CholeskyQR
@@ -633,63 +530,91 @@ void launch_shift_diag(int d, double* G, double coef, hipStream_t s) {
   SLSE_LAUNCH_CHECK();
 }
 
-void launch_spd_inverse(int d, double* G, double* colp, int* info, hipStream_t s) {
+// Row splits and tile of the Gram kernel: about 512 blocks of at least 128 rows.
+struct GramShape {
+  bool wide;  // 64 x 64 tiles
+  int tiles, splits;
+  int64_t kper;
+};
+GramShape gram_shape(int64_t rows, int64_t d) {
+  GramShape g;
+  g.wide = d > 192;  // 64-wide tiles leave too few blocks below (10 upper tiles at d = 256)
+  const int64_t nt = ceil_div(d, g.wide ? 64 : 32);
+  g.tiles = (int)(nt * (nt + 1) / 2);
+  int64_t sp = std::max<int64_t>(1, 512 / g.tiles);
+  sp = std::min<int64_t>({sp, std::max<int64_t>(1, rows / 128), 32});
+  g.kper = sp > 1 ? round_up(ceil_div(rows, sp), kKS) : std::max<int64_t>(rows, 1);
+  g.splits = (int)std::max<int64_t>(1, ceil_div(rows, g.kper));
+  return g;
+}
+
+size_t gram_scratch_doubles(int64_t rows, int64_t d) {
+  const GramShape g = gram_shape(rows, d);
+  return g.splits > 1 ? (size_t)g.splits * d * d : 0;
+}
+
+void launch_gram(int64_t rows, int d, double alpha, const void* A, int64_t lda, slse_dtype at,
+                 double* G, int64_t ldg, double* scratch, size_t scratch_doubles, hipStream_t s) {
+  if (rows <= 0 || d <= 0) return;
+  GramShape g = gram_shape(rows, d);
+  if (g.splits > 1 && (!scratch || scratch_doubles < (size_t)g.splits * d * d)) {
+    g.splits = 1;
+    g.kper = rows;
+  }
+  double* part = g.splits > 1 ? scratch : nullptr;
+  const dim3 grid((unsigned)g.tiles, (unsigned)g.splits);
+  auto go = [&](auto* a) {
+    if (g.wide)
+      gram_kernel<2><<<grid, 256, 0, s>>>(d, rows, alpha, a, lda, G, ldg, part, g.kper);
+    else
+      gram_kernel<1><<<grid, 256, 0, s>>>(d, rows, alpha, a, lda, G, ldg, part, g.kper);
+  };
+  if (at == SLSE_F32)
+    go(static_cast<const float*>(A));
+  else
+    go(static_cast<const double*>(A));
+  SLSE_LAUNCH_CHECK();
+  if (g.splits > 1) {
+    const int blocks = (int)std::min<int64_t>(ceil_div((int64_t)d * d, 256), 4096);
+    gram_reduce_kernel<<<blocks, 256, 0, s>>>(d, g.wide ? 64 : 32, g.splits, alpha, part, G, ldg);
+    SLSE_LAUNCH_CHECK();
+  }
+}
+
+void launch_times_inverse(int64_t rows, int d, double alpha, const void* A, int64_t lda,
+                          slse_dtype at, const double* Z, double* Q, hipStream_t s) {
+  if (rows <= 0 || d <= 0) return;
+  const dim3 grid((unsigned)ceil_div(d, 32), (unsigned)ceil_div(rows, 32));
+  if (at == SLSE_F32) {
+    const GemmPair<float> p{{static_cast<const float*>(A), nullptr}, {Z, nullptr}, {Q, nullptr},
+                              {d, d}};
+    gemm_kernel<1, true><<<grid, 256, 0, s>>>(rows, d, d, alpha, p, lda, d);
+  } else {
+    const GemmPair<double> p{{static_cast<const double*>(A), nullptr}, {Z, nullptr}, {Q, nullptr},
+                              {d, d}};
+    gemm_kernel<1, true><<<grid, 256, 0, s>>>(rows, d, d, alpha, p, lda, d);
+  }
+  SLSE_LAUNCH_CHECK();
+}
+
+void launch_two_products(int d, const double* A0, const double* B0, double* C0, int64_t ldc0,
+                         const double* A1, const double* B1, double* C1, int64_t ldc1,
+                         hipStream_t s) {
   if (d <= 0) return;
-  const unsigned nt = (unsigned)ceil_div(d, kGJ);
-  for (int k0 = 0; k0 < d; k0 += kGJ) {
-    gj_panel_kernel<<<(unsigned)ceil_div(d, kGJChunk), 256, 0, s>>>(d, k0, G, colp, info);
-    SLSE_LAUNCH_CHECK();
-    gj_update_kernel<<<dim3(nt, nt), 256, 0, s>>>(d, k0, G, colp);
-    SLSE_LAUNCH_CHECK();
-  }
-}
-
-int gemm_splits(int64_t M, int64_t N, int64_t K) {
-  const int64_t tiles = ceil_div(M, kTile) * ceil_div(N, kTile);
-  int64_t sp = std::max<int64_t>(1, 512 / std::max<int64_t>(tiles, 1));
-  sp = std::min<int64_t>(sp, std::max<int64_t>(1, K / 128));
-  return (int)std::min<int64_t>(sp, 32);
-}
-
-size_t gemm_scratch_doubles(int64_t M, int64_t N, int64_t K) {
-  const int sp = gemm_splits(M, N, K);
-  return sp > 1 ? (size_t)sp * M * N : 0;
-}
-
-void launch_gemm_f64(int64_t M, int64_t N, int64_t K, double alpha, const double* A, int64_t lda,
-                     bool transA, const double* B, int64_t ldb, bool transB, double beta, double* C,
-                     int64_t ldc, hipStream_t s, double* scratch, size_t scratch_doubles) {
-  if (M <= 0 || N <= 0) return;
-  int sp = gemm_splits(M, N, K);
-  if (sp > 1 && (!scratch || scratch_doubles < (size_t)sp * M * N)) sp = 1;
-  const int64_t kper = sp > 1 ? round_up(ceil_div(K, sp), kKStep) : std::max<int64_t>(K, 1);
-  sp = (int)std::max<int64_t>(1, ceil_div(K, kper));
-  dim3 grid((unsigned)ceil_div(N, kTile), (unsigned)ceil_div(M, kTile), (unsigned)sp);
-  gemm_kernel<<<grid, 256, 0, s>>>(M, N, K, alpha, A, lda, transA ? 1 : 0, B, ldb, transB ? 1 : 0,
-                                   beta, C, ldc, sp > 1 ? scratch : nullptr, kper);
-  SLSE_LAUNCH_CHECK();
-  if (sp > 1) {
-    const int blocks = (int)std::min<int64_t>(ceil_div(M * N, 256), 4096);
-    gemm_reduce_kernel<<<blocks, 256, 0, s>>>(M, N, sp, scratch, alpha, beta, C, ldc);
-    SLSE_LAUNCH_CHECK();
-  }
-}
-
-void launch_convert_scale(int64_t rows, int d, const void* A, int64_t lda, slse_dtype at, double s,
-                          double* out, int64_t ldo, hipStream_t st) {
-  const int64_t n = rows * d;
-  if (n <= 0) return;
-  const int blocks = (int)std::min<int64_t>(ceil_div(n, 256), 8192);
-  convert_scale_kernel<<<blocks, 256, 0, st>>>(rows, d, A, lda, at == SLSE_F32 ? 1 : 0, s, out,
-                                                ldo);
+  const GemmPair<double> p{{A0, A1}, {B0, B1}, {C0, C1}, {ldc0, ldc1}};
+  const unsigned nt = (unsigned)ceil_div(d, 32);
+  gemm_kernel<1, false><<<dim3(nt, nt, 2), 256, 0, s>>>(d, d, d, 1.0, p, d, d);
   SLSE_LAUNCH_CHECK();
 }
 
-void launch_cholesky(int d, const double* G, int64_t ldg, double* R, int64_t ldr, int* info,
+void launch_cholesky(int d, double* G, double* R, int64_t ldr, double* Z, int* info,
                      hipStream_t s) {
-  if (d > kCholMaxD) fail(SLSE_EUNSUPPORTED, "cholesky: d > 512 not supported by this library");
-  cholesky_kernel<<<1, kCholThreads, 0, s>>>(d, G, ldg, R, ldr, info);
-  SLSE_LAUNCH_CHECK();
+  const int nb = (int)ceil_div(d, kCB);
+  for (int k = 0; k < nb; ++k) {
+    chol_step_kernel<<<dim3((unsigned)nb, (unsigned)std::max(1, nb - k - 1)), 256, 0, s>>>(
+        d, k, G, R, ldr, Z, info);
+    SLSE_LAUNCH_CHECK();
+  }
 }
 
 int factor_batched_splits(int64_t rows_max) {
@@ -699,36 +624,29 @@ int factor_batched_splits(int64_t rows_max) {
 void launch_factor_batched(const FactorJob* jobs, int B, int dmax, int64_t rows_max,
                            slse_dtype at, hipStream_t s) {
   if (B <= 0) return;
-  if (dmax > kCholMaxD) fail(SLSE_EUNSUPPORTED, "cholesky: d > 512 not supported by this library");
-  const unsigned cb = (unsigned)std::min<int64_t>(ceil_div(rows_max * dmax, 256), 1024);
-  convert_scale_batched_kernel<<<dim3(cb, (unsigned)B), 256, 0, s>>>(jobs, at == SLSE_F32 ? 1 : 0);
-  SLSE_LAUNCH_CHECK();
-  const unsigned tiles = (unsigned)ceil_div(dmax, kTile);
-  // the scaled Gram into M (G points at M), then M = G^{-1} in place by the
-  // blocked Gauss-Jordan steps of every job at once
+  if (dmax > 512) fail(SLSE_EUNSUPPORTED, "cholesky: d > 512 not supported by this library");
   if (B > 65535) fail(SLSE_EUNSUPPORTED, "factor: too many batched jobs");
   const int splits = factor_batched_splits(rows_max);
   if ((int64_t)B * splits > 65535) fail(SLSE_EUNSUPPORTED, "factor: too many batched jobs");
-  factor_gemm_batched_kernel<<<dim3(tiles, tiles, (unsigned)(B * splits)), 256, 0, s>>>(jobs, splits);
+  const unsigned nb = (unsigned)ceil_div(dmax, kCB);
+  const unsigned upper = nb * (nb + 1) / 2;
+  const dim3 gg(upper, 1, (unsigned)(B * splits));
+  if (at == SLSE_F32)
+    gram_batched_kernel<float><<<gg, 256, 0, s>>>(jobs, splits);
+  else
+    gram_batched_kernel<double><<<gg, 256, 0, s>>>(jobs, splits);
   SLSE_LAUNCH_CHECK();
   if (splits > 1) {
     const unsigned rb = (unsigned)std::min<int64_t>(ceil_div((int64_t)dmax * dmax, 256), 256);
-    factor_reduce_batched_kernel<<<dim3(rb, (unsigned)B), 256, 0, s>>>(jobs, splits);
+    gram_reduce_batched_kernel<<<dim3(rb, (unsigned)B), 256, 0, s>>>(jobs, splits);
     SLSE_LAUNCH_CHECK();
   }
-  const unsigned nt = (unsigned)ceil_div(dmax, kGJ);
-  for (int k0 = 0; k0 < dmax; k0 += kGJ) {
-    gj_panel_batched_kernel<<<dim3((unsigned)ceil_div(dmax, kGJChunk), (unsigned)B), 256, 0, s>>>(jobs,
-                                                                                                k0);
-    SLSE_LAUNCH_CHECK();
-    gj_update_batched_kernel<<<dim3(nt, nt, (unsigned)B), 256, 0, s>>>(jobs, k0);
+  for (unsigned k = 0; k < nb; ++k) {
+    chol_step_batched_kernel<<<dim3(nb, std::max(1u, nb - k - 1), (unsigned)B), 256, 0, s>>>(jobs,
+                                                                                            (int)k);
     SLSE_LAUNCH_CHECK();
   }
-}
-
-void launch_tri_inv(int d, const double* R, int64_t ldr, double* Rinv, int64_t ldi, hipStream_t s) {
-  if (d > kInvMaxD) fail(SLSE_EUNSUPPORTED, "tri_inv: d > 512 not supported by this library");
-  tri_inv_kernel<<<(int)ceil_div(d, 4), 256, 0, s>>>(d, R, ldr, Rinv, ldi);
+  inverse_batched_kernel<<<dim3(upper, 1, (unsigned)B), 256, 0, s>>>(jobs);
   SLSE_LAUNCH_CHECK();
 }
 

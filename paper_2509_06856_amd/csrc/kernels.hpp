@@ -231,45 +231,41 @@ void launch_gauss_generate(uint64_t seed, uint64_t stream_id, int64_t m, int64_t
 // --------------------------------------------------------------------------
 // Dense FP64 helpers for the factorization.
 // --------------------------------------------------------------------------
-// C[MxN] = alpha * op(A) * op(B) + beta * C, all FP64 row-major.  Small outputs
-// with long K are split over K into `scratch` (gemm_scratch_doubles entries)
-// and summed in split order.
-size_t gemm_scratch_doubles(int64_t M, int64_t N, int64_t K);
-void launch_gemm_f64(int64_t M, int64_t N, int64_t K, double alpha, const double* A, int64_t lda,
-                     bool transA, const double* B, int64_t ldb, bool transB, double beta, double* C,
-                     int64_t ldc, hipStream_t s, double* scratch = nullptr,
-                     size_t scratch_doubles = 0);
-// out[i][k] = s * A[i][k] for i < rows, k < d (A in F32 or F64).
-void launch_convert_scale(int64_t rows, int d, const void* A, int64_t lda, slse_dtype at, double s,
-                          double* out, int64_t ldo, hipStream_t st);
-// R = upper Cholesky factor of the SPD d x d matrix G (R^T R = G); info[0] = 0 or (j+1) of the
-// first bad pivot.  G is read only.
-void launch_cholesky(int d, const double* G, int64_t ldg, double* R, int64_t ldr, int* info,
+// G = alpha A^T A (both triangles, ld ldg) for A rows x d in F32 or F64, summed in
+// FP64.  Long A are split over rows into `scratch` (gram_scratch_doubles
+// entries) and summed in split order.
+size_t gram_scratch_doubles(int64_t rows, int64_t d);
+void launch_gram(int64_t rows, int d, double alpha, const void* A, int64_t lda, slse_dtype at,
+                 double* G, int64_t ldg, double* scratch, size_t scratch_doubles, hipStream_t s);
+// Q = alpha A Z^T (rows x d, ld d): A R^{-1} for Z = R^{-T}
+void launch_times_inverse(int64_t rows, int d, double alpha, const void* A, int64_t lda,
+                          slse_dtype at, const double* Z, double* Q, hipStream_t s);
+// C0 = A0 B0 and C1 = A1 B1 (d x d, ld d; C with its own ld) in one launch
+void launch_two_products(int d, const double* A0, const double* B0, double* C0, int64_t ldc0,
+                         const double* A1, const double* B1, double* C1, int64_t ldc1,
+                         hipStream_t s);
+// R = upper Cholesky factor of the SPD d x d matrix G (R^T R = G, strict lower
+// zeroed; R may be null) and Z = R^{-T} (d x d, ld d, strict upper zeroed).  G
+// (ld d) is destroyed.  info[0] (zero on entry) becomes j + 1 of the first
+// non-positive or non-finite pivot.
+void launch_cholesky(int d, double* G, double* R, int64_t ldr, double* Z, int* info,
                      hipStream_t s);
-// G = G^{-1} in place for SPD G (d x d, ld = d) by blocked Gauss-Jordan; colp
-// is d x 32 scratch.  info[0] (zero on entry) becomes k0 + 1 of the first
-// pivot block with a non-positive or non-finite pivot.
-void launch_spd_inverse(int d, double* G, double* colp, int* info, hipStream_t s);
 // G += coef * trace(G) * I (d x d, ld = d).
 void launch_shift_diag(int d, double* G, double coef, hipStream_t s);
-// Rinv = R^{-1} (upper triangular, row-major d x d) for upper triangular R.
-void launch_tri_inv(int d, const double* R, int64_t ldr, double* Rinv, int64_t ldi, hipStream_t s);
 
-// One Cholesky-route factorization of a batch: Ad = scale * A[:, :d] (FP64),
-// G = Ad^T Ad, then M = G^{-1} by the blocked Gauss-Jordan steps of the
-// single-problem route (info[0]: first non-positive pivot block + 1).  Every
-// buffer is the job's own, row-major with leading dimension d (A: lda); G may
-// be M (the Gram is then inverted in place).
+// One Cholesky-route factorization of a batch: G = scale A^T A, Z = R^{-T} of its
+// Cholesky factor R, M = Z^T Z = G^{-1} (info[0]: first bad pivot + 1).  Every
+// buffer is the job's own, row-major with leading dimension d (A: lda); G is
+// destroyed and may be M.
 struct FactorJob {
   const void* A = nullptr;
   int64_t lda = 0;
   int64_t rows = 0;
   int d = 0;
   double scale = 1.0;
-  double* Ad = nullptr;
   double* G = nullptr;
+  double* Z = nullptr;
   double* M = nullptr;
-  double* colp = nullptr;  // d x 32 Gauss-Jordan column panel
   double* part = nullptr;  // splits x d x d partial Grams (factor_batched_splits > 1)
   int* info = nullptr;
 };

@@ -355,81 +355,79 @@ void enqueue_sketch(const SketchShape& s, uint64_t seed, const void* X, int64_t 
 }
 
 // ---------------------------------------------------------------------------
-// Factorization: R^T R = scale A^T A, then L = R^{-T} and M = L^T L = H_hat^{-1}.
+// Factorization: R^T R = scale A^T A, Z = R^{-T} and M = Z^T Z = H_hat^{-1}.
 // ---------------------------------------------------------------------------
 struct FactorBufs {
-  double* Ad = nullptr;  // rows x d
-  double* G = nullptr;   // d x d
-  double* R = nullptr;   // d x d (ldr)
-  double* L = nullptr;   // d x d: R^{-1}
+  double* G = nullptr;   // d x d: the Gram matrix, destroyed by its factorization
+  double* Z = nullptr;   // d x d: R^{-T}
   double* M = nullptr;   // d x d
-  double* Q = nullptr;   // rows x d (QR route)
-  double* R2 = nullptr;  // d x d (QR route)
-  int* info = nullptr;   // 2 ints
-  double* part = nullptr;  // split-K scratch of the GEMMs
+  // QR route: the two orthogonalised sketches, the factors of the passes and
+  // their inverses, one intermediate product
+  double *Q0 = nullptr, *Q1 = nullptr;                    // rows x d
+  double *R0 = nullptr, *R1 = nullptr, *R2 = nullptr;     // d x d
+  double *Z1 = nullptr, *Z2 = nullptr, *U = nullptr;      // d x d
+  int* info = nullptr;     // 3 ints: first bad pivot + 1 of each factorization
+  double* part = nullptr;  // row-split scratch of the Gram matrices
   size_t part_n = 0;
-  double* colp = nullptr;  // d x 32 panel scratch of the Gauss-Jordan inverse
 };
 
 FactorBufs reserve_factor(slse_ctx* ctx, int64_t rows, int64_t d, slse_factor_method method) {
   FactorBufs f;
-  f.Ad = ctx->arena.get_t<double>("f_Ad", rows * d);
   f.G = ctx->arena.get_t<double>("f_G", d * d);
-  f.R = ctx->arena.get_t<double>("f_R", d * d);
-  f.L = ctx->arena.get_t<double>("f_L", d * d);
+  f.Z = ctx->arena.get_t<double>("f_Z", d * d);
   f.M = ctx->arena.get_t<double>("f_M", d * d);
   if (method == SLSE_FACTOR_QR) {
-    f.Q = ctx->arena.get_t<double>("f_Q", rows * d);
+    f.Q0 = ctx->arena.get_t<double>("f_Q0", rows * d);
+    f.Q1 = ctx->arena.get_t<double>("f_Q1", rows * d);
+    f.R0 = ctx->arena.get_t<double>("f_R0", d * d);
+    f.R1 = ctx->arena.get_t<double>("f_R1", d * d);
     f.R2 = ctx->arena.get_t<double>("f_R2", d * d);
+    f.Z1 = ctx->arena.get_t<double>("f_Z1", d * d);
+    f.Z2 = ctx->arena.get_t<double>("f_Z2", d * d);
+    f.U = ctx->arena.get_t<double>("f_U", d * d);
   }
   f.info = ctx->arena.get_t<int>("f_info", 4, true);
-  f.part_n = std::max(gemm_scratch_doubles(d, d, rows), gemm_scratch_doubles(d, d, d));
-  if (method == SLSE_FACTOR_QR) f.part_n = std::max(f.part_n, gemm_scratch_doubles(rows, d, d));
+  f.part_n = std::max(gram_scratch_doubles(rows, d), gram_scratch_doubles(d, d));
   f.part = ctx->arena.get_t<double>("f_part", f.part_n + 1);
-  f.colp = ctx->arena.get_t<double>("f_colp", d * 32);
   return f;
 }
 
-// M (ldm = d) into f.M, and R (ldr = d) into f.R when need_R or on the QR
-// route.  Without R the Cholesky route inverts the Gram matrix directly
-// (M = G^{-1}, blocked Gauss-Jordan): the iteration needs only M.
+// M (ldm) and, when given, R (ldr).
 void enqueue_factor(const FactorBufs& f, int64_t rows, int d, const void* A, int64_t lda,
                     slse_dtype at, double scale, slse_factor_method method, hipStream_t st,
-                    bool need_R = false) {
-  launch_convert_scale(rows, d, A, lda, at, std::sqrt(scale), f.Ad, d, st);
-  if (method == SLSE_FACTOR_CHOL && !need_R) {
-    launch_gemm_f64(d, d, rows, 1.0, f.Ad, d, true, f.Ad, d, false, 0.0, f.M, d, st, f.part,
-                    f.part_n);
-    launch_fill_i32(f.info, 0, 3, st);
-    launch_spd_inverse(d, f.M, f.colp, f.info, st);
-    return;
-  }
-  launch_gemm_f64(d, d, rows, 1.0, f.Ad, d, true, f.Ad, d, false, 0.0, f.G, d, st, f.part, f.part_n);
+                    double* R, int64_t ldr, double* M, int64_t ldm) {
+  launch_fill_i32(f.info, 0, 3, st);
   if (method == SLSE_FACTOR_QR) {
+    if (d > 512) fail(SLSE_EUNSUPPORTED, "cholesky: d > 512 not supported by this library");
+    launch_gram(rows, d, scale, A, lda, at, f.G, d, f.part, f.part_n, st);
     // shifted CholeskyQR3 (Fukaya, Kannan, Nakatsukasa, Yamamoto, Yanagisawa,
     // SIAM J. Sci. Comput. 2020): a Cholesky of G + s I with
     // s = 11 (rows d + d (d + 1)) u ||A||_F^2 always exists; Q0 = A R0^{-1} then
     // has a modest condition number, and two CholeskyQR passes finish the job.
     // R = R2 R1 R0 matches Householder's R to O(kappa u) for kappa up to ~u^{-1}.
+    // The inverses come with the factors, so R^{-T} = Z2 Z1 Z0.
     const double u = std::ldexp(1.0, -53);
     launch_shift_diag(d, f.G, 11.0 * ((double)rows * d + (double)d * (d + 1)) * u, st);
-    launch_cholesky(d, f.G, d, f.R, d, f.info, st);                        // R0
-    launch_tri_inv(d, f.R, d, f.L, d, st);
-    launch_gemm_f64(rows, d, d, 1.0, f.Ad, d, false, f.L, d, false, 0.0, f.Q, d, st, f.part, f.part_n);
-    launch_gemm_f64(d, d, rows, 1.0, f.Q, d, true, f.Q, d, false, 0.0, f.G, d, st, f.part, f.part_n);
-    launch_cholesky(d, f.G, d, f.R2, d, f.info + 1, st);                   // R1
-    launch_tri_inv(d, f.R2, d, f.L, d, st);
-    launch_gemm_f64(rows, d, d, 1.0, f.Q, d, false, f.L, d, false, 0.0, f.Ad, d, st, f.part, f.part_n);
-    launch_gemm_f64(d, d, rows, 1.0, f.Ad, d, true, f.Ad, d, false, 0.0, f.G, d, st, f.part, f.part_n);
-    launch_cholesky(d, f.G, d, f.L, d, f.info + 2, st);                    // R2
-    launch_gemm_f64(d, d, d, 1.0, f.R2, d, false, f.R, d, false, 0.0, f.G, d, st, f.part, f.part_n);
-    launch_gemm_f64(d, d, d, 1.0, f.L, d, false, f.G, d, false, 0.0, f.R, d, st, f.part, f.part_n);
+    launch_cholesky(d, f.G, f.R0, d, f.Z, f.info, st);
+    launch_times_inverse(rows, d, std::sqrt(scale), A, lda, at, f.Z, f.Q0, st);
+    launch_gram(rows, d, 1.0, f.Q0, d, SLSE_F64, f.G, d, f.part, f.part_n, st);
+    launch_cholesky(d, f.G, f.R1, d, f.Z1, f.info + 1, st);
+    launch_times_inverse(rows, d, 1.0, f.Q0, d, SLSE_F64, f.Z1, f.Q1, st);
+    launch_gram(rows, d, 1.0, f.Q1, d, SLSE_F64, f.G, d, f.part, f.part_n, st);
+    launch_cholesky(d, f.G, f.R2, d, f.Z2, f.info + 2, st);
+    launch_two_products(d, f.R1, f.R0, f.G, d, f.Z1, f.Z, f.U, d, st);
+    launch_two_products(d, f.R2, f.G, R ? R : f.R0, R ? ldr : d, f.Z2, f.U, f.Z, d, st);
   } else {
-    launch_cholesky(d, f.G, d, f.R, d, f.info, st);
+    launch_gram(rows, d, scale, A, lda, at, f.G, d, f.part, f.part_n, st);
+    launch_cholesky(d, f.G, R, ldr, f.Z, f.info, st);
   }
-  // M = R^{-1} R^{-T}
-  launch_tri_inv(d, f.R, d, f.L, d, st);
-  launch_gemm_f64(d, d, d, 1.0, f.L, d, false, f.L, d, true, 0.0, f.M, d, st, f.part, f.part_n);
+  if (M) launch_gram(d, d, 1.0, f.Z, d, SLSE_F64, M, ldm, f.part, f.part_n, st);
+}
+
+// M into f.M (the iteration needs no R).
+void enqueue_factor(const FactorBufs& f, int64_t rows, int d, const void* A, int64_t lda,
+                    slse_dtype at, double scale, slse_factor_method method, hipStream_t st) {
+  enqueue_factor(f, rows, d, A, lda, at, scale, method, st, nullptr, 0, f.M, d);
 }
 
 // ---------------------------------------------------------------------------
@@ -1168,7 +1166,7 @@ struct BatchPlan {
   int B = 0;
   // bytes / entries of each pool (for the plan checks)
   int64_t a_bytes = 0, ah_bytes = 0, m_n = 0, beta_n = 0, part_n = 0;
-  int64_t bf_ad_n = 0, bf_cp_n = 0, bf_sq_n = 0, bf_splits = 1;
+  int64_t bf_splits = 1;
   size_t bsz_bytes = 0;  // shared SRHT workspaces
   slse_dtype t = SLSE_F32;
   std::vector<SketchShape> sk;
@@ -1649,24 +1647,15 @@ std::pair<std::string, bool> plan_batched(slse_ctx* ctx, int B, const slse_probl
   bp.rmax = max_r;
   bp.batched_factor = fm == SLSE_FACTOR_CHOL;
   if (bp.batched_factor) {
-    // each problem owns its scaled sketch Ad and a Gauss-Jordan column panel;
-    // the Gram is formed in its M-pool slot and inverted there
+    // the Gram is formed and factored in its M-pool slot; R^{-T} in its own
     const int splits = factor_batched_splits(max_r);
-    int64_t ad_n = 0, cp_n = 0, sq_n = 0;
-    for (int b = 0; b < B; ++b) {
-      ad_n += bp.sk[b].r * ps[b].d;
-      cp_n += ps[b].d * 32;
-      sq_n += ps[b].d * ps[b].d;
-    }
-    double* adp = ctx->arena.get_t<double>("bfAd", (size_t)ad_n);
-    double* cpp = ctx->arena.get_t<double>("bfColp", (size_t)cp_n);
+    int64_t sq_n = 0;
+    for (int b = 0; b < B; ++b) sq_n += ps[b].d * ps[b].d;
+    double* zp = ctx->arena.get_t<double>("bfZ", (size_t)sq_n);
     double* pp = splits > 1 ? ctx->arena.get_t<double>("bfPart", (size_t)(splits * sq_n)) : nullptr;
-    bp.bf_ad_n = ad_n;
-    bp.bf_cp_n = cp_n;
-    bp.bf_sq_n = sq_n;
     bp.bf_splits = splits;
     bp.h_jobs.resize(B);
-    int64_t ao = 0, co = 0, so = 0;
+    int64_t so = 0;
     for (int b = 0; b < B; ++b) {
       FactorJob& j = bp.h_jobs[b];
       const int64_t d = ps[b].d;
@@ -1674,15 +1663,12 @@ std::pair<std::string, bool> plan_batched(slse_ctx* ctx, int B, const slse_probl
       j.lda = bp.lda[b];
       j.rows = bp.sk[b].r;
       j.d = (int)d;
-      j.scale = std::sqrt(bp.sk[b].hat_scale);
-      j.Ad = adp + ao;
+      j.scale = bp.sk[b].hat_scale;
       j.M = bp.Mpool + bp.m_off[b];
       j.G = j.M;
-      j.colp = cpp + co;
+      j.Z = zp + so;
       j.part = pp ? pp + splits * so : nullptr;
       j.info = bp.finfo + 3 * b;
-      ao += j.rows * d;
-      co += d * 32;
       so += d * d;
     }
     bp.d_jobs = ctx->arena.get_t<FactorJob>("bJobs", (size_t)B);
@@ -1905,8 +1891,7 @@ void check_batch_plan(const Arena& ar, const BatchPlan& bp, const slse_problem* 
     if (bp.batched_factor) {
       const FactorJob& j = bp.h_jobs[b];
       inside(j.A, (j.rows - 1) * j.lda * es + d * es, "bAhat", tag + " factor input");
-      inside(j.Ad, j.rows * d * 8, "bfAd", tag + " factor Ad");
-      inside(j.colp, d * 32 * 8, "bfColp", tag + " factor panel");
+      inside(j.Z, d * d * 8, "bfZ", tag + " factor Z");
       inside(j.M, d * d * 8, "bM", tag + " factor M");
       if (j.part) inside(j.part, bp.bf_splits * d * d * 8, "bfPart", tag + " factor partials");
       inside(j.info, 3 * 4, "bInfo", tag + " factor info");
@@ -2126,13 +2111,7 @@ slse_status slse_factor(slse_ctx* ctx, int64_t rows, int64_t d, const void* A, i
     FactorBufs f = reserve_factor(ctx, rows, d, method);
     if (ctx->arena.grew) ctx->drop_graphs();
     ctx->pre.valid = false;
-    launch_fill_i32(f.info, 0, 3, st);
-    enqueue_factor(f, rows, (int)d, A, lda, a_t, scale, method, st, true);
-    SLSE_HIP(hipMemcpy2DAsync(R, ldr * sizeof(double), f.R, d * sizeof(double), d * sizeof(double),
-                              d, hipMemcpyDeviceToDevice, st));
-    if (M)
-      SLSE_HIP(hipMemcpy2DAsync(M, ldm * sizeof(double), f.M, d * sizeof(double),
-                                d * sizeof(double), d, hipMemcpyDeviceToDevice, st));
+    enqueue_factor(f, rows, (int)d, A, lda, a_t, scale, method, st, R, ldr, M, ldm);
     int info[3] = {0, 0, 0};
     SLSE_HIP(hipMemcpyAsync(info, f.info, sizeof(info), hipMemcpyDeviceToHost, st));
     SLSE_HIP(hipStreamSynchronize(st));
