@@ -178,7 +178,7 @@ slse_status slse_fused_resid_grad(slse_ctx* ctx, int64_t n, int64_t d, const voi
  * allocate device memory (code under hipGraph capture, tight serving loops,
  * harnesses that forbid allocation).  Same arguments, result and errors; the
  * call allocates nothing: the pass's partial sums live in a fixed device array
- * of the library (about 4.4 MB per device, held until the process ends) that
+ * of the library (about 4.2 MB per device, held until the process ends) that
  * slse_ctx_create locates on its device.  Limits: d <= 1024 (EINVAL above) and
  * grids of at most 512 blocks (the tuned launch shape of slse_fused_resid_grad
  * is reused when known and capped there).  Every call on one device uses the

@@ -3,16 +3,26 @@
 //
 // Layout: a row of X is split over a group of `lpr` lanes; lane l of the group
 // owns the vector chunks c*lpr + l (c < NCH) of VEC consecutive elements, so a
-// wave's loads of one row are contiguous.  Per row the group forms the partial
+// wave's loads of one row are contiguous.  Rows may start at any element: the
+// 16-byte loads need no 16-byte alignment, and where d is no multiple of the
+// chunks the last one is moved back to end with the row, its elements that
+// another lane owns replaced by zeros (1000003 x 101 float32: 377 us with
+// element loads behind a guard each, 93 us so).  Per row the group forms the partial
 // dot x_j . beta, all-reduces it across its lanes (xor shuffles), and every
 // lane folds r_j = y_j - x_j . beta into its own slice of g.  A wave streams
 // 64/lpr rows per step, UNROLL steps in flight, over one contiguous chunk of
 // rows per block.  At the end the wave's row
 // groups, then the block's waves, are summed; the block writes one partial
-// row; the last block of every group of `group_size` blocks adds its group's
-// rows in block order (deterministic for a fixed launch shape).
+// row, and the kernel that follows on the stream (the sum below, or the update
+// step of a narrow problem) adds the rows in a fixed order (deterministic for a
+// fixed launch shape).  The kernel boundary is the hand-off: a ticket per
+// block, with the release and acquire it needs across the XCDs' caches, cost
+// about 50 ns a block one after another (1000003 x 101 float32: 93, 106 and 139 us
+// on 256, 512 and 1024 blocks with tickets, 88, 88 and 88 without; 2^20 x 256:
+// 170.9 -> 164.2 us; the mixed solve at 2^22 x 512 43.5 -> 42.2 ms).
 #include <algorithm>
 #include <cstdlib>
+#include <type_traits>
 
 #include "kernels.hpp"
 
@@ -29,34 +39,21 @@ namespace {
 #endif
 constexpr int kThreads = SLSE_RG_THREADS;
 constexpr int kWaves = kThreads / 64;
-constexpr int kGroupSize = 32;  // blocks summed by the last block of each group
 
-typedef double f64x2 __attribute__((ext_vector_type(2)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
+// a vector of VEC elements whose address is a multiple of the element size
 template <typename T, int VEC>
-struct VecT;
-template <>
-struct VecT<double, 2> {
-  using type = f64x2;
+struct VecT {
+  typedef T type __attribute__((ext_vector_type(VEC), aligned(sizeof(T))));
 };
-template <>
-struct VecT<float, 4> {
-  using type = f32x4;
-};
-template <>
-struct VecT<double, 1> {
-  using type = double;
-};
-template <>
-struct VecT<float, 1> {
-  using type = float;
+template <typename T>
+struct VecT<T, 1> {
+  using type = T;
 };
 
 template <typename T, int VEC>
 __device__ __forceinline__ void load_vec(const T* __restrict__ p, T (&v)[VEC]) {
   using V = typename VecT<T, VEC>::type;
-  V x = __builtin_nontemporal_load(reinterpret_cast<const V*>(p));
+  const V x = __builtin_nontemporal_load(reinterpret_cast<const V*>(p));
   if constexpr (VEC == 1) {
     v[0] = x;
   } else {
@@ -106,16 +103,16 @@ constexpr int unroll_for() {
 }
 
 // FULL: d = NCH * lpr * VEC, so every chunk is a whole vector inside the row.
+// Otherwise NCH is the exact chunk count (d > (NCH - 1) lpr VEC) and only the
+// last chunk can reach past the row.
 template <typename T, typename Acc, int VEC, int NCH, bool HAS_Y, bool FULL>
 __global__ __launch_bounds__(kThreads) void resid_grad_kernel(
     int64_t n, int d, const T* __restrict__ X, int64_t ldx, const T* __restrict__ Y, int64_t incy,
-    const double* __restrict__ beta, int lpr, double* __restrict__ partial,
-    double* __restrict__ gpart, int* __restrict__ counters, int ldp,
+    const double* __restrict__ beta, int lpr, double* __restrict__ partial, int ldp,
     const int* __restrict__ done) {
-  constexpr int UNROLL = unroll_for<T, VEC, NCH, FULL ? SLSE_RG_DEPTH : 1>();
+  constexpr int UNROLL = unroll_for<T, VEC, NCH, SLSE_RG_DEPTH>();
   if (done && *done) return;
   __shared__ double s_red[kWaves][1025];
-  __shared__ int s_ticket;
 
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
@@ -123,16 +120,18 @@ __global__ __launch_bounds__(kThreads) void resid_grad_kernel(
   const int grp = lane / lpr;
   const int l = lane - grp * lpr;
 
+  // the last chunk: its first column, and which of its elements this lane owns
+  const int col_last = ((NCH - 1) * lpr + l) * VEC;
+  const int off_last = FULL ? col_last : min(col_last, d - VEC);
+  auto owns = [&](int c, int v) { return FULL || c < NCH - 1 || off_last + v >= col_last; };
+  auto offset = [&](int c) { return c == NCH - 1 ? off_last : (c * lpr + l) * VEC; };
+
   // beta slice of this lane
   Acc b[NCH][VEC];
-  bool full[NCH];
 #pragma unroll
-  for (int c = 0; c < NCH; ++c) {
-    const int col0 = (c * lpr + l) * VEC;
-    full[c] = col0 + VEC <= d;
+  for (int c = 0; c < NCH; ++c)
 #pragma unroll
-    for (int v = 0; v < VEC; ++v) b[c][v] = (col0 + v < d) ? (Acc)beta[col0 + v] : (Acc)0;
-  }
+    for (int v = 0; v < VEC; ++v) b[c][v] = owns(c, v) ? (Acc)beta[offset(c) + v] : (Acc)0;
 
   Acc acc[NCH][VEC];
 #pragma unroll
@@ -148,130 +147,85 @@ __global__ __launch_bounds__(kThreads) void resid_grad_kernel(
   const int64_t r0 = (int64_t)blockIdx.x * chunk;
   const int64_t r1 = min(n, r0 + chunk);
 
-  int64_t base = r0 + wave * gpw + grp;
-  if constexpr (FULL) {
-    // main loop: every row of the step is in range for the whole wave (the
-    // bound is wave-uniform), so the loads carry no guards and no branches
-    const int64_t wave_base0 = r0 + wave * gpw;
-    const int64_t last_off = (int64_t)(gpw - 1) + (int64_t)(UNROLL - 1) * rs;
-    int64_t wb = wave_base0;
-    for (; wb + last_off < r1; wb += (int64_t)rs * UNROLL) {
-      const int64_t row0 = wb + grp;
-      T x[UNROLL][NCH][VEC];
-      T y[UNROLL];
-#pragma unroll
-      for (int u = 0; u < UNROLL; ++u) {
-        const T* xr = X + (row0 + (int64_t)u * rs) * ldx;
-#pragma unroll
-        for (int c = 0; c < NCH; ++c) load_vec<T, VEC>(xr + (c * lpr + l) * VEC, x[u][c]);
-        if constexpr (HAS_Y) {
-          y[u] = __builtin_nontemporal_load(Y + (row0 + (int64_t)u * rs) * incy);
-        } else {
-          y[u] = 0;
-        }
-      }
-      // partial dots row by row (the widened values of a row die with its dot)
-      Acc dot[UNROLL];
-#pragma unroll
-      for (int u = 0; u < UNROLL; ++u) {
-        __builtin_amdgcn_sched_barrier(0);
-        Acc p0 = 0, p1 = 0;
-#pragma unroll
-        for (int c = 0; c < NCH; ++c)
-#pragma unroll
-          for (int v = 0; v < VEC; ++v) {
-            if ((c * VEC + v) & 1)
-              p1 = fma(widen<Acc>(x[u][c][v]), b[c][v], p1);
-            else
-              p0 = fma(widen<Acc>(x[u][c][v]), b[c][v], p0);
-          }
-        dot[u] = p0 + p1;
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      // all-reduce the rows' dots inside each lane group, the rows interleaved
-      for (int m = lpr >> 1; m > 0; m >>= 1) {
-        Acc o[UNROLL];
-#pragma unroll
-        for (int u = 0; u < UNROLL; ++u) o[u] = lane_xor(dot[u], m, lane);
-#pragma unroll
-        for (int u = 0; u < UNROLL; ++u) dot[u] += o[u];
-      }
-#pragma unroll
-      for (int u = 0; u < UNROLL; ++u) {
-        const Acc r = (Acc)y[u] - dot[u];
-#pragma unroll
-        for (int c = 0; c < NCH; ++c)
-#pragma unroll
-          for (int v = 0; v < VEC; ++v) acc[c][v] = fma(r, widen_again<Acc>(x[u][c][v]), acc[c][v]);
-        rr = fma(r, r, rr);
-      }
-    }
-    // tail: one row per lane group at a time, whole vectors, row guard only
-    for (int64_t row = wb + grp; row < r1; row += rs) {
-      const T* xr = X + row * ldx;
-      T x[NCH][VEC];
-#pragma unroll
-      for (int c = 0; c < NCH; ++c) load_vec<T, VEC>(xr + (c * lpr + l) * VEC, x[c]);
-      T y0 = 0;
-      if constexpr (HAS_Y) y0 = Y[row * incy];
-      Acc dot = 0;
-#pragma unroll
-      for (int c = 0; c < NCH; ++c)
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) dot = fma((Acc)x[c][v], b[c][v], dot);
-      // lanes of a group share the row, so the group's shuffles stay inside
-      // lanes that are all active
-      dot = lane_group_sum(dot, lpr);
-      const Acc r = (Acc)y0 - dot;
-#pragma unroll
-      for (int c = 0; c < NCH; ++c)
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) acc[c][v] = fma(r, (Acc)x[c][v], acc[c][v]);
-      rr = fma(r, r, rr);
-    }
-    base = r1;  // nothing left for the guarded loop
-  }
-  // guarded loop (every row when not FULL)
-  for (; base < r1; base += (int64_t)rs * UNROLL) {
+  // UNROLL rows per lane group, from `row0` every rs rows.  PART: some of them
+  // may lie past r1; those read row r1 - 1 and count as zeros.
+  auto step = [&](int64_t row0, auto part) {
+    constexpr bool PART = decltype(part)::value;
     T x[UNROLL][NCH][VEC];
     T y[UNROLL];
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {
-      const int64_t row = base + (int64_t)u * rs;
-      const bool ok = row < r1;
-      const T* xr = X + (ok ? row : 0) * ldx;
+      int64_t row = row0 + (int64_t)u * rs;
+      if constexpr (PART) row = min(row, r1 - 1);
+      const T* xr = X + row * ldx;
 #pragma unroll
-      for (int c = 0; c < NCH; ++c) {
-        const int col0 = (c * lpr + l) * VEC;
-        if (ok && full[c]) {
-          load_vec<T, VEC>(xr + col0, x[u][c]);
-        } else {
-#pragma unroll
-          for (int v = 0; v < VEC; ++v) x[u][c][v] = (ok && col0 + v < d) ? xr[col0 + v] : (T)0;
-        }
-      }
+      for (int c = 0; c < NCH; ++c) load_vec<T, VEC>(xr + offset(c), x[u][c]);
       if constexpr (HAS_Y) {
-        y[u] = ok ? Y[row * incy] : (T)0;
+        y[u] = __builtin_nontemporal_load(Y + row * incy);
       } else {
         y[u] = 0;
       }
     }
+    if constexpr (!FULL) {
+#pragma unroll
+      for (int u = 0; u < UNROLL; ++u)
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) x[u][NCH - 1][v] = owns(NCH - 1, v) ? x[u][NCH - 1][v] : (T)0;
+    }
+    if constexpr (PART) {
+#pragma unroll
+      for (int u = 0; u < UNROLL; ++u) {
+        const bool in = row0 + (int64_t)u * rs < r1;
+        y[u] = in ? y[u] : (T)0;
+#pragma unroll
+        for (int c = 0; c < NCH; ++c)
+#pragma unroll
+          for (int v = 0; v < VEC; ++v) x[u][c][v] = in ? x[u][c][v] : (T)0;
+      }
+    }
+    // partial dots row by row (the widened values of a row die with its dot)
+    Acc dot[UNROLL];
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {
-      Acc dot = 0;
+      __builtin_amdgcn_sched_barrier(0);
+      Acc p0 = 0, p1 = 0;
 #pragma unroll
       for (int c = 0; c < NCH; ++c)
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) dot = fma((Acc)x[u][c][v], b[c][v], dot);
-      dot = lane_group_sum(dot, lpr);
-      const Acc r = (Acc)y[u] - dot;  // zero for rows past n (x = y = 0)
+        for (int v = 0; v < VEC; ++v) {
+          if ((c * VEC + v) & 1)
+            p1 = fma(widen<Acc>(x[u][c][v]), b[c][v], p1);
+          else
+            p0 = fma(widen<Acc>(x[u][c][v]), b[c][v], p0);
+        }
+      dot[u] = p0 + p1;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // all-reduce the rows' dots inside each lane group, the rows interleaved
+    for (int m = lpr >> 1; m > 0; m >>= 1) {
+      Acc o[UNROLL];
+#pragma unroll
+      for (int u = 0; u < UNROLL; ++u) o[u] = lane_xor(dot[u], m, lane);
+#pragma unroll
+      for (int u = 0; u < UNROLL; ++u) dot[u] += o[u];
+    }
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u) {
+      const Acc r = (Acc)y[u] - dot[u];
 #pragma unroll
       for (int c = 0; c < NCH; ++c)
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) acc[c][v] = fma(r, (Acc)x[u][c][v], acc[c][v]);
+        for (int v = 0; v < VEC; ++v) acc[c][v] = fma(r, widen_again<Acc>(x[u][c][v]), acc[c][v]);
       rr = fma(r, r, rr);
     }
-  }
+  };
+  // whole steps while every row of the step is in range for the whole wave
+  // (the bound is wave-uniform: no guards and no branches), then one last step
+  // that may reach past the chunk
+  const int64_t last_off = (int64_t)(gpw - 1) + (int64_t)(UNROLL - 1) * rs;
+  int64_t wb = r0 + wave * gpw;
+  for (; wb + last_off < r1; wb += (int64_t)rs * UNROLL) step(wb + grp, std::false_type{});
+  if (wb < r1) step(wb + grp, std::true_type{});
 
   // sum the wave's row groups: lanes with equal l hold the same columns
   double accd[NCH][VEC];
@@ -295,8 +249,8 @@ __global__ __launch_bounds__(kThreads) void resid_grad_kernel(
       for (int c = 0; c < NCH; ++c)
 #pragma unroll
         for (int v = 0; v < VEC; ++v) {
-          const int col = (c * lpr + l) * VEC + v;
-          if (col >= c0 && col < c0 + 1024 && col < d) s_red[wave][col - c0] = accd[c][v];
+          const int col = offset(c) + v;
+          if (owns(c, v) && col >= c0 && col < c0 + 1024) s_red[wave][col - c0] = accd[c][v];
         }
       if (l == 0 && d >= c0 && d < c0 + 1024) s_red[wave][d - c0] = rrd;
     }
@@ -305,47 +259,49 @@ __global__ __launch_bounds__(kThreads) void resid_grad_kernel(
       double t = 0.0;
 #pragma unroll
       for (int w = 0; w < kWaves; ++w) t += s_red[w][col - c0];
-      store_device(prow + col, t);
+      prow[col] = t;
     }
     __syncthreads();
   }
-
-  // last block of the group sums the group's partial rows in block order
-  wait_memory();
-  __syncthreads();
-  const int group = blockIdx.x / kGroupSize;
-  const int g0 = group * kGroupSize;
-  const int gsz = min(kGroupSize, (int)gridDim.x - g0);
-  if (threadIdx.x == 0) {
-    s_ticket = take_ticket(&counters[group]);
-    if (s_ticket == gsz - 1) acquire_partials();
-  }
-  __syncthreads();
-  if (s_ticket == gsz - 1) {
-    for (int col = threadIdx.x; col < d + 1; col += kThreads) {
-      double v[kGroupSize];
-#pragma unroll
-      for (int bk = 0; bk < kGroupSize; ++bk)
-        v[bk] = bk < gsz ? load_device(partial + (int64_t)(g0 + bk) * ldp + col) : 0.0;
-      double t = 0.0;
-#pragma unroll
-      for (int bk = 0; bk < kGroupSize; ++bk) t += v[bk];
-      gpart[(int64_t)group * ldp + col] = t;
-    }
-    if (threadIdx.x == 0) atomicExch(&counters[group], 0);
-  }
 }
 
-__global__ void finalize_grad_kernel(const double* __restrict__ gpart, int groups, int ldp, int d,
-                                     double scale, double* __restrict__ g, double* __restrict__ rn) {
-  const int col = blockIdx.x * blockDim.x + threadIdx.x;
-  if (col > d) return;
+// g = scale * the sum of the partial rows (columns 0..d-1), rn = scale * the
+// sum of their last column.  Sixteen columns per block: 64 row groups sum every
+// 64th row, then each wave its four groups by lane exchange, then the waves
+// in order.
+constexpr int kSumThreads = 1024;
+constexpr int kSumCols = 16;
+__global__ __launch_bounds__(kSumThreads) void sum_rows_kernel(
+    const double* __restrict__ part, int rows, int ldp, int d, double scale,
+    double* __restrict__ g, double* __restrict__ rn) {
+  __shared__ double s[kSumThreads / 64][kSumCols];
+  const int c = threadIdx.x % kSumCols, rg = threadIdx.x / kSumCols;
+  const int col = blockIdx.x * kSumCols + c;
+  constexpr int kGroups = kSumThreads / kSumCols;
   double t = 0.0;
-  for (int k = 0; k < groups; ++k) t += gpart[(int64_t)k * ldp + col];
-  if (col < d) {
-    g[col] = scale * t;
-  } else if (rn) {
-    rn[0] = scale * t;
+  if (col <= d) {
+    int k = rg;
+    for (; k + 3 * kGroups < rows; k += 4 * kGroups) {
+      double v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = part[(int64_t)(k + u * kGroups) * ldp + col];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) t += v[u];
+    }
+    for (; k < rows; k += kGroups) t += part[(int64_t)k * ldp + col];
+  }
+  t += wave_xor(t, 16);
+  t += wave_xor(t, 32);
+  if ((threadIdx.x & 63) < kSumCols) s[threadIdx.x >> 6][c] = t;
+  __syncthreads();
+  if (threadIdx.x < kSumCols && col <= d) {
+    double v = 0.0;
+#pragma unroll
+    for (int w = 0; w < kSumThreads / 64; ++w) v += s[w][c];
+    if (col < d)
+      g[col] = scale * v;
+    else if (rn)
+      rn[0] = scale * v;
   }
 }
 
@@ -355,38 +311,41 @@ void launch_t(const ResidGradPlan& pl, const ResidGradArgs& a, hipStream_t s) {
   const T* Y = static_cast<const T*>(a.Y);
   if (Y) {
     resid_grad_kernel<T, Acc, VEC, NCH, true, FULL><<<pl.blocks, kThreads, 0, s>>>(
-        a.n, a.d, X, a.ldx, Y, a.incy, a.beta, pl.lpr, a.partial, a.gpart, a.counters, pl.ldp,
-        a.done);
+        a.n, a.d, X, a.ldx, Y, a.incy, a.beta, pl.lpr, a.partial, pl.ldp, a.done);
   } else {
     resid_grad_kernel<T, Acc, VEC, NCH, false, FULL><<<pl.blocks, kThreads, 0, s>>>(
-        a.n, a.d, X, a.ldx, Y, a.incy, a.beta, pl.lpr, a.partial, a.gpart, a.counters, pl.ldp,
-        a.done);
-  }
-}
-
-template <typename T, typename Acc, int VEC, bool FULL>
-void launch_nch(const ResidGradPlan& pl, const ResidGradArgs& a, hipStream_t s) {
-  switch (pl.nch) {
-    case 1: launch_t<T, Acc, VEC, 1, FULL>(pl, a, s); break;
-    case 2: launch_t<T, Acc, VEC, 2, FULL>(pl, a, s); break;
-    case 4: launch_t<T, Acc, VEC, 4, FULL>(pl, a, s); break;
-    case 8: launch_t<T, Acc, VEC, 8, FULL>(pl, a, s); break;
-    case 16: launch_t<T, Acc, VEC, 16, FULL>(pl, a, s); break;
-    default: fail(SLSE_EUNSUPPORTED, "resid_grad: unsupported chunk count");
+        a.n, a.d, X, a.ldx, Y, a.incy, a.beta, pl.lpr, a.partial, pl.ldp, a.done);
   }
 }
 
 template <typename T, typename Acc>
 void launch_vec(const ResidGradPlan& pl, const ResidGradArgs& a, hipStream_t s) {
   constexpr int V = 16 / sizeof(T);
-  if (pl.vec == V) {
-    if (pl.full)
-      launch_nch<T, Acc, V, true>(pl, a, s);
-    else
-      launch_nch<T, Acc, V, false>(pl, a, s);
-  } else {
-    launch_nch<T, Acc, 1, false>(pl, a, s);
+  if (pl.vec == 1) {
+    launch_t<T, Acc, 1, 1, false>(pl, a, s);
+    return;
   }
+  if (pl.full) {
+    switch (pl.nch) {
+      case 1: launch_t<T, Acc, V, 1, true>(pl, a, s); return;
+      case 2: launch_t<T, Acc, V, 2, true>(pl, a, s); return;
+      case 4: launch_t<T, Acc, V, 4, true>(pl, a, s); return;
+      case 8: launch_t<T, Acc, V, 8, true>(pl, a, s); return;
+      case 16: launch_t<T, Acc, V, 16, true>(pl, a, s); return;
+    }
+  } else {
+    switch (pl.nch) {
+      case 1: launch_t<T, Acc, V, 1, false>(pl, a, s); return;
+      case 2: launch_t<T, Acc, V, 2, false>(pl, a, s); return;
+      case 3: launch_t<T, Acc, V, 3, false>(pl, a, s); return;
+      case 4: launch_t<T, Acc, V, 4, false>(pl, a, s); return;
+      case 5: launch_t<T, Acc, V, 5, false>(pl, a, s); return;
+      case 6: launch_t<T, Acc, V, 6, false>(pl, a, s); return;
+      case 7: launch_t<T, Acc, V, 7, false>(pl, a, s); return;
+      case 8: launch_t<T, Acc, V, 8, false>(pl, a, s); return;
+    }
+  }
+  fail(SLSE_EUNSUPPORTED, "resid_grad: unsupported chunk count");
 }
 
 }  // namespace
@@ -396,8 +355,8 @@ ResidGradPlan plan_resid_grad(int64_t n, int d, slse_dtype storage, const void* 
   ResidGradPlan pl;
   const int es = (int)dtype_size(storage);
   const int vfull = 16 / es;
-  const bool aligned = (reinterpret_cast<uintptr_t>(X) % 16 == 0) && ((ldx * es) % 16 == 0);
-  pl.vec = aligned ? vfull : 1;
+  // vectors at any element address; rows shorter than one take an element per lane
+  pl.vec = d >= vfull ? vfull : 1;
   const int nvec = (int)ceil_div(d, pl.vec);
   // default: about eight vector chunks per lane (measured best for wide rows);
   // lane groups are powers of 2 up to a wave
@@ -407,38 +366,32 @@ ResidGradPlan plan_resid_grad(int64_t n, int d, slse_dtype storage, const void* 
   if (const char* e = std::getenv("SLSE_RG_LPR")) lpr = std::atoi(e);
   lpr = std::max(1, std::min(64, lpr));
   while (lpr & (lpr - 1)) lpr &= lpr - 1;
-  int nch = (int)ceil_div(nvec, lpr);
-  int p2 = 1;
-  while (p2 < nch) p2 *= 2;
-  while (p2 > 16 && lpr < 64) {  // too many chunks: widen the lane group
-    lpr *= 2;
-    nch = (int)ceil_div(nvec, lpr);
-    p2 = 1;
-    while (p2 < nch) p2 *= 2;
-  }
-  if (p2 > 16) fail(SLSE_EUNSUPPORTED, "resid_grad: d too large for this build");
+  bool full_ok = pl.vec > 1 && is_pow2(nvec) && d % pl.vec == 0;
+  if (const char* e = std::getenv("SLSE_RG_FULL")) full_ok = full_ok && std::atoi(e) != 0;
+  // whole chunks: 1, 2, 4, 8 or 16 per lane; with a moved last chunk 1 to 8; one
+  // element per lane below a vector
+  const int most = pl.vec == 1 ? 1 : full_ok ? 16 : 8;
+  while (lpr < 64 && ceil_div(nvec, lpr) > most) lpr *= 2;
+  pl.nch = (int)ceil_div(nvec, lpr);
+  if (pl.nch > most) fail(SLSE_EUNSUPPORTED, "resid_grad: d too large for this build");
   pl.lpr = lpr;
-  pl.nch = p2;
-  pl.full = pl.vec > 1 && d % pl.vec == 0 && (int64_t)p2 * lpr * pl.vec == d;
-  if (const char* e = std::getenv("SLSE_RG_FULL")) pl.full = pl.full && std::atoi(e) != 0;
+  pl.full = full_ok && (int64_t)pl.nch * lpr * pl.vec == d;
   pl.ldp = (int)round_up(d + 1, 8);
   const int rows_per_block_step = kWaves * (64 / lpr);
   const int bytes_per_vec = pl.vec * es;
-  const int unroll = std::max(1, std::min(16, 256 / (p2 * bytes_per_vec)));
+  const int unroll = std::max(1, std::min(16, 256 / (pl.nch * bytes_per_vec)));
   // an override may choose another grid, never one above the capacity the
-  // partial rows and group counters were allocated for
+  // partial rows were allocated for
   int target = std::min(grid_blocks, capacity);
   if (const char* e = std::getenv("SLSE_RG_BLOCKS"))
     target = std::max(1, std::min(capacity, std::atoi(e)));
   int64_t want = ceil_div(std::max<int64_t>(n, 1), (int64_t)rows_per_block_step * unroll);
   pl.blocks = (int)std::max<int64_t>(1, std::min<int64_t>(want, target));
-  pl.group_size = kGroupSize;
-  pl.groups = (int)ceil_div(pl.blocks, pl.group_size);
   return pl;
 }
 
 void launch_resid_grad(const ResidGradPlan& pl, const ResidGradArgs& a, hipStream_t s) {
-  if (pl.blocks > a.capacity_blocks || pl.groups > ceil_div(a.capacity_blocks, pl.group_size))
+  if (pl.blocks > a.capacity_blocks)
     fail(SLSE_EINVAL, "resid_grad: plan exceeds the scratch capacity");
   if (a.storage == SLSE_F64) {
     if (a.accum == SLSE_F64)
@@ -456,11 +409,10 @@ void launch_resid_grad(const ResidGradPlan& pl, const ResidGradArgs& a, hipStrea
   SLSE_LAUNCH_CHECK();
 }
 
-void launch_finalize_grad(const double* gpart, int groups, int ldp, int d, double scale,
-                          double* g_out, double* rnorm2_out, hipStream_t s) {
-  const int threads = 256;
-  finalize_grad_kernel<<<(int)ceil_div(d + 1, threads), threads, 0, s>>>(gpart, groups, ldp, d,
-                                                                         scale, g_out, rnorm2_out);
+void launch_sum_rows(const double* part, int rows, int ldp, int d, double scale, double* g,
+                     double* rnorm2, hipStream_t s) {
+  sum_rows_kernel<<<(int)ceil_div(d + 1, kSumCols), kSumThreads, 0, s>>>(part, rows, ldp, d, scale,
+                                                                       g, rnorm2);
   SLSE_LAUNCH_CHECK();
 }
 

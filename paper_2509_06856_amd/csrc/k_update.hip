@@ -1,8 +1,8 @@
 // M-IHS step with a fixed Hessian sketch (eqs. (98) and (99)):
 //   beta_{t+1} = beta_t + mu * H_hat^{-1} g_t + eta * (beta_t - beta_{t-1}),
 // g_t = c X^T (Y - X beta_t) being the negative gradient produced by the fused
-// residual-gradient pass (its per-group partial rows are summed here, in a
-// fixed order).  H_hat^{-1} is applied as the dense symmetric matrix
+// residual-gradient pass (its partial rows, summed here in a fixed order for
+// narrow problems and by their own kernel for wider ones).  H_hat^{-1} is applied as the dense symmetric matrix
 // M = R^{-1} R^{-T} (a GEMV spread over blocks).  The step also reduces
 //   ||M g_t||^2 and ||beta_{t+1}||^2,
 // whose ratio estimates the relative error of beta_t against the fixed point
@@ -16,29 +16,71 @@ namespace slse {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kWaves = kThreads / 64;
 
-__global__ __launch_bounds__(kThreads) void mihs_update_kernel(UpdateArgs a, int rows_per_block) {
+// Up to this many columns one block takes the whole step: it sums the pass's
+// partial rows itself (no launch in between) and needs no hand-off between
+// blocks for the estimate (a whole solve of 16384 x 32, 40 steps: 867 -> 672 us
+// together with the passes' own hand-off gone).  One CU then reads M and the rows: at
+// 128 columns 0.4 MB, about what a launch costs; the rows and M grow with d
+// and d^2.
+constexpr int kOneBlockD = 128;
+constexpr int kOneThreads = 1024;
+
+// the estimate's last sums: gp = g . Mg, pp = ||Mg||^2, bb = ||beta_{t+1}||^2
+__device__ __forceinline__ void finish_step(const UpdateArgs& a, double gp, double pp, double bb) {
+  const double est = bb > 0.0 ? sqrt(pp / bb) : sqrt(pp);
+  if (a.sur_out) a.sur_out[0] = est;
+  const bool finite = isfinite(gp) && isfinite(pp) && isfinite(bb);
+  if (!finite && a.status) atomicExch(a.status, 1);
+  if (a.done && a.tol2 > 0.0 && (!finite || est * est <= a.tol2)) atomicExch(a.done, 1);
+}
+
+// THREADS = kOneThreads: one block (d <= kOneBlockD); kThreads: rows_per_block
+// rows of M per block, the partial rows already summed (a.rows <= 1)
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void mihs_update_kernel(UpdateArgs a, int rows_per_block) {
+  constexpr bool ONE = THREADS == kOneThreads;
+  constexpr int WAVES = THREADS / 64;
   if (a.done && *a.done) return;
   extern __shared__ double s_g[];
-  __shared__ double s_red[3][kWaves];
+  __shared__ double s_red[3][WAVES];
   __shared__ int s_ticket;
   const int d = a.d;
-  for (int k = threadIdx.x; k < d; k += kThreads) {
-    // fixed-order sum over the groups, loads issued eight at a time
+  if constexpr (ONE) {
+    // 2^lc columns x THREADS / 2^lc row groups, each summing every such row
+    // (eight loads in flight), then the groups in order
+    __shared__ double s_p[kOneThreads];
+    int lc = 0;
+    while ((1 << lc) < d) ++lc;
+    const int groups = THREADS >> lc;
+    const int c = threadIdx.x & ((1 << lc) - 1), rg = threadIdx.x >> lc;
     double t = 0.0;
-    int q = 0;
-    for (; q + 8 <= a.groups; q += 8) {
-      double v[8];
+    if (c < d) {
+      int k = rg;
+      for (; k + 7 * groups < a.rows; k += 8 * groups) {
+        double v[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = a.gpart[(int64_t)(q + u) * a.ldp + k];
+        for (int u = 0; u < 8; ++u) v[u] = a.part[(int64_t)(k + u * groups) * a.ldp + c];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) t += v[u];
+        for (int u = 0; u < 8; ++u) t += v[u];
+      }
+      for (; k < a.rows; k += groups) t += a.part[(int64_t)k * a.ldp + c];
     }
-    for (; q < a.groups; ++q) t += a.gpart[(int64_t)q * a.ldp + k];
-    double g = a.scale * t;
-    if (a.w) g += a.w[k * a.incw];
-    s_g[k] = g;
+    s_p[threadIdx.x] = t;
+    __syncthreads();
+    if ((int)threadIdx.x < d) {
+      double v = 0.0;
+      for (int q = 0; q < groups; ++q) v += s_p[(q << lc) + threadIdx.x];
+      double g = a.scale * v;
+      if (a.w) g += a.w[threadIdx.x * a.incw];
+      s_g[threadIdx.x] = g;
+    }
+  } else {
+    for (int k = threadIdx.x; k < d; k += THREADS) {
+      double g = a.rows ? a.scale * a.part[k] : 0.0;
+      if (a.w) g += a.w[k * a.incw];
+      s_g[k] = g;
+    }
   }
   __syncthreads();
 
@@ -46,7 +88,7 @@ __global__ __launch_bounds__(kThreads) void mihs_update_kernel(UpdateArgs a, int
   const int wave = threadIdx.x >> 6;
   double gp = 0.0, pp = 0.0, bb = 0.0;
   const int row0 = blockIdx.x * rows_per_block;
-  for (int j = wave; j < rows_per_block; j += kWaves) {
+  for (int j = wave; j < rows_per_block; j += WAVES) {
     const int i = row0 + j;
     if (i >= d) break;
     const double* Mi = a.M + (int64_t)i * a.ldm;
@@ -71,47 +113,52 @@ __global__ __launch_bounds__(kThreads) void mihs_update_kernel(UpdateArgs a, int
     s_red[2][wave] = bb;
   }
   __syncthreads();
-  if (threadIdx.x < 3) {
-    double t = 0.0;
-    for (int w = 0; w < kWaves; ++w) t += s_red[threadIdx.x][w];
-    store_device(a.sur_partial + 3 * blockIdx.x + threadIdx.x, t);
-  }
-  wait_memory();
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    s_ticket = take_ticket(a.sur_counter);
-    if (s_ticket == (int)gridDim.x - 1) acquire_partials();
-  }
-  __syncthreads();
-  if (s_ticket != (int)gridDim.x - 1) return;
-  // the last block: every thread sums a fixed subset of the block partials,
-  // then a fixed tree over the threads (deterministic)
-  __shared__ double s_tail[3][kThreads];
-  double tgp = 0.0, tpp = 0.0, tbb = 0.0;
-  for (int b = threadIdx.x; b < (int)gridDim.x; b += kThreads) {
-    tgp += load_device(a.sur_partial + 3 * b + 0);
-    tpp += load_device(a.sur_partial + 3 * b + 1);
-    tbb += load_device(a.sur_partial + 3 * b + 2);
-  }
-  s_tail[0][threadIdx.x] = tgp;
-  s_tail[1][threadIdx.x] = tpp;
-  s_tail[2][threadIdx.x] = tbb;
-  __syncthreads();
-  for (int h = kThreads / 2; h > 0; h >>= 1) {
-    if ((int)threadIdx.x < h)
-      for (int c = 0; c < 3; ++c) s_tail[c][threadIdx.x] += s_tail[c][threadIdx.x + h];
+  if constexpr (ONE) {
+    if (threadIdx.x == 0) {
+      gp = pp = bb = 0.0;
+      for (int w = 0; w < WAVES; ++w) {
+        gp += s_red[0][w];
+        pp += s_red[1][w];
+        bb += s_red[2][w];
+      }
+      finish_step(a, gp, pp, bb);
+    }
+  } else {
+    if (threadIdx.x < 3) {
+      double t = 0.0;
+      for (int w = 0; w < WAVES; ++w) t += s_red[threadIdx.x][w];
+      store_device(a.sur_partial + 3 * blockIdx.x + threadIdx.x, t);
+    }
+    wait_memory();
     __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    tgp = s_tail[0][0];
-    tpp = s_tail[1][0];
-    tbb = s_tail[2][0];
-    const double est = tbb > 0.0 ? sqrt(tpp / tbb) : sqrt(tpp);
-    if (a.sur_out) a.sur_out[0] = est;
-    const bool finite = isfinite(tgp) && isfinite(tpp) && isfinite(tbb);
-    if (!finite && a.status) atomicExch(a.status, 1);
-    if (a.done && a.tol2 > 0.0 && (!finite || est * est <= a.tol2)) atomicExch(a.done, 1);
-    atomicExch(a.sur_counter, 0);
+    if (threadIdx.x == 0) {
+      s_ticket = take_ticket(a.sur_counter);
+      if (s_ticket == (int)gridDim.x - 1) acquire_partials();
+    }
+    __syncthreads();
+    if (s_ticket != (int)gridDim.x - 1) return;
+    // the last block: every thread sums a fixed subset of the block partials,
+    // then a fixed tree over the threads (deterministic)
+    __shared__ double s_tail[3][THREADS];
+    double tgp = 0.0, tpp = 0.0, tbb = 0.0;
+    for (int b = threadIdx.x; b < (int)gridDim.x; b += THREADS) {
+      tgp += load_device(a.sur_partial + 3 * b + 0);
+      tpp += load_device(a.sur_partial + 3 * b + 1);
+      tbb += load_device(a.sur_partial + 3 * b + 2);
+    }
+    s_tail[0][threadIdx.x] = tgp;
+    s_tail[1][threadIdx.x] = tpp;
+    s_tail[2][threadIdx.x] = tbb;
+    __syncthreads();
+    for (int h = THREADS / 2; h > 0; h >>= 1) {
+      if ((int)threadIdx.x < h)
+        for (int c = 0; c < 3; ++c) s_tail[c][threadIdx.x] += s_tail[c][threadIdx.x + h];
+      __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+      finish_step(a, s_tail[0][0], s_tail[1][0], s_tail[2][0]);
+      atomicExch(a.sur_counter, 0);
+    }
   }
 }
 
@@ -165,22 +212,27 @@ __global__ void copy_f64_kernel(const double* __restrict__ s, double* __restrict
 int grid_for(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(n, 256), 4096)); }
 
 int rows_per_block_for(int d) {
-  // about 64 blocks: each block re-reads the group partials, so fewer blocks
-  // for larger d keep that traffic near the size of M itself
+  // about 64 blocks
   int rpb = (int)ceil_div(d, 64);
-  return (int)round_up(std::max(rpb, kWaves), kWaves);
+  return (int)round_up(std::max(rpb, kThreads / 64), kThreads / 64);
 }
 
 }  // namespace
 
+bool update_sums_rows(int d) { return d <= kOneBlockD; }
+
 int update_blocks(int d) { return (int)ceil_div(d, rows_per_block_for(d)); }
 
 void launch_update(const UpdateArgs& a, hipStream_t s) {
-  const int rpb = rows_per_block_for(a.d);
-  const int blocks = (int)ceil_div(a.d, rpb);
   const size_t shm = (size_t)a.d * sizeof(double);
   if (shm > 64 * 1024) fail(SLSE_EUNSUPPORTED, "update: d too large for this library");
-  mihs_update_kernel<<<blocks, kThreads, shm, s>>>(a, rpb);
+  if (update_sums_rows(a.d)) {
+    mihs_update_kernel<kOneThreads><<<1, kOneThreads, shm, s>>>(a, a.d);
+  } else {
+    if (a.rows > 1) fail(SLSE_EINVAL, "update: the partial rows of a wide problem come summed");
+    const int rpb = rows_per_block_for(a.d);
+    mihs_update_kernel<kThreads><<<(int)ceil_div(a.d, rpb), kThreads, shm, s>>>(a, rpb);
+  }
   SLSE_LAUNCH_CHECK();
 }
 

@@ -9,16 +9,13 @@
 namespace slse {
 
 // --------------------------------------------------------------------------
-// Fused residual-gradient (one pass over X): per-group partial sums of
+// Fused residual-gradient (one pass over X): per-block partial sums of
 //   X[0:n]^T (Y - X beta)   and   ||Y - X beta||^2
-// written to gpart[group][0..d] (index d holds the residual norm).  The
-// launch reduces its block partials to `groups` rows itself (the last block
-// of each group sums its group's blocks in a fixed order).
+// written to partial[block][0..d] (index d holds the residual norm), to be
+// summed by the next kernel on the stream.
 // --------------------------------------------------------------------------
 struct ResidGradPlan {
   int blocks = 0;
-  int groups = 0;
-  int group_size = 0;
   int lpr = 0;   // lanes per row
   int vec = 0;   // elements per vector load
   int nch = 0;   // vector chunks per lane
@@ -42,21 +39,19 @@ struct ResidGradArgs {
   slse_dtype accum = SLSE_F64;
   const double* beta = nullptr;
   double* partial = nullptr;  // [blocks][ldp]
-  double* gpart = nullptr;    // [groups][ldp]
-  int* counters = nullptr;    // [groups], zero before the first launch; left zero
-  int capacity_blocks = 0;    // rows allocated in `partial` (groups: ceil(capacity / 32))
+  int capacity_blocks = 0;    // rows allocated in `partial`
   const int* done = nullptr;  // optional early-exit flag
 };
 
 void launch_resid_grad(const ResidGradPlan& pl, const ResidGradArgs& a, hipStream_t s);
 
-// g = scale * sum_g gpart[g][0..d) (and rnorm2 = scale * sum_g gpart[g][d]).
-void launch_finalize_grad(const double* gpart, int groups, int ldp, int d, double scale,
-                          double* g_out, double* rnorm2_out, hipStream_t s);
+// g = scale * sum_r part[r][0..d) and, if given, rnorm2 = scale * sum_r part[r][d].
+void launch_sum_rows(const double* part, int rows, int ldp, int d, double scale, double* g,
+                     double* rnorm2, hipStream_t s);
 
 // --------------------------------------------------------------------------
 // M-IHS update (eqs. (98)/(99)) with the preconditioner M = H_hat^{-1}:
-//   g      = scale * sum_groups gpart (+ w)
+//   g      = scale * sum_rows part (+ w)
 //   p      = M g
 //   beta'  = beta + mu p + eta (beta - beta_prev)
 // surrogate ||R^{-T} g||^2 = g . p is reduced into sur_out[0] (if given);
@@ -64,8 +59,8 @@ void launch_finalize_grad(const double* gpart, int groups, int ldp, int d, doubl
 // `done`, and later steps are skipped.
 // --------------------------------------------------------------------------
 struct UpdateArgs {
-  const double* gpart = nullptr;
-  int groups = 0;
+  const double* part = nullptr;  // [rows][ldp]: a pass's partial rows, or their sum (rows = 1)
+  int rows = 0;                  // 0: g = w
   int ldp = 0;
   int d = 0;
   double scale = 1.0;
@@ -90,6 +85,9 @@ struct UpdateArgs {
 };
 
 int update_blocks(int d);
+// whether the update of d columns sums the pass's partial rows itself (wider ones
+// take the sum of launch_sum_rows)
+bool update_sums_rows(int d);
 void launch_update(const UpdateArgs& a, hipStream_t s);
 
 // rel_out[0] = ||beta - ref|| / ||ref|| and delta = beta - ref (either may be null).

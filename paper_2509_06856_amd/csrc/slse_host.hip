@@ -436,8 +436,7 @@ void enqueue_factor(const FactorBufs& f, int64_t rows, int d, const void* A, int
 struct IterBufs {
   double* beta[3];
   double* partial = nullptr;
-  double* gpart = nullptr;
-  int* counters = nullptr;
+  double* g = nullptr;  // the summed partial rows (problems wider than the update sums itself)
   double* sur_partial = nullptr;
   int* sur_counter = nullptr;
   int* flags = nullptr;  // [0] done, [1] non-finite
@@ -455,9 +454,7 @@ IterBufs reserve_iter(slse_ctx* ctx, int64_t d, const char* tag) {
   b.grid_blocks = std::max(64, 2 * ctx->num_cus);
   const int64_t ldp = round_up(d + 1, 8);
   b.partial = ctx->arena.get_t<double>(t + "_partial", b.max_blocks * ldp);
-  const int groups = (int)ceil_div(b.max_blocks, 32);
-  b.gpart = ctx->arena.get_t<double>(t + "_gpart", groups * ldp);
-  b.counters = ctx->arena.get_t<int>(t + "_counters", groups, true);
+  b.g = ctx->arena.get_t<double>(t + "_g", ldp);
   b.sur_partial = ctx->arena.get_t<double>(t + "_surp", 3 * update_blocks((int)d) + 8);
   b.sur_counter = ctx->arena.get_t<int>(t + "_surc", 4, true);
   b.flags = ctx->arena.get_t<int>(t + "_flags", 4);
@@ -528,8 +525,6 @@ void tune_resid_grad(slse_ctx* ctx, const IterBufs& b, int64_t n, int d, slse_dt
       a.accum = accum;
       a.beta = b.beta[0];
       a.partial = b.partial;
-      a.gpart = b.gpart;
-      a.counters = b.counters;
       a.capacity_blocks = b.max_blocks;
       launch_resid_grad(pl, a, st);
       SLSE_HIP(hipEventRecord(e0, st));
@@ -590,11 +585,9 @@ struct Stepper {
     a.accum = SLSE_F64;
     a.beta = b.err_delta;
     a.partial = b.partial;
-    a.gpart = b.gpart;
-    a.counters = b.counters;
     a.capacity_blocks = b.max_blocks;
     launch_resid_grad(pl, a, st);
-    launch_finalize_grad(b.gpart, pl.groups, pl.ldp, d, 1.0, b.err_g, err.pred + t, st);
+    launch_sum_rows(b.partial, pl.blocks, pl.ldp, d, 1.0, b.err_g, err.pred + t, st);
   }
 
   // beta_{t0} = beta0 (zeros if NULL), beta_{t0-1} = beta_prev (beta0 if NULL)
@@ -636,15 +629,18 @@ struct Stepper {
     a.accum = accum;
     a.beta = b.beta[cur];
     a.partial = b.partial;
-    a.gpart = b.gpart;
-    a.counters = b.counters;
     a.capacity_blocks = b.max_blocks;
     a.done = b.flags;
     launch_resid_grad(pl, a, st);
     const int next = (cur + 1) % 3 == prev ? (cur + 2) % 3 : (cur + 1) % 3;
     UpdateArgs u;
-    u.gpart = b.gpart;
-    u.groups = pl.groups;
+    u.part = b.partial;
+    u.rows = pl.blocks;
+    if (!update_sums_rows(d)) {
+      launch_sum_rows(b.partial, pl.blocks, pl.ldp, d, 1.0, b.g, nullptr, st);
+      u.part = b.g;
+      u.rows = 1;
+    }
     u.ldp = pl.ldp;
     u.d = d;
     u.scale = scale;
@@ -1102,10 +1098,8 @@ slse_status backward_impl(slse_ctx* ctx, const slse_problem* p, const slse_param
   S.start(nullptr, nullptr);
   launch_fill_f64(zero, 0.0, d, st);
   {
-    // gpart rows of zero: reuse the update kernel with groups = 0 and w added
+    // no partial rows: the update kernel with g = w
     UpdateArgs u;
-    u.gpart = ib.gpart;
-    u.groups = 0;
     u.ldp = (int)round_up(d + 1, 8);
     u.d = d;
     u.scale = 1.0;
@@ -1957,8 +1951,8 @@ void check_batch_plan(const Arena& ar, const BatchPlan& bp, const slse_problem* 
 
 // ---------------------------------------------------------------------------
 // Fixed device scratch of the allocation-free residual-gradient entry point
-// (slse_fused_resid_grad_noalloc): the group tickets, group partial rows and
-// block partial rows of one pass, for grids of up to kNoAllocBlocks blocks and
+// (slse_fused_resid_grad_noalloc): the block
+// partial rows of one pass, for grids of up to kNoAllocBlocks blocks and
 // d <= kNoAllocMaxD.  Each device holds its own copy for the life of the
 // process, located once per device when a context is created on it; calls on
 // one device share it, so they must not overlap.
@@ -1966,11 +1960,7 @@ void check_batch_plan(const Arena& ar, const BatchPlan& bp, const slse_problem* 
 constexpr int kNoAllocBlocks = 512;
 constexpr int kNoAllocMaxD = 1024;
 constexpr int64_t kNoAllocLdp = 1032;  // partial row stride at d = kNoAllocMaxD: d + 1 rounded to 8
-constexpr int64_t kNoAllocGroups = kNoAllocBlocks / 32;
-constexpr size_t kNoAllocTicketBytes = 256;
-constexpr size_t kNoAllocGpartBytes = ((kNoAllocGroups * kNoAllocLdp * 8 + 255) / 256) * 256;
-constexpr size_t kNoAllocBytes =
-    kNoAllocTicketBytes + kNoAllocGpartBytes + (size_t)kNoAllocBlocks * kNoAllocLdp * 8;
+constexpr size_t kNoAllocBytes = (size_t)kNoAllocBlocks * kNoAllocLdp * 8;
 constexpr int kNoAllocMaxDevices = 64;
 
 static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
@@ -1978,8 +1968,7 @@ static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
 std::mutex g_scratch_mu;
 char* g_scratch_ptr[kNoAllocMaxDevices] = {};
 
-// With `device` current: find this device's copy of `scratch` and clear its
-// tickets (every pass leaves them at zero again).
+// With `device` current: find this device's copy of `scratch`.
 void setup_noalloc_scratch(int device) {
   std::lock_guard<std::mutex> lock(g_scratch_mu);
   require(device >= 0 && device < kNoAllocMaxDevices, "device index above the scratch table");
@@ -1987,8 +1976,6 @@ void setup_noalloc_scratch(int device) {
   void* p = nullptr;
   SLSE_HIP(hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)));
   require(p != nullptr, "no device address for the fixed scratch");
-  launch_fill_i32(static_cast<int*>(p), 0, (int64_t)(kNoAllocTicketBytes / sizeof(int)), nullptr);
-  SLSE_HIP(hipStreamSynchronize(nullptr));
   g_scratch_ptr[device] = static_cast<char*>(p);
 }
 
@@ -2158,11 +2145,9 @@ slse_status slse_fused_resid_grad(slse_ctx* ctx, int64_t n, int64_t d, const voi
     a.accum = accum;
     a.beta = beta;
     a.partial = b.partial;
-    a.gpart = b.gpart;
-    a.counters = b.counters;
     a.capacity_blocks = b.max_blocks;
     launch_resid_grad(pl, a, st);
-    launch_finalize_grad(b.gpart, pl.groups, pl.ldp, (int)d, scale, g_out, rnorm2_out, st);
+    launch_sum_rows(b.partial, pl.blocks, pl.ldp, (int)d, scale, g_out, rnorm2_out, st);
     return SLSE_OK;
   });
 }
@@ -2208,12 +2193,10 @@ slse_status slse_fused_resid_grad_noalloc(slse_ctx* ctx, int64_t n, int64_t d, c
     a.storage = storage;
     a.accum = accum;
     a.beta = beta;
-    a.counters = reinterpret_cast<int*>(base);
-    a.gpart = reinterpret_cast<double*>(base + kNoAllocTicketBytes);
-    a.partial = reinterpret_cast<double*>(base + kNoAllocTicketBytes + kNoAllocGpartBytes);
+    a.partial = reinterpret_cast<double*>(base);
     a.capacity_blocks = kNoAllocBlocks;
     launch_resid_grad(pl, a, st);
-    launch_finalize_grad(a.gpart, pl.groups, pl.ldp, (int)d, scale, g_out, rnorm2_out, st);
+    launch_sum_rows(a.partial, pl.blocks, pl.ldp, (int)d, scale, g_out, rnorm2_out, st);
     return SLSE_OK;
   });
 }
