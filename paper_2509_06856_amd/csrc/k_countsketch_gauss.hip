@@ -14,10 +14,10 @@
 // atomics, so sums agree with any other order to rounding, not bit for bit.
 //
 // Gaussian: A = G [X|Y] with G_kj iid N(0, 1) drawn on the fly (Philox block
-// (j, k >> 3) -> four Box-Muller pairs).  Tiled 64 (sketch rows) x 64
-// (columns) per block with the N rows split over blocks; partial tiles are
-// summed in split order by a second kernel.  FP64 data accumulates in FP64,
-// FP32 data in FP32.
+// (j, k >> 3) -> four Box-Muller pairs), multiplied on the matrix cores with
+// the N rows split over blocks; partial tiles are summed in split order by a
+// second kernel.  FP64 data is multiplied and accumulated in FP64, FP32 data in
+// FP32, or, on request, rounded to BF16 and accumulated in FP32.
 #include <algorithm>
 #include <cstdlib>
 
@@ -1054,78 +1054,163 @@ __device__ __forceinline__ void box_muller8_fast(uint64_t seed, uint64_t stream,
   box_muller8_words(w.w, z);
 }
 
-constexpr int kGT = 64;   // tile (sketch rows and columns)
-constexpr int kGK = 16;   // data rows per step
+constexpr int kGT = 64;  // tile (sketch rows and columns) that the split plan counts
+constexpr int kGK = 32;  // data rows per step
 
-template <typename T, typename Acc>
-__global__ __launch_bounds__(kThreads) void gauss_kernel(int64_t N, int d, const T* __restrict__ X,
-                                                         int64_t ldx, const T* __restrict__ Y,
-                                                         uint64_t seed, uint64_t stream, int64_t m,
-                                                         int splits, Acc* __restrict__ part,
-                                                         int64_t ldp) {
-  __shared__ Acc Gs[kGK][kGT + 1];
-  __shared__ Acc Ws[kGK][kGT + 1];
-  const int tx = threadIdx.x % 16;
-  const int ty = threadIdx.x / 16;
-  const int64_t k0 = (int64_t)blockIdx.y * kGT;  // sketch rows
-  const int c0 = blockIdx.x * kGT;               // columns of [X|Y]
-  const int split = blockIdx.z;
-  const int64_t per = ceil_div(N, (int64_t)splits);
-  const int64_t j_begin = split * per;
-  const int64_t j_end = min(N, j_begin + per);
-  Acc acc[4][4] = {};
-  for (int64_t j0 = j_begin; j0 < j_end; j0 += kGK) {
-    // G tile: kGT rows x kGK data rows = 8 row blocks x 16 columns of Philox blocks
-    if (threadIdx.x < (kGT / 8) * kGK) {
-      const int kb = threadIdx.x / kGK;  // which group of 8 sketch rows
-      const int jj = threadIdx.x % kGK;
-      const int64_t j = j0 + jj;
-      float z[8];
-      if (j < j_end) {
-        box_muller8(seed, stream, (uint64_t)j, (uint64_t)((k0 >> 3) + kb), z);
-      } else {
+// The lane layouts of the FP32 and FP64 matrix-core products of 16 x 16 x 4: lane
+// l holds A[l % 16][l / 16] and B[l / 16][l % 16]; accumulator r of lane l is
+// C[4 (l / 16) + r][l % 16] in FP32 and C[4 r + l / 16][l % 16] in FP64.
+template <typename T>
+struct GaussAcc {
+  typedef T type __attribute__((ext_vector_type(4)));
+};
+__device__ __forceinline__ GaussAcc<float>::type mfma16(float a, float b, GaussAcc<float>::type c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ GaussAcc<double>::type mfma16(double a, double b,
+                                                         GaussAcc<double>::type c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+template <typename T>
+__device__ __forceinline__ int acc_row(int lane, int r) {
+  return sizeof(T) == 4 ? 4 * (lane >> 4) + r : 4 * r + (lane >> 4);
+}
+
+// G [X|Y] in the data's own precision on the matrix cores: 16 NW sketch rows
+// x 16 NT columns per block, one sub-range of a split's data rows, kGK rows per
+// step; wave w multiplies sketch rows 16 w .. 16 w + 15 with every column
+// tile, so G is drawn once per column block.  Per step and SIMD a wave's draw of G
+// (one Philox block and its Box-Muller per thread, about 3400 cycles) and its
+// products (NT x 8 of 64 cycles in FP64, 32 in FP32) are about equal at 100
+// columns, and which of the two units bounds the kernel changes with the width;
+// so the two waves of a SIMD (or the blocks of a CU) take them in opposite order:
+// one draws G of the next step while the other multiplies this one.  G (as
+// FP32, the type that it is drawn in) and [X|Y] are double-buffered in LDS, the
+// rows of X copied straight into it a dword per lane (any alignment), one
+// barrier per step.  Row strides of an odd number of 16-value groups keep the
+// four k of an operand read in distinct banks.
+// Measured (S of 16 d rows and S_hat of 6 d; 64 x 64 tiles of VALU products,
+// G drawn again per 64 columns, before): FP64 2^17 x 64 2.70 -> 0.99 ms, 65536 x 128
+// 3.63 -> 1.48 ms, 16384 x 32 1.68 -> 0.10 ms; FP32 the same shapes 2.04 -> 0.69,
+// 2.42 -> 0.85, 1.42 -> 0.09 ms.
+template <typename T, int NT, int NW>
+__global__ __launch_bounds__(64 * NW) void gauss_kernel(int64_t N, int d, const T* __restrict__ X,
+                                                        int64_t ldx, const T* __restrict__ Y,
+                                                        uint64_t seed, uint64_t stream, int64_t m,
+                                                        int splits, int sub, int64_t per,
+                                                        int64_t sub_per, T* __restrict__ part,
+                                                        int64_t ldp) {
+  constexpr int MT = 16 * NW;
+  constexpr int GS = MT + 16;        // row stride of the G tile
+  constexpr int WS = 16 * (NT | 1);  // row stride of the [X|Y] tile
+  constexpr int TW = sizeof(T) / 4;  // dwords per value
+  static_assert(MT / 8 * kGK == 64 * NW, "one Philox block per thread per step");
+  __shared__ __attribute__((aligned(16))) float Gs[2][kGK * GS];
+  __shared__ __attribute__((aligned(16))) T Ws[2][kGK * WS];
+  const int t = threadIdx.x;
+  const int lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int64_t k0 = (int64_t)blockIdx.x * MT;  // sketch rows
+  const int c0 = blockIdx.y * 16 * NT;          // columns of [X|Y]
+  const int nx = min(16 * NT, d - c0);          // columns of X in this block (can be 0)
+  const int yc = d - c0;                        // Y's column in the tile
+  const bool has_y = yc < 16 * NT;
+  const int split = blockIdx.z / sub, q = blockIdx.z % sub;
+  const int64_t s_end = min(N, (split + 1) * per);
+  const int64_t j_begin = min(split * per + q * sub_per, s_end);
+  const int64_t j_end = min(s_end, j_begin + sub_per);
+  const int steps = (int)ceil_div(j_end - j_begin, (int64_t)kGK);
+  // columns past [X|Y] stay zero, and so do the rows past the range
+  for (int e = t; e < 2 * kGK * WS; e += 64 * NW) Ws[0][e] = (T)0;
+  __syncthreads();
+
+  const int kb = t % (MT / 8), jj = t / (MT / 8);  // this thread's Philox block of a step
+  const bool draws = k0 + 8 * kb < m;
+  auto draw = [&](int s) {
+    if (!draws) return;  // rows past m: their products are never stored
+    const int64_t j = j_begin + (int64_t)s * kGK + jj;
+    float z[8];
+    box_muller8(seed, stream, (uint64_t)j, (uint64_t)((k0 >> 3) + kb), z);
+    const bool live = j < j_end;
+    GaussAcc<float>::type lo, hi;
 #pragma unroll
-        for (int q = 0; q < 8; ++q) z[q] = 0.0f;
-      }
-#pragma unroll
-      for (int q = 0; q < 8; ++q) Gs[jj][kb * 8 + q] = (Acc)z[q];
+    for (int i = 0; i < 4; ++i) {
+      lo[i] = live ? z[i] : 0.0f;
+      hi[i] = live ? z[4 + i] : 0.0f;
     }
-    for (int e = threadIdx.x; e < kGK * kGT; e += kThreads) {
-      const int jj = e / kGT, cc = e % kGT;
-      const int64_t j = j0 + jj;
-      const int col = c0 + cc;
-      Acc v = 0;
-      if (j < j_end) {
-        if (col < d)
-          v = (Acc)X[j * ldx + col];
-        else if (col == d)
-          v = (Acc)Y[j];
+    float* g = &Gs[s & 1][jj * GS + 8 * kb];
+    *reinterpret_cast<GaussAcc<float>::type*>(g) = lo;
+    *reinterpret_cast<GaussAcc<float>::type*>(g + 4) = hi;
+  };
+  auto copy = [&](int s) {
+    const int64_t j0 = j_begin + (int64_t)s * kGK;
+    T* Wb = Ws[s & 1];
+#pragma unroll
+    for (int i = 0; i < kGK / NW; ++i) {
+      const int k = wave + NW * i;
+      if (j0 + k < j_end) {
+        const uint32_t* src = reinterpret_cast<const uint32_t*>(X + (j0 + k) * ldx + c0);
+        for (int w = 0; w < nx * TW; w += 64)
+          if (w + lane < nx * TW)
+            __builtin_amdgcn_global_load_lds(
+                (const SLSE_GLOBAL void*)(src + w + lane),
+                (__attribute__((address_space(3))) void*)(reinterpret_cast<uint32_t*>(Wb + k * WS) + w),
+                4, 0, 0);
+      } else {  // the last step's rows past the range
+        for (int c = lane; c < nx; c += 64) Wb[k * WS + c] = (T)0;
       }
-      Ws[jj][cc] = v;
     }
-    __syncthreads();
+  };
+
+  typename GaussAcc<T>::type acc[NT];
 #pragma unroll
-    for (int jj = 0; jj < kGK; ++jj) {
-      Acc a[4], b[4];
+  for (int u = 0; u < NT; ++u)
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        a[u] = Gs[jj][ty + 16 * u];
-        b[u] = Ws[jj][tx + 16 * u];
-      }
+    for (int r = 0; r < 4; ++r) acc[u][r] = (T)0;
+  const bool mine = k0 + 16 * wave < m;
+  auto multiply = [&](int s) {
+    if (!mine) return;
+    const float* Gb = &Gs[s & 1][16 * wave + (lane & 15)];
+    const T* Wb = &Ws[s & 1][lane & 15];
+#pragma unroll 2
+    for (int ks = 0; ks < kGK; ks += 4) {
+      const int k = ks + (lane >> 4);
+      const T a = (T)Gb[k * GS];
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) acc[u][v] = fma(a[u], b[v], acc[u][v]);
+      for (int u = 0; u < NT; ++u) acc[u] = mfma16(a, Wb[k * WS + 16 * u], acc[u]);
     }
-    __syncthreads();
+  };
+
+  const bool draws_first = NW > 4 ? wave < NW / 2 : (blockIdx.x + blockIdx.z) & 1;
+  const bool y_thread = has_y && t < kGK;
+  if (steps > 0) {
+    copy(0);
+    draw(0);
+    if (y_thread) Ws[0][t * WS + yc] = j_begin + t < j_end ? Y[j_begin + t] : (T)0;
   }
+  for (int s = 0; s < steps; ++s) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this step's rows of X are in LDS
+    __syncthreads();
+    const bool more = s + 1 < steps;
+    T y = 0;
+    if (more) {
+      const int64_t j = j_begin + (int64_t)(s + 1) * kGK + t;
+      if (y_thread && j < j_end) y = Y[j];
+      copy(s + 1);
+    }
+    if (more && draws_first) draw(s + 1);
+    multiply(s);
+    if (more && !draws_first) draw(s + 1);
+    if (more && y_thread) Ws[(s + 1) & 1][t * WS + yc] = y;
+  }
+  if (!mine) return;
 #pragma unroll
-  for (int u = 0; u < 4; ++u)
+  for (int u = 0; u < NT; ++u)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int64_t k = k0 + ty + 16 * u;
-      const int col = c0 + tx + 16 * v;
-      if (k < m && col <= d) part[((int64_t)split * m + k) * ldp + col] = acc[u][v];
+    for (int r = 0; r < 4; ++r) {
+      const int64_t k = k0 + 16 * wave + acc_row<T>(lane, r);
+      const int col = c0 + 16 * u + (lane & 15);
+      if (k < m && col <= d) part[((int64_t)blockIdx.z * m + k) * ldp + col] = acc[u][r];
     }
 }
 
@@ -1766,7 +1851,7 @@ void countsketch_t(const CountSketchArgs& a, hipStream_t s) {
 // partial sums
 size_t gauss_partial_bytes(const GaussianArgs& a) {
   const size_t es = (a.t == SLSE_F64 && !a.bf16) ? 8 : 4;
-  return (size_t)a.splits * (size_t)a.m * (size_t)round_up(a.d + 1, 4) * es;
+  return (size_t)a.splits * (size_t)a.sub * (size_t)a.m * (size_t)round_up(a.d + 1, 4) * es;
 }
 size_t gauss_tile_bytes(const GaussianArgs& a) {
   if (!a.bf16) return 0;
@@ -1799,19 +1884,62 @@ void gaussian_mfma(const GaussianArgs& a, hipStream_t s) {
   SLSE_LAUNCH_CHECK();
 }
 
-template <typename T, typename Acc>
+// Column tiles of 16 per block of the FP32 / FP64 kernel: every column in one
+// block while the two [X|Y] tiles fit in LDS beside those of G (17 tiles in
+// FP32, 13 in FP64: 160 KB), else the least number of equal blocks; then the next
+// width that is built.  Products of tiles past [X|Y] are wasted, so the widths lie
+// close together.
+constexpr int kGaussTiles[] = {1, 2, 3, 4, 5, 7, 9, 11, 13, 17};
+int gauss_tiles(int d, slse_dtype t) {
+  const int nt = (int)ceil_div(d + 1, 16);
+  const int most = t == SLSE_F64 ? 13 : 17;
+  const int want = (int)ceil_div(nt, ceil_div(nt, most));
+  for (int w : kGaussTiles)
+    if (w >= want) return w;
+  return most;
+}
+// Sketch rows per block: 128, or 64 where that leaves less of the last block
+// empty (few rows: what is drawn past m is skipped, but its waves idle)
+int gauss_waves(int64_t m) { return ceil_div(m, 64) % 2 == 1 && m < 512 ? 4 : 8; }
+
+template <typename T, int NT>
+void gauss_launch(const GaussianArgs& a, T* part, int64_t ldp, hipStream_t s) {
+  const int nw = gauss_waves(a.m);
+  const int64_t per = ceil_div(a.N, (int64_t)a.splits);
+  const int64_t sub_per = round_up(ceil_div(per, (int64_t)a.sub), kGK);
+  const dim3 grid((unsigned)ceil_div(a.m, 16 * nw), (unsigned)ceil_div(a.d + 1, 16 * NT),
+                  (unsigned)(a.splits * a.sub));
+  const T* X = static_cast<const T*>(a.X);
+  const T* Y = static_cast<const T*>(a.Y);
+  if (nw == 8)
+    gauss_kernel<T, NT, 8><<<grid, 512, 0, s>>>(a.N, a.d, X, a.ldx, Y, a.seed, a.stream_id, a.m,
+                                               a.splits, a.sub, per, sub_per, part, ldp);
+  else
+    gauss_kernel<T, NT, 4><<<grid, 256, 0, s>>>(a.N, a.d, X, a.ldx, Y, a.seed, a.stream_id, a.m,
+                                               a.splits, a.sub, per, sub_per, part, ldp);
+  SLSE_LAUNCH_CHECK();
+}
+
+template <typename T>
 void gaussian_t(const GaussianArgs& a, hipStream_t s) {
   const int cols = a.d + 1;
   const int64_t ldp = round_up(cols, 4);
-  Acc* part = std::is_same<Acc, double>::value ? reinterpret_cast<Acc*>(a.partial64)
-                                               : reinterpret_cast<Acc*>(a.partial);
-  dim3 grid((unsigned)ceil_div(cols, kGT), (unsigned)ceil_div(a.m, kGT), (unsigned)a.splits);
-  gauss_kernel<T, Acc><<<grid, kThreads, 0, s>>>(a.N, a.d, static_cast<const T*>(a.X), a.ldx,
-                                                  static_cast<const T*>(a.Y), a.seed, a.stream_id,
-                                                  a.m, a.splits, part, ldp);
-  SLSE_LAUNCH_CHECK();
-  gauss_reduce_kernel<T, Acc><<<grid1(a.m * cols), 256, 0, s>>>(part, a.splits, a.m, cols, ldp,
-                                                                 static_cast<T*>(a.A), a.lda);
+  T* part = sizeof(T) == 8 ? reinterpret_cast<T*>(a.partial64) : reinterpret_cast<T*>(a.partial);
+  switch (gauss_tiles(a.d, a.t)) {
+    case 1: gauss_launch<T, 1>(a, part, ldp, s); break;
+    case 2: gauss_launch<T, 2>(a, part, ldp, s); break;
+    case 3: gauss_launch<T, 3>(a, part, ldp, s); break;
+    case 4: gauss_launch<T, 4>(a, part, ldp, s); break;
+    case 5: gauss_launch<T, 5>(a, part, ldp, s); break;
+    case 7: gauss_launch<T, 7>(a, part, ldp, s); break;
+    case 9: gauss_launch<T, 9>(a, part, ldp, s); break;
+    case 11: gauss_launch<T, 11>(a, part, ldp, s); break;
+    case 13: gauss_launch<T, 13>(a, part, ldp, s); break;
+    default:
+      if constexpr (sizeof(T) == 4) gauss_launch<T, 17>(a, part, ldp, s);
+  }
+  gauss_reduce_kernel<T, T><<<grid1(a.m * cols), 256, 0, s>>>(part, a.splits * a.sub, a.m, cols, ldp,
+                                                               static_cast<T*>(a.A), a.lda);
   SLSE_LAUNCH_CHECK();
 }
 
@@ -1836,6 +1964,16 @@ void gaussian_plan(GaussianArgs& a) {
   int64_t splits = std::max<int64_t>(1, 2048 / std::max<int64_t>(tiles, 1));
   splits = std::min<int64_t>(splits, std::max<int64_t>(1, a.N / 4096));
   a.splits = (int)splits;
+  a.sub = 1;
+  if (!a.bf16) {
+    // the FP32 / FP64 kernel's blocks are large: sub-ranges of a split (at least
+    // 256 rows) until there are two per CU
+    const int64_t blocks = ceil_div(a.d + 1, 16 * gauss_tiles(a.d, a.t)) *
+                           ceil_div(a.m, 16 * gauss_waves(a.m)) * splits;
+    const int64_t rows = ceil_div(std::max<int64_t>(a.N, 1), splits);
+    a.sub = (int)std::max<int64_t>(
+        1, std::min<int64_t>(ceil_div(512, std::max<int64_t>(blocks, 1)), rows / 256));
+  }
 }
 
 size_t gaussian_scratch_bytes(const GaussianArgs& a) {
@@ -1850,9 +1988,9 @@ void launch_gaussian(const GaussianArgs& a, hipStream_t s) {
     return;
   }
   if (a.t == SLSE_F64)
-    gaussian_t<double, double>(a, s);
+    gaussian_t<double>(a, s);
   else if (a.t == SLSE_F32)
-    gaussian_t<float, float>(a, s);
+    gaussian_t<float>(a, s);
   else
     fail(SLSE_EUNSUPPORTED, "gaussian: dtype");
 }

@@ -212,7 +212,8 @@ struct GaussianArgs {
   int64_t lda = 0;
   float* partial = nullptr;   // split-K scratch
   double* partial64 = nullptr;
-  int splits = 0;
+  int splits = 0;             // contiguous ranges of data rows, added in order
+  int sub = 1;                // FP32 / FP64: parts that each range is summed in, in order too
   bool bf16 = false;          // BF16 operands on the matrix cores, FP32 accumulation
   bool tiles_ready = false;   // BF16: the scratch already holds this [X|Y]'s staged tiles
 };
