@@ -20,6 +20,7 @@
 // FP32, or, on request, rounded to BF16 and accumulated in FP32.
 #include <algorithm>
 #include <cstdlib>
+#include <type_traits>
 
 #include "kernels.hpp"
 #include "rng.hpp"
@@ -40,41 +41,46 @@ __global__ void fill_kernel(T* __restrict__ p, int64_t rows, int64_t cols, int64
   }
 }
 
-constexpr int kHistLds = 8192;  // Hessian buckets counted in LDS up to this many
+constexpr int kHistLds = 8192;  // Hessian buckets counted in a wave's LDS up to this many
 
-// bucket sizes of the largest level (DO_K) and of S_hat (HAT)
-template <bool LDS_H, bool HAT, bool DO_K = true>
-__global__ __launch_bounds__(kThreads) void cs_count_kernel(int64_t n, uint64_t seed,
-                                                            uint64_t mK_mask, int64_t r,
-                                                            int* __restrict__ cntK,
-                                                            int* __restrict__ cntH) {
-  __shared__ int hist[LDS_H && HAT ? kHistLds : 1];
-  if constexpr (LDS_H && HAT) {
-    for (int k = threadIdx.x; k < r; k += kThreads) hist[k] = 0;
-    __syncthreads();
-  }
+// The largest level's rows in their buckets: every row's bucket (complemented
+// for a negative sign) and its arrival number there, which the count's atomic
+// returns anyway; the list is then placed without drawing the hash or an
+// atomic again (2^20 rows: count and fill 122 -> 62 us).
+__global__ __launch_bounds__(kThreads) void cs_count_rank_kernel(int64_t n, uint64_t seed,
+                                                                 uint64_t mK_mask,
+                                                                 int* __restrict__ cntK,
+                                                                 int* __restrict__ keys,
+                                                                 int* __restrict__ rank) {
   for (int64_t j = blockIdx.x * (int64_t)kThreads + threadIdx.x; j < n;
        j += (int64_t)gridDim.x * kThreads) {
-    if constexpr (DO_K) {
-      uint64_t h;
-      int sg;
-      rng::cs_hash(seed, (uint64_t)j, mK_mask, h, sg);
-      atomicAdd(cntK + h, 1);
-    }
-    if constexpr (HAT) {
-      uint64_t hh;
-      int sh;
-      rng::cs_hash_hat(seed, (uint64_t)j, (uint64_t)r, hh, sh);
-      if constexpr (LDS_H)
-        atomicAdd(hist + hh, 1);
-      else
-        atomicAdd(cntH + hh, 1);
-    }
+    uint64_t h;
+    int sg;
+    rng::cs_hash(seed, (uint64_t)j, mK_mask, h, sg);
+    keys[j] = sg > 0 ? (int)h : ~(int)h;
+    rank[j] = atomicAdd(cntK + h, 1);
   }
-  if constexpr (LDS_H && HAT) {
-    __syncthreads();
-    for (int k = threadIdx.x; k < r; k += kThreads)
-      if (hist[k]) atomicAdd(cntH + k, hist[k]);
+}
+__global__ __launch_bounds__(kThreads) void cs_place_kernel(int64_t n, const int* __restrict__ off,
+                                                            const int* __restrict__ keys,
+                                                            const int* __restrict__ rank,
+                                                            int* __restrict__ list) {
+  for (int64_t j = blockIdx.x * (int64_t)kThreads + threadIdx.x; j < n;
+       j += (int64_t)gridDim.x * kThreads) {
+    const int key = keys[j];
+    list[off[key < 0 ? ~key : key] + rank[j]] = key < 0 ? ~(int)j : (int)j;
+  }
+}
+
+// bucket sizes of S_hat (more buckets than a wave's LDS counts)
+__global__ __launch_bounds__(kThreads) void cs_count_kernel(int64_t n, uint64_t seed, int64_t r,
+                                                            int* __restrict__ cntH) {
+  for (int64_t j = blockIdx.x * (int64_t)kThreads + threadIdx.x; j < n;
+       j += (int64_t)gridDim.x * kThreads) {
+    uint64_t hh;
+    int sh;
+    rng::cs_hash_hat(seed, (uint64_t)j, (uint64_t)r, hh, sh);
+    atomicAdd(cntH + hh, 1);
   }
 }
 
@@ -84,72 +90,82 @@ __global__ __launch_bounds__(kThreads) void cs_count_kernel(int64_t n, uint64_t 
 // first slot of its rows in every bucket; the wave then lists its rows in
 // order, 64 at a time (a row's place among the batch's rows of its bucket
 // comes from comparing buckets across the lanes).  Up to kHistLds buckets.
-constexpr int kHatWaves = 1024;
+// 1024 waves, and twice as many below 2^21 rows, where a wave's chain of 64-row
+// steps is what takes the time.
+int cs_list_waves(int64_t n) { return n < (int64_t(1) << 21) ? 2048 : 1024; }
 
 // per wave: its rows' counts per bucket (cntW row w), and the bucket sizes
-// (integer sums: the order of the additions does not matter)
-__global__ __launch_bounds__(64) void cs_hat_count_kernel(int64_t n, int64_t chunk, uint64_t seed,
-                                                          int64_t r, int* __restrict__ cntW,
-                                                          int* __restrict__ cntH) {
-  __shared__ int hist[kHistLds];
-  for (int k = threadIdx.x; k < r; k += 64) hist[k] = 0;
+// (integer sums: the order of the additions does not matter).  Four waves to a
+// block (fewer where their counts would not fit in 64 KB of LDS), whose counts
+// are added before they go to the global totals: every wave adding its own took
+// 20 us of atomics on a few hundred addresses.
+constexpr int kCountWaves = 4;
+int cs_count_waves(int64_t buckets) {
+  int w = kCountWaves;
+  while (w > 1 && w * buckets * (int64_t)sizeof(int) > 65536) w /= 2;
+  return w;
+}
+// totals += the block's counts of n buckets (hist: one row of n per wave)
+__device__ __forceinline__ void add_block_counts(const int* hist, int64_t n, int* __restrict__ tot) {
+  const int nw = blockDim.x >> 6;
+  for (int k = threadIdx.x; k < n; k += blockDim.x) {
+    int c = 0;
+    for (int q = 0; q < nw; ++q) c += hist[q * n + k];
+    if (c) atomicAdd(tot + k, c);
+  }
+}
+__global__ __launch_bounds__(64 * kCountWaves) void cs_hat_count_kernel(
+    int64_t n, int64_t chunk, int waves, uint64_t seed, int64_t r, int* __restrict__ cntW,
+    int* __restrict__ cntH) {
+  extern __shared__ int s_hist[];  // waves of the block x r
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t w = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave;
+  int* hist = s_hist + wave * r;
+  for (int k = lane; k < r; k += 64) hist[k] = 0;
   __syncthreads();
-  const int64_t j0 = (int64_t)blockIdx.x * chunk, j1 = min(n, j0 + chunk);
-  for (int64_t j = j0 + threadIdx.x; j < j1; j += 64) {
+  const int64_t j0 = w * chunk, j1 = min(n, j0 + chunk);
+  for (int64_t j = j0 + lane; j < j1; j += 64) {
     uint64_t hh;
     int sh;
     rng::cs_hash_hat(seed, (uint64_t)j, (uint64_t)r, hh, sh);
     atomicAdd(hist + hh, 1);
   }
   __syncthreads();
-  for (int k = threadIdx.x; k < r; k += 64) {
-    const int c = hist[k];
-    cntW[(int64_t)blockIdx.x * r + k] = c;
-    if (c) atomicAdd(cntH + k, c);
-  }
+  if (w < waves)
+    for (int k = lane; k < r; k += 64) cntW[w * r + k] = hist[k];
+  add_block_counts(s_hist, r, cntH);
 }
 
 // per bucket: the exclusive scan of the bucket totals (written to off, with
 // off[r] = their sum) and the first slot of every wave's rows (in place over
-// the counts).  A block takes 64 buckets: its threads first sum the totals
-// before them and one wave scans its 64; then its 16 waves each sum a
-// sixteenth of the waves' rows (lanes on consecutive buckets: coalesced), the
-// sixteen partial sums are scanned in LDS, and every wave writes its rows'
-// running starts.  Integer sums: exact in any order.
-constexpr int kColTile = 64;
+// the counts).  A block takes 16 buckets: its threads first sum the totals
+// before them and 16 lanes scan its own; then 64 thread groups each sum a 64th
+// of the waves' rows (a group's threads on consecutive buckets), the partial sums
+// are scanned in LDS, and every group writes its rows' running starts.  What
+// bounds it is the chain of a group's loads, so the groups are many and short
+// (64 buckets and 16 groups per block: 10.8 us at 1024 waves, 9.8 us at 2048 so).  Integer
+// sums: exact in any order.
+constexpr int kColTile = 16;
+constexpr int kColGroups = 1024 / kColTile;
 __global__ __launch_bounds__(1024) void cs_colscan_kernel(int64_t r, int waves,
                                                           int* __restrict__ cntW,
                                                           const int* __restrict__ tot,
                                                           int* __restrict__ off) {
-  __shared__ int part[16][kColTile];
+  __shared__ int part[kColGroups][kColTile];
   __shared__ int red[16];
   __shared__ int base[kColTile];
-  const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
+  const int c = threadIdx.x % kColTile, g = threadIdx.x / kColTile;
   const int64_t c0 = (int64_t)blockIdx.x * kColTile;
-  const int64_t k = c0 + lane;
+  const int64_t k = c0 + c;
   int pre = 0;
   for (int64_t e = threadIdx.x; e < c0; e += 1024) pre += tot[e];
   for (int m = 32; m > 0; m >>= 1) pre += __shfl_xor(pre, m, 64);
-  if (lane == 0) red[g] = pre;
-  __syncthreads();
-  if (g == 0) {
-    int p0 = 0;
-    for (int h = 0; h < 16; ++h) p0 += red[h];
-    const int t = k < r ? tot[k] : 0;
-    int incl = t;
-    for (int m = 1; m < 64; m <<= 1) {
-      const int v = __shfl_up(incl, m, 64);
-      if (lane >= m) incl += v;
-    }
-    base[lane] = p0 + incl - t;
-    if (k < r) off[k] = p0 + incl - t;
-    if (k == r - 1) off[r] = p0 + incl;
-  }
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = pre;
   // (both walks over the waves' rows load 16 counts at a time, so that their
   // loads are in flight together instead of one after another)
   constexpr int kB = 16;
-  const int per = (waves + 15) / 16;
-  const int w0 = g * per, w1 = min(waves, w0 + per);
+  const int per = (waves + kColGroups - 1) / kColGroups;
+  const int w0 = min(waves, g * per), w1 = min(waves, w0 + per);
   int t = 0;
   if (k < r) {
     int w = w0;
@@ -162,11 +178,25 @@ __global__ __launch_bounds__(1024) void cs_colscan_kernel(int64_t r, int waves,
     }
     for (; w < w1; ++w) t += cntW[(int64_t)w * r + k];
   }
-  part[g][lane] = t;
+  part[g][c] = t;
+  __syncthreads();
+  if (threadIdx.x < kColTile) {
+    int p0 = 0;
+    for (int h = 0; h < 16; ++h) p0 += red[h];
+    const int own = k < r ? tot[k] : 0;
+    int incl = own;
+    for (int m = 1; m < kColTile; m <<= 1) {
+      const int v = __shfl_up(incl, m, kColTile);
+      if (c >= m) incl += v;
+    }
+    base[c] = p0 + incl - own;
+    if (k < r) off[k] = p0 + incl - own;
+    if (k == r - 1) off[r] = p0 + incl;
+  }
   __syncthreads();
   if (k < r) {
-    int run = base[lane];
-    for (int h = 0; h < g; ++h) run += part[h][lane];
+    int run = base[c];
+    for (int h = 0; h < g; ++h) run += part[h][c];
     int w = w0;
     for (; w + kB <= w1; w += kB) {
       int v[kB];
@@ -179,9 +209,9 @@ __global__ __launch_bounds__(1024) void cs_colscan_kernel(int64_t r, int waves,
       }
     }
     for (; w < w1; ++w) {
-      const int c = cntW[(int64_t)w * r + k];
+      const int n = cntW[(int64_t)w * r + k];
       cntW[(int64_t)w * r + k] = run;
-      run += c;
+      run += n;
     }
   }
 }
@@ -214,18 +244,19 @@ __device__ __forceinline__ void digit_rank(int dg, bool valid, int bits, int& be
 // PASS 0 draws the rows' buckets (digit = low bits); PASS 1 reads the first
 // pass's keys (digit = the bits above shift)
 template <int PASS>
-__global__ __launch_bounds__(64) void cs_digit_count_kernel(int64_t n, int64_t chunk, uint64_t seed,
-                                                            uint64_t mK_mask, int shift, int bits,
-                                                            const int* __restrict__ keys,
-                                                            int* __restrict__ cntW,
-                                                            int* __restrict__ tot) {
-  __shared__ int hist[kDigits];
+__global__ __launch_bounds__(64 * kCountWaves) void cs_digit_count_kernel(
+    int64_t n, int64_t chunk, int waves, uint64_t seed, uint64_t mK_mask, int shift, int bits,
+    const int* __restrict__ keys, int* __restrict__ cntW, int* __restrict__ tot) {
+  extern __shared__ int s_hist[];  // waves of the block x nd
   const int nd = 1 << bits;
-  for (int k = threadIdx.x; k < nd; k += 64) hist[k] = 0;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t w = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave;
+  int* hist = s_hist + wave * nd;
+  for (int k = lane; k < nd; k += 64) hist[k] = 0;
   __syncthreads();
-  const int64_t j0 = (int64_t)blockIdx.x * chunk, j1 = min(n, j0 + chunk);
+  const int64_t j0 = w * chunk, j1 = min(n, j0 + chunk);
   if constexpr (PASS == 0) {
-    for (int64_t j = j0 + threadIdx.x; j < j1; j += 64) {
+    for (int64_t j = j0 + lane; j < j1; j += 64) {
       uint64_t h;
       int sg;
       rng::cs_hash(seed, (uint64_t)j, mK_mask, h, sg);
@@ -233,7 +264,7 @@ __global__ __launch_bounds__(64) void cs_digit_count_kernel(int64_t n, int64_t c
     }
   } else {
     // four rows per thread per round, their loads in flight together
-    for (int64_t jb = j0 + threadIdx.x; jb < j1; jb += 256) {
+    for (int64_t jb = j0 + lane; jb < j1; jb += 256) {
       int key[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) key[u] = jb + 64 * u < j1 ? keys[jb + 64 * u] : -1;
@@ -243,11 +274,9 @@ __global__ __launch_bounds__(64) void cs_digit_count_kernel(int64_t n, int64_t c
     }
   }
   __syncthreads();
-  for (int k = threadIdx.x; k < nd; k += 64) {
-    const int c = hist[k];
-    cntW[(int64_t)blockIdx.x * nd + k] = c;
-    if (c) atomicAdd(tot + k, c);
-  }
+  if (w < waves)
+    for (int k = lane; k < nd; k += 64) cntW[w * nd + k] = hist[k];
+  add_block_counts(s_hist, nd, tot);
 }
 
 // PASS 0: writes (bucket, entry) of every row in low-digit order; PASS 1:
@@ -313,7 +342,7 @@ __global__ __launch_bounds__(64) void cs_hat_fill_kernel(int64_t n, int64_t chun
                                                          int64_t r, int bits,
                                                          const int* __restrict__ offW,
                                                          int* __restrict__ listH) {
-  __shared__ int cur[kHistLds];
+  extern __shared__ int cur[];  // r cursors
   const int lane = threadIdx.x;
   for (int k = lane; k < r; k += 64) cur[k] = offW[(int64_t)blockIdx.x * r + k];
   __syncthreads();
@@ -350,20 +379,22 @@ __global__ __launch_bounds__(64) void cs_hat_fill_kernel(int64_t n, int64_t chun
 // ranges, so one kernel hashes each row once for the count and once for the
 // fill.  Count: per wave, its rows per Hessian bucket (cntW) and per low
 // digit (cntWd), and the totals of both.
-__global__ __launch_bounds__(64) void cs_lists_count_kernel(int64_t n, int64_t chunk, uint64_t seed,
-                                                            int64_t r, uint64_t mK_mask, int bits,
-                                                            int* __restrict__ cntW,
-                                                            int* __restrict__ cntH,
-                                                            int* __restrict__ cntWd,
-                                                            int* __restrict__ dtot) {
-  __shared__ int hist[kHistLds];
-  __shared__ int histd[kDigits];
+__global__ __launch_bounds__(64 * kCountWaves) void cs_lists_count_kernel(
+    int64_t n, int64_t chunk, int waves, uint64_t seed, int64_t r, uint64_t mK_mask, int bits,
+    int* __restrict__ cntW, int* __restrict__ cntH, int* __restrict__ cntWd,
+    int* __restrict__ dtot) {
+  extern __shared__ int s_hist[];  // waves of the block x r, then x nd
   const int nd = 1 << bits;
-  for (int k = threadIdx.x; k < r; k += 64) hist[k] = 0;
-  for (int k = threadIdx.x; k < nd; k += 64) histd[k] = 0;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const int64_t w = (int64_t)blockIdx.x * nw + wave;
+  int* hist = s_hist + wave * r;
+  int* s_histd = s_hist + nw * r;
+  int* histd = s_histd + wave * nd;
+  for (int k = lane; k < r; k += 64) hist[k] = 0;
+  for (int k = lane; k < nd; k += 64) histd[k] = 0;
   __syncthreads();
-  const int64_t j0 = (int64_t)blockIdx.x * chunk, j1 = min(n, j0 + chunk);
-  for (int64_t j = j0 + threadIdx.x; j < j1; j += 64) {
+  const int64_t j0 = w * chunk, j1 = min(n, j0 + chunk);
+  for (int64_t j = j0 + lane; j < j1; j += 64) {
     uint64_t hh, h;
     int sh, sg;
     rng::cs_hash_hat(seed, (uint64_t)j, (uint64_t)r, hh, sh);
@@ -372,16 +403,12 @@ __global__ __launch_bounds__(64) void cs_lists_count_kernel(int64_t n, int64_t c
     atomicAdd(histd + ((int)h & (nd - 1)), 1);
   }
   __syncthreads();
-  for (int k = threadIdx.x; k < r; k += 64) {
-    const int c = hist[k];
-    cntW[(int64_t)blockIdx.x * r + k] = c;
-    if (c) atomicAdd(cntH + k, c);
+  if (w < waves) {
+    for (int k = lane; k < r; k += 64) cntW[w * r + k] = hist[k];
+    for (int k = lane; k < nd; k += 64) cntWd[w * nd + k] = histd[k];
   }
-  for (int k = threadIdx.x; k < nd; k += 64) {
-    const int c = histd[k];
-    cntWd[(int64_t)blockIdx.x * nd + k] = c;
-    if (c) atomicAdd(dtot + k, c);
-  }
+  add_block_counts(s_hist, r, cntH);
+  add_block_counts(s_histd, nd, dtot);
 }
 
 // Fill: every row into its Hessian bucket's list (listH) and, by its low
@@ -499,32 +526,20 @@ __global__ void scan_carry_kernel(int* __restrict__ out, int64_t n, const int* _
   if (i < n) out[i] += totals[i / kScanTile];
 }
 
-// list every row in its bucket of the largest level (DO_K) and of S_hat
-// (HAT): entry = j, or ~j when the sign is -1
-template <bool HAT, bool DO_K = true>
-__global__ __launch_bounds__(kThreads) void cs_fill_kernel(int64_t n, uint64_t seed, uint64_t mK_mask,
-                                                           int64_t r, int* __restrict__ curK,
-                                                           int* __restrict__ listK,
+// list every row in its bucket of S_hat: entry = j, or ~j when the sign is -1
+__global__ __launch_bounds__(kThreads) void cs_fill_kernel(int64_t n, uint64_t seed, int64_t r,
                                                            int* __restrict__ curH,
                                                            int* __restrict__ listH) {
   for (int64_t j = blockIdx.x * (int64_t)kThreads + threadIdx.x; j < n;
        j += (int64_t)gridDim.x * kThreads) {
-    if constexpr (DO_K) {
-      uint64_t h;
-      int sg;
-      rng::cs_hash(seed, (uint64_t)j, mK_mask, h, sg);
-      listK[atomicAdd(curK + h, 1)] = sg > 0 ? (int)j : ~(int)j;
-    }
-    if constexpr (HAT) {
-      uint64_t hh;
-      int sh;
-      rng::cs_hash_hat(seed, (uint64_t)j, (uint64_t)r, hh, sh);
-      listH[atomicAdd(curH + hh, 1)] = sh > 0 ? (int)j : ~(int)j;
-    }
+    uint64_t hh;
+    int sh;
+    rng::cs_hash_hat(seed, (uint64_t)j, (uint64_t)r, hh, sh);
+    listH[atomicAdd(curH + hh, 1)] = sh > 0 ? (int)j : ~(int)j;
   }
 }
 
-// The fill claims slots with atomics, so the order of a bucket's rows varies
+// These claim slots with atomics, so the order of a bucket's rows varies
 // from run to run, and with it the rounding of the bucket's sum.  Sorting
 // every bucket's entries by row index afterwards makes the lists, and every
 // sum over them, the same on every run.  An entry is j or ~j (negative sign).
@@ -608,18 +623,46 @@ __global__ __launch_bounds__(kSortThreads) void cs_sort_large_kernel(int64_t nb,
   }
 }
 
+// Rows of X read through a list are spread over lane groups: a row takes `lpr`
+// lanes (a power of 2) of VEC columns each, CH such chunks per pass, and a wave
+// holds 64 / lpr rows side by side, so rows narrower than a wave's 64 VEC columns
+// leave no lane idle.  The 16-byte loads take any element address; where d ends
+// inside a vector, the last vector is moved back to end with the row and its
+// lane writes only the columns that no other lane holds.
+template <typename T, int VEC>
+struct ElemVec {
+  typedef T type __attribute__((ext_vector_type(VEC), aligned(sizeof(T))));
+};
+template <typename T>
+struct ElemVec<T, 1> {
+  using type = T;
+};
+template <typename T, int VEC>
+__device__ __forceinline__ void load_elems(const T* p, T (&x)[VEC]) {
+  using V = typename ElemVec<T, VEC>::type;
+  const V v = __builtin_nontemporal_load(reinterpret_cast<const V*>(p));
+  if constexpr (VEC == 1) {
+    x[0] = v;
+  } else {
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) x[i] = v[i];
+  }
+}
+
 // out row (bucket b, part p of P): sum of s(j) [x_j | y_j] over list entries
 // [off[b] + p len / P, off[b] + (p + 1) len / P), len = off[b+1] - off[b].
-// One wave per (bucket, part); a lane holds VEC columns of a 64 VEC-column
-// chunk, eight list entries in flight.
+// One wave per (bucket, part): its lane groups take every (64 / lpr)-th entry, U
+// rows of each in flight, and are summed at the end.
 template <typename T, int VEC, int CH>
-__global__ __launch_bounds__(kThreads) void cs_gather_kernel(int64_t nb, int parts, int d,
+__global__ __launch_bounds__(kThreads) void cs_gather_kernel(int64_t nb, int parts, int d, int lanes,
                                                              const T* __restrict__ X, int64_t ldx,
                                                              const T* __restrict__ Y,
                                                              const int* __restrict__ off,
                                                              const int* __restrict__ list,
                                                              T* __restrict__ out, int64_t ldo) {
   const int lane = threadIdx.x & 63;
+  const int lpr = CH > 1 ? 64 : lanes;  // several chunks a pass: rows wider than a wave
+  const int groups = 64 / lpr, grp = lane / lpr, l = lane & (lpr - 1);
   const int64_t nw = nb * parts;
   for (int64_t w = (int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6); w < nw;
        w += (int64_t)gridDim.x * kWaves) {
@@ -629,55 +672,61 @@ __global__ __launch_bounds__(kThreads) void cs_gather_kernel(int64_t nb, int par
     const int e0 = o0 + (int)((int64_t)len * p / parts);
     const int e1 = o0 + (int)((int64_t)len * (p + 1) / parts);
     T* orow = out + w * ldo;
-    // CH chunks of 64 VEC columns per pass: a row's chunks are loaded together
-    constexpr int U = 8 / CH;  // list entries per batch: eight loads in flight
-    for (int c0 = 0; c0 < d; c0 += 64 * VEC * CH) {
+    // rows per lane group in flight: eight, but two of a row's chunks at a time
+    // for rows wider than a wave, whose 2 KB runs the memory serves faster with
+    // fewer of them open (2^22 x 512 float32: 5.47 ms per sketch with four, 5.37 with two)
+    constexpr int U = CH > 1 ? 2 : 8;
+    for (int c0 = 0; c0 < d; c0 += lpr * VEC * CH) {
+      int col[CH], at[CH];
+#pragma unroll
+      for (int h = 0; h < CH; ++h) {
+        col[h] = c0 + (h * lpr + l) * VEC;
+        at[h] = min(col[h], d - VEC);
+      }
       T acc[CH][VEC];
 #pragma unroll
       for (int h = 0; h < CH; ++h)
 #pragma unroll
         for (int v = 0; v < VEC; ++v) acc[h][v] = 0;
-      for (int e = e0; e < e1; e += U) {
+      // U entries per group from e; PART: those past the end are not added
+      auto batch = [&](int e, auto part) {
+        constexpr bool PART = decltype(part)::value;
         T x[U][CH][VEC];
-        int neg = 0;
+        int ent[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          const int ent = e + u < e1 ? list[e + u] : 0;
-          const bool ok = e + u < e1;
-          const int64_t j = ent < 0 ? (int64_t)~ent : (int64_t)ent;
-          neg |= (ent < 0 ? 1 : 0) << u;
+          const int eu = e + u * groups + grp;
+          ent[u] = list[PART ? min(eu, e1 - 1) : eu];
+          const int64_t j = ent[u] < 0 ? (int64_t)~ent[u] : (int64_t)ent[u];
+          const T* xr = X + j * ldx;
 #pragma unroll
-          for (int h = 0; h < CH; ++h) {
-            const int col = c0 + h * 64 * VEC + lane * VEC;
-            const T* xr = X + j * ldx + col;
-            if (ok && col + VEC <= d) {
-              if constexpr (VEC > 1) {
-                typedef T V __attribute__((ext_vector_type(VEC)));
-                const V t = __builtin_nontemporal_load(reinterpret_cast<const V*>(xr));
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) x[u][h][v] = t[v];
-              } else {
-                x[u][h][0] = __builtin_nontemporal_load(xr);
-              }
-            } else {
-#pragma unroll
-              for (int v = 0; v < VEC; ++v) x[u][h][v] = (ok && col + v < d) ? xr[v] : (T)0;
-            }
-          }
+          for (int h = 0; h < CH; ++h) load_elems<T, VEC>(xr + at[h], x[u][h]);
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u)
+        for (int u = 0; u < U; ++u) {
+          const bool in = !PART || e + u * groups + grp < e1;
+          const T sign = ent[u] < 0 ? (T)-1 : (T)1;
 #pragma unroll
           for (int h = 0; h < CH; ++h)
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) acc[h][v] += ((neg >> u) & 1) ? -x[u][h][v] : x[u][h][v];
-      }
+            for (int v = 0; v < VEC; ++v)
+              acc[h][v] = fma(sign, in ? x[u][h][v] : (T)0, acc[h][v]);
+        }
+      };
+      int e = e0;
+      for (; e + U * groups <= e1; e += U * groups) batch(e, std::false_type{});
+      if (e < e1) batch(e, std::true_type{});
+      for (int m = lpr; m < 64; m <<= 1)
 #pragma unroll
-      for (int h = 0; h < CH; ++h) {
-        const int col = c0 + h * 64 * VEC + lane * VEC;
+        for (int h = 0; h < CH; ++h)
 #pragma unroll
-        for (int v = 0; v < VEC; ++v)
-          if (col + v < d) orow[col + v] = acc[h][v];
+          for (int v = 0; v < VEC; ++v) acc[h][v] += __shfl_xor(acc[h][v], m, 64);
+      if (grp == 0) {
+#pragma unroll
+        for (int h = 0; h < CH; ++h)
+#pragma unroll
+          for (int v = 0; v < VEC; ++v)
+            if (at[h] + v >= col[h]) orow[at[h] + v] = acc[h][v];
       }
     }
     // the Y column: lanes split the list, then a wave sum in lane order
@@ -694,11 +743,11 @@ __global__ __launch_bounds__(kThreads) void cs_gather_kernel(int64_t nb, int par
 }
 
 // Level K straight from [X|Y] together with the L levels below it (levels
-// of m_K / 2, .., m_K / 2^L buckets, when the schedule has them).  One wave
+// of m_K / 2, .., m_K / 2^L buckets, when the schedule has them).  One lane group
 // per family of B = 2^L level-K buckets k_q = f + q mf (q < B, mf = m_K / B):
 // by h(j) mod m_i, the rows of the whole family land in bucket f of level
-// K - L.  The wave gathers the family's rows (about 2B of them, eight loads in
-// flight), keeps the B bucket sums of a chunk of 64 VEC columns in registers
+// K - L.  The group gathers the family's rows (about 2B of them, eight loads in
+// flight), keeps the B bucket sums of its columns in registers
 // and writes them with their halvings: level K - l receives the B / 2^l sums
 // A_{K-l}[f + q mf] = A_{K-l+1}[f + q mf] + A_{K-l+1}[f + (q + B / 2^l) mf],
 // the fold fold(A)[k] = A[k] + A[k + m/2] of the smaller levels.
@@ -708,32 +757,59 @@ struct FamilyTargets {
 
 template <typename T, int VEC, int L, int CH>
 __global__ __launch_bounds__(kThreads) void cs_gather_family_kernel(
-    int64_t mf, int d, const T* __restrict__ X, int64_t ldx, const T* __restrict__ Y,
+    int64_t mf, int d, int lanes, const T* __restrict__ X, int64_t ldx, const T* __restrict__ Y,
     const int* __restrict__ off, const int* __restrict__ list, T* __restrict__ A, int64_t lda,
     FamilyTargets tg, bool a_vec) {
   constexpr int B = 1 << L;
   constexpr int U = 8 / CH;  // rows per batch: eight loads in flight
   const int lane = threadIdx.x & 63;
-  for (int64_t f = (int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6); f < mf;
-       f += (int64_t)gridDim.x * kWaves) {
-    // lane q < B: the list range of bucket k_q, and its start in the family's entries
+  const int lpr = CH > 1 ? 64 : lanes;
+  const int groups = 64 / lpr, grp = lane / lpr, l = lane & (lpr - 1);
+  for (int64_t f0 = ((int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6)) * groups; f0 < mf;
+       f0 += (int64_t)gridDim.x * kWaves * groups) {
+    // the groups past the last family repeat it without rows and without stores
+    const bool live = CH > 1 || f0 + grp < mf;
+    const int64_t f = live ? f0 + grp : mf - 1;
+    // lane l < B of the group: the list range of bucket k_l (lpr >= 8 >= B)
     int o0 = 0, len = 0;
-    if (lane < B) {
-      const int64_t k = f + (int64_t)lane * mf;
+    if (l < B) {
+      const int64_t k = f + (int64_t)l * mf;
       o0 = off[k];
-      len = off[k + 1] - o0;
+      len = live ? off[k + 1] - o0 : 0;
     }
     // every lane keeps each bucket's list offset and first entry index
     int oo[B], st[B];
     int E = 0;
 #pragma unroll
     for (int q = 0; q < B; ++q) {
-      oo[q] = __shfl(o0, q, 64);
+      oo[q] = __shfl(o0, q, lpr);
       st[q] = E;
-      E += __shfl(len, q, 64);
+      E += __shfl(len, q, lpr);
     }
-    // CH chunks of 64 VEC columns per pass: a row's chunks are loaded together
-    for (int c0 = 0; c0 < d; c0 += 64 * VEC * CH) {
+    int Emax = E;  // of the wave's groups
+    for (int m = lpr; m < 64; m <<= 1) Emax = max(Emax, __shfl_xor(Emax, m, 64));
+    // bucket and list position of the family's entry e
+    auto locate = [&](int e, int& qe, int& pos) {
+      qe = 0;
+      int oq = oo[0], sq = 0;
+#pragma unroll
+      for (int q = 1; q < B; ++q) {
+        const int on = oo[q], sn = st[q];
+        const bool past = e >= sn;
+        qe = past ? q : qe;
+        oq = past ? on : oq;
+        sq = past ? sn : sq;
+      }
+      pos = oq + (e - sq);
+    };
+    // CH chunks of lpr VEC columns per pass: a row's chunks are loaded together
+    for (int c0 = 0; c0 < d; c0 += lpr * VEC * CH) {
+      int col[CH], at[CH];
+#pragma unroll
+      for (int h = 0; h < CH; ++h) {
+        col[h] = c0 + (h * lpr + l) * VEC;
+        at[h] = min(col[h], d - VEC);
+      }
       T acc[CH][B][VEC];
 #pragma unroll
       for (int h = 0; h < CH; ++h)
@@ -741,47 +817,33 @@ __global__ __launch_bounds__(kThreads) void cs_gather_family_kernel(
         for (int q = 0; q < B; ++q)
 #pragma unroll
           for (int v = 0; v < VEC; ++v) acc[h][q][v] = (T)0;
-      for (int r0 = 0; r0 < E; r0 += 64) {
-        // lane e of this round holds entry r0 + e and its bucket
-        const int e = r0 + lane;
-        int qe = 0, oq = oo[0], sq = st[0];
-#pragma unroll
-        for (int q = 1; q < B; ++q)
-          if (e >= st[q]) {
-            qe = q;
-            oq = oo[q];
-            sq = st[q];
-          }
-        const int ent = e < E ? list[oq + (e - sq)] : 0;
-        const int n = min(64, E - r0);
+      for (int r0 = 0; r0 < Emax; r0 += lpr) {
+        // lane l of the group holds entry r0 + l of its family and the entry's bucket
+        int qe, pos;
+        locate(r0 + l, qe, pos);
+        const int ent = r0 + l < E ? list[pos] : 0;
+        const int n = min(lpr, Emax - r0);
         for (int u0 = 0; u0 < n; u0 += U) {
           T x[U][CH][VEC];
           int qu[U];
           int neg = 0;
 #pragma unroll
           for (int u = 0; u < U; ++u) {
-            const bool ok = u0 + u < n;
-            const int eu = __shfl(ent, (u0 + u) & 63, 64);
-            qu[u] = ok ? __shfl(qe, (u0 + u) & 63, 64) : -1;
+            const bool ok = u0 + u < n && r0 + u0 + u < E;
+            const int src = (u0 + u) & (lpr - 1);
+            const int eu = __shfl(ent, src, lpr);
+            const int qs = __shfl(qe, src, lpr);
+            qu[u] = ok ? qs : -1;
             const int64_t j = eu < 0 ? (int64_t)~eu : (int64_t)eu;
             neg |= (eu < 0 ? 1 : 0) << u;
+            const T* xr = X + j * ldx;
 #pragma unroll
-            for (int h = 0; h < CH; ++h) {
-              const int col = c0 + h * 64 * VEC + lane * VEC;
-              const T* xr = X + j * ldx + col;
-              if (ok && col + VEC <= d) {
-                if constexpr (VEC > 1) {
-                  typedef T V __attribute__((ext_vector_type(VEC)));
-                  const V t = __builtin_nontemporal_load(reinterpret_cast<const V*>(xr));
+            for (int h = 0; h < CH; ++h)
 #pragma unroll
-                  for (int v = 0; v < VEC; ++v) x[u][h][v] = t[v];
-                } else {
-                  x[u][h][0] = __builtin_nontemporal_load(xr);
-                }
-              } else {
+              for (int v = 0; v < VEC; ++v) x[u][h][v] = (T)0;
+            if (ok) {
 #pragma unroll
-                for (int v = 0; v < VEC; ++v) x[u][h][v] = (ok && col + v < d) ? xr[v] : (T)0;
-              }
+              for (int h = 0; h < CH; ++h) load_elems<T, VEC>(xr + at[h], x[u][h]);
             }
           }
 #pragma unroll
@@ -797,9 +859,9 @@ __global__ __launch_bounds__(kThreads) void cs_gather_family_kernel(
       }
       // level K, then the halvings down to level K - L
 #pragma unroll
-      for (int l = 0; l <= L; ++l) {
-        const int nq = B >> l;
-        if (l > 0) {
+      for (int lv = 0; lv <= L; ++lv) {
+        const int nq = B >> lv;
+        if (lv > 0) {
 #pragma unroll
           for (int q = 0; q < (B >> 1); ++q)
             if (q < nq)
@@ -808,46 +870,41 @@ __global__ __launch_bounds__(kThreads) void cs_gather_family_kernel(
 #pragma unroll
                 for (int v = 0; v < VEC; ++v) acc[h][q][v] += acc[h][q + nq][v];
         }
+        if (!live) continue;
 #pragma unroll
         for (int q = 0; q < B; ++q) {
           if (q >= nq) continue;
-          T* orow = A + (tg.off[l] + f + (int64_t)q * mf) * lda;
+          T* orow = A + (tg.off[lv] + f + (int64_t)q * mf) * lda;
 #pragma unroll
           for (int h = 0; h < CH; ++h) {
-            const int col = c0 + h * 64 * VEC + lane * VEC;
             if constexpr (VEC > 1) {
-              if (a_vec && col + VEC <= d) {
+              if (a_vec && at[h] == col[h]) {
                 typedef T V __attribute__((ext_vector_type(VEC)));
                 V t;
 #pragma unroll
                 for (int v = 0; v < VEC; ++v) t[v] = acc[h][q][v];
                 // streaming stores: the levels are not read again by this
                 // pass, and keeping them out of L2 leaves it to the gathers
-                __builtin_nontemporal_store(t, reinterpret_cast<V*>(orow + col));
+                __builtin_nontemporal_store(t, reinterpret_cast<V*>(orow + col[h]));
                 continue;
               }
             }
 #pragma unroll
             for (int v = 0; v < VEC; ++v)
-              if (col + v < d) orow[col + v] = acc[h][q][v];
+              if (at[h] + v >= col[h]) orow[at[h] + v] = acc[h][q][v];
           }
         }
       }
     }
-    // the Y column: lanes split the entries, then one wave sum per bucket in lane order
+    // the Y column: the group's lanes split the entries, then one sum per
+    // bucket over the group in lane order
     T ys[B];
 #pragma unroll
     for (int q = 0; q < B; ++q) ys[q] = (T)0;
-    for (int e = lane; e < E; e += 64) {
-      int qe = 0, oq = oo[0], sq = st[0];
-#pragma unroll
-      for (int q = 1; q < B; ++q)
-        if (e >= st[q]) {
-          qe = q;
-          oq = oo[q];
-          sq = st[q];
-        }
-      const int ent = list[oq + (e - sq)];
+    for (int e = l; e < E; e += lpr) {
+      int qe, pos;
+      locate(e, qe, pos);
+      const int ent = list[pos];
       const int64_t j = ent < 0 ? (int64_t)~ent : (int64_t)ent;
       const T y = Y[j];
 #pragma unroll
@@ -856,21 +913,21 @@ __global__ __launch_bounds__(kThreads) void cs_gather_family_kernel(
     }
 #pragma unroll
     for (int q = 0; q < B; ++q)
-      for (int m = 32; m > 0; m >>= 1) ys[q] += __shfl_xor(ys[q], m, 64);
+      for (int m = lpr >> 1; m > 0; m >>= 1) ys[q] += __shfl_xor(ys[q], m, 64);
 #pragma unroll
-    for (int l = 0; l <= L; ++l) {
-      const int nq = B >> l;
-      if (l > 0) {
+    for (int lv = 0; lv <= L; ++lv) {
+      const int nq = B >> lv;
+      if (lv > 0) {
 #pragma unroll
         for (int q = 0; q < (B >> 1); ++q)
           if (q < nq) ys[q] += ys[q + nq];
       }
-      if (lane < nq) {
+      if (live && l < nq) {
         T yv = ys[0];
 #pragma unroll
         for (int q = 1; q < B; ++q)
-          if (lane == q) yv = ys[q];
-        A[(tg.off[l] + f + (int64_t)lane * mf) * lda + d] = yv;
+          if (l == q) yv = ys[q];
+        A[(tg.off[lv] + f + (int64_t)l * mf) * lda + d] = yv;
       }
     }
   }
@@ -1546,10 +1603,22 @@ __global__ void debug_gauss_kernel(uint64_t seed, uint64_t stream, int64_t k0, i
 
 int grid1(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(n, 256), 8192)); }
 
-// parts of each Hessian bucket: about 1024 listed rows per wave
+// parts of each Hessian bucket: enough for about 6144 waves (six per SIMD keep
+// the gather's random rows in flight), each of at least 64 rows.  2^20 x 64
+// float64 in 384 buckets: 3 parts of 1024 rows on half of each wave's lanes 567 us,
+// 16 parts with two rows side by side 98 us.
 int cs_hat_parts(int64_t N, int64_t r) {
   const int64_t per = ceil_div(std::max<int64_t>(N, 1), std::max<int64_t>(r, 1));
-  return (int)std::max<int64_t>(1, std::min<int64_t>(64, ceil_div(per, 1024)));
+  const int64_t want = ceil_div(6144, std::max<int64_t>(r, 1));
+  return (int)std::max<int64_t>(1, std::min<int64_t>({64, want, ceil_div(per, 64)}));
+}
+
+// lanes per row of the gathers: VEC columns a lane, from 8 lanes (a family's
+// buckets are looked up by the first 8 lanes of its group) to a wave
+int cs_lanes(int d, int vec) {
+  int lpr = 8;
+  while (lpr < 64 && lpr * vec < d) lpr *= 2;
+  return lpr;
 }
 
 __global__ void copy_i32_kernel(const int* __restrict__ src, int* __restrict__ dst, int64_t n) {
@@ -1571,7 +1640,8 @@ struct CsScratch {
   int waves;
   int64_t chunk;
   bool radix;                    // the largest level's lists by the counting sort
-  int *keysA, *valsA, *keysB;    // its passes' buckets and entries
+  int *keysA, *valsA, *keysB;    // its passes' buckets and entries (keysA, valsA: or the rows'
+                                 // buckets and arrival numbers)
   int *dtot, *doff;              // per-digit totals and their scan
   void* partH;
   size_t bytes;
@@ -1601,17 +1671,17 @@ CsScratch cs_scratch(const CountSketchArgs& a) {
   // per-wave row ranges: the Hessian lists in row order when their counts fit
   // in a wave's LDS; the largest level's by the counting sort when its
   // buckets take at most two digits
-  const int64_t w = std::min<int64_t>(kHatWaves, ceil_div(std::max<int64_t>(a.N, 1), 64));
+  const int64_t w = std::min<int64_t>(cs_list_waves(a.N), ceil_div(std::max<int64_t>(a.N, 1), 64));
   c.chunk = round_up(ceil_div(std::max<int64_t>(a.N, 1), w), 64);
   c.waves = (int)ceil_div(std::max<int64_t>(a.N, 1), c.chunk);
   const bool hat_rows = a.r <= kHistLds;
   c.radix = ilog2_ceil(mK) <= 2 * kDigitBits;
   c.cntW = hat_rows ? reinterpret_cast<int*>(take(sizeof(int) * (size_t)c.waves * a.r)) : nullptr;
   c.cntWd = c.radix ? reinterpret_cast<int*>(take(sizeof(int) * (size_t)c.waves * kDigits)) : nullptr;
-  c.keysA = c.valsA = c.keysB = c.dtot = c.doff = nullptr;
+  c.keysA = reinterpret_cast<int*>(take(sizeof(int) * a.N));
+  c.valsA = reinterpret_cast<int*>(take(sizeof(int) * a.N));
+  c.keysB = c.dtot = c.doff = nullptr;
   if (c.radix) {
-    c.keysA = reinterpret_cast<int*>(take(sizeof(int) * a.N));
-    c.valsA = reinterpret_cast<int*>(take(sizeof(int) * a.N));
     c.keysB = reinterpret_cast<int*>(take(sizeof(int) * a.N));
     c.dtot = reinterpret_cast<int*>(take(sizeof(int) * (kDigits + 1)));
     c.doff = reinterpret_cast<int*>(take(sizeof(int) * (kDigits + 1)));
@@ -1636,13 +1706,13 @@ void gather(int64_t nb, int parts, const CountSketchArgs& a, const int* off, con
   const T* X = static_cast<const T*>(a.X);
   const T* Y = static_cast<const T*>(a.Y);
   constexpr int V = 16 / sizeof(T);
-  const bool vec = (reinterpret_cast<uintptr_t>(X) % 16 == 0) && ((a.ldx * (int64_t)sizeof(T)) % 16 == 0);
-  if (vec && a.d > 64 * V)  // rows wider than one chunk: two chunks of a row per pass
-    cs_gather_kernel<T, V, 2><<<blocks, kThreads, 0, s>>>(nb, parts, a.d, X, a.ldx, Y, off, list, out, ldo);
-  else if (vec)
-    cs_gather_kernel<T, V, 1><<<blocks, kThreads, 0, s>>>(nb, parts, a.d, X, a.ldx, Y, off, list, out, ldo);
+  const int lpr = cs_lanes(a.d, a.d >= V ? V : 1);
+  if (a.d > 64 * V)  // rows wider than one chunk: two chunks of a row per pass
+    cs_gather_kernel<T, V, 2><<<blocks, kThreads, 0, s>>>(nb, parts, a.d, lpr, X, a.ldx, Y, off, list, out, ldo);
+  else if (a.d >= V)
+    cs_gather_kernel<T, V, 1><<<blocks, kThreads, 0, s>>>(nb, parts, a.d, lpr, X, a.ldx, Y, off, list, out, ldo);
   else
-    cs_gather_kernel<T, 1, 1><<<blocks, kThreads, 0, s>>>(nb, parts, a.d, X, a.ldx, Y, off, list, out, ldo);
+    cs_gather_kernel<T, 1, 1><<<blocks, kThreads, 0, s>>>(nb, parts, a.d, lpr, X, a.ldx, Y, off, list, out, ldo);
   SLSE_LAUNCH_CHECK();
 }
 
@@ -1659,15 +1729,17 @@ void gather_family(int L, const CountSketchArgs& a, const int* off, const int* l
     tg.off[l] = o;
     if (l < L) o -= a.m[a.K - 2 - l];
   }
-  const unsigned blocks = (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(mf, kWaves), 65536));
   const T* X = static_cast<const T*>(a.X);
   const T* Y = static_cast<const T*>(a.Y);
   constexpr int V = 16 / sizeof(T);
-  const bool vec = (reinterpret_cast<uintptr_t>(X) % 16 == 0) && ((a.ldx * (int64_t)sizeof(T)) % 16 == 0);
+  const bool vec = a.d >= V;
+  const int lpr = cs_lanes(a.d, vec ? V : 1);
+  const unsigned blocks = (unsigned)std::max<int64_t>(
+      1, std::min<int64_t>(ceil_div(mf, (int64_t)kWaves * (64 / lpr)), 65536));
   const bool a_vec = (reinterpret_cast<uintptr_t>(A) % 16 == 0) && ((a.lda * (int64_t)sizeof(T)) % 16 == 0);
 #define SLSE_FAMILY(VV, LL, CC)                                                                 \
-  cs_gather_family_kernel<T, VV, LL, CC><<<blocks, kThreads, 0, s>>>(mf, a.d, X, a.ldx, Y, off,   \
-                                                                     list, A, a.lda, tg, a_vec)
+  cs_gather_family_kernel<T, VV, LL, CC><<<blocks, kThreads, 0, s>>>(mf, a.d, lpr, X, a.ldx, Y,    \
+                                                                     off, list, A, a.lda, tg, a_vec)
   // rows wider than one chunk of 64 V columns: two chunks of a row per pass
   const bool two = a.d > 64 * V;
   if (vec && two) {
@@ -1754,10 +1826,21 @@ void countsketch_t(const CountSketchArgs& a, hipStream_t s) {
   if (const char* e = std::getenv("SLSE_CS_SORT")) radix = sc.radix && std::atoi(e) != 0;
   const bool hat_rows = a.r <= kHistLds;
   const unsigned ncs = (unsigned)ceil_div(kDigits, kColTile);
+  // count kernels: waves per block, blocks and LDS for `buckets` counts per wave
+  struct CountShape {
+    unsigned blocks, threads;
+    size_t lds;
+  };
+  auto count_shape = [&](int64_t buckets) {
+    const int w = cs_count_waves(buckets);
+    return CountShape{(unsigned)ceil_div(sc.waves, w), (unsigned)(64 * w),
+                      (size_t)w * (size_t)buckets * sizeof(int)};
+  };
   auto digit_pass1 = [&](int shift, int bits) {  // high digit: counts, first slots, fill
     fill_kernel<int><<<grid1(kDigits), 256, 0, s>>>(sc.dtot, 1, kDigits, kDigits);
-    cs_digit_count_kernel<1><<<(unsigned)sc.waves, 64, 0, s>>>(a.N, sc.chunk, a.seed, mK_mask, shift,
-                                                              bits, sc.keysA, sc.cntWd, sc.dtot);
+    const CountShape cd = count_shape(int64_t(1) << bits);
+    cs_digit_count_kernel<1><<<cd.blocks, cd.threads, cd.lds, s>>>(
+        a.N, sc.chunk, sc.waves, a.seed, mK_mask, shift, bits, sc.keysA, sc.cntWd, sc.dtot);
     cs_colscan_kernel<<<ncs, 1024, 0, s>>>(int64_t(1) << bits, sc.waves, sc.cntWd, sc.dtot, sc.doff);
     cs_digit_fill_kernel<1><<<(unsigned)sc.waves, 64, 0, s>>>(
         a.N, sc.chunk, a.seed, mK_mask, shift, bits, sc.cntWd, sc.keysA, sc.valsA, sc.keysB, sc.listK);
@@ -1768,8 +1851,10 @@ void countsketch_t(const CountSketchArgs& a, hipStream_t s) {
     const int b0 = std::min(p, kDigitBits), b1 = p - b0;
     fill_kernel<int><<<grid1(kDigits), 256, 0, s>>>(sc.dtot, 1, kDigits, kDigits);
     fill_kernel<int><<<grid1(a.r), 256, 0, s>>>(sc.cntH, 1, a.r, a.r);
-    cs_lists_count_kernel<<<(unsigned)sc.waves, 64, 0, s>>>(a.N, sc.chunk, a.seed, a.r, mK_mask, b0,
-                                                            sc.cntW, sc.cntH, sc.cntWd, sc.dtot);
+    const CountShape cl = count_shape(a.r + (int64_t(1) << b0));
+    cs_lists_count_kernel<<<cl.blocks, cl.threads, cl.lds, s>>>(a.N, sc.chunk, sc.waves, a.seed, a.r,
+                                                               mK_mask, b0, sc.cntW, sc.cntH,
+                                                               sc.cntWd, sc.dtot);
     cs_colscan_kernel<<<ncs, 1024, 0, s>>>(int64_t(1) << b0, sc.waves, sc.cntWd, sc.dtot, sc.doff);
     cs_colscan_kernel<<<(unsigned)ceil_div(a.r, kColTile), 1024, 0, s>>>(a.r, sc.waves, sc.cntW,
                                                                         sc.cntH, sc.offH);
@@ -1784,8 +1869,9 @@ void countsketch_t(const CountSketchArgs& a, hipStream_t s) {
       const int p = ilog2_ceil(mK);
       const int b0 = std::min(p, kDigitBits), b1 = p - b0;
       fill_kernel<int><<<grid1(kDigits), 256, 0, s>>>(sc.dtot, 1, kDigits, kDigits);
-      cs_digit_count_kernel<0><<<(unsigned)sc.waves, 64, 0, s>>>(a.N, sc.chunk, a.seed, mK_mask, 0,
-                                                                b0, nullptr, sc.cntWd, sc.dtot);
+      const CountShape cd = count_shape(int64_t(1) << b0);
+      cs_digit_count_kernel<0><<<cd.blocks, cd.threads, cd.lds, s>>>(
+          a.N, sc.chunk, sc.waves, a.seed, mK_mask, 0, b0, nullptr, sc.cntWd, sc.dtot);
       cs_colscan_kernel<<<ncs, 1024, 0, s>>>(int64_t(1) << b0, sc.waves, sc.cntWd, sc.dtot, sc.doff);
       cs_digit_fill_kernel<0><<<(unsigned)sc.waves, 64, 0, s>>>(
           a.N, sc.chunk, a.seed, mK_mask, 0, b0, sc.cntWd, nullptr, nullptr,
@@ -1794,31 +1880,27 @@ void countsketch_t(const CountSketchArgs& a, hipStream_t s) {
       cs_starts_kernel<<<grid1(a.N + 1), 256, 0, s>>>(a.N, mK, sc.keysB, sc.offK);
     } else {
       fill_kernel<int><<<grid1(mK), 256, 0, s>>>(sc.cntK, 1, mK, mK);
-      cs_count_kernel<false, false, true><<<rb, kThreads, 0, s>>>(a.N, a.seed, mK_mask, a.r, sc.cntK,
-                                                                  nullptr);
+      cs_count_rank_kernel<<<rb, kThreads, 0, s>>>(a.N, a.seed, mK_mask, sc.cntK, sc.keysA, sc.valsA);
       scan_exclusive(sc.cntK, sc.offK, mK, sc.totals, s);
-      copy_i32(sc.offK, sc.cntK, mK, s);
-      cs_fill_kernel<false, true><<<rb, kThreads, 0, s>>>(a.N, a.seed, mK_mask, a.r, sc.cntK,
-                                                          sc.listK, nullptr, nullptr);
+      cs_place_kernel<<<rb, kThreads, 0, s>>>(a.N, sc.offK, sc.keysA, sc.valsA, sc.listK);
       cs_sort_small_kernel<<<grid1(mK), 256, 0, s>>>(mK, sc.offK, sc.listK);
     }
     SLSE_LAUNCH_CHECK();
     // 2. the Hessian buckets' lists, in row order too
     fill_kernel<int><<<grid1(a.r), 256, 0, s>>>(sc.cntH, 1, a.r, a.r);
     if (hat_rows) {
-      cs_hat_count_kernel<<<(unsigned)sc.waves, 64, 0, s>>>(a.N, sc.chunk, a.seed, a.r, sc.cntW,
-                                                            sc.cntH);
+      const CountShape ch = count_shape(a.r);
+      cs_hat_count_kernel<<<ch.blocks, ch.threads, ch.lds, s>>>(a.N, sc.chunk, sc.waves, a.seed, a.r,
+                                                               sc.cntW, sc.cntH);
       cs_colscan_kernel<<<(unsigned)ceil_div(a.r, kColTile), 1024, 0, s>>>(a.r, sc.waves, sc.cntW,
                                                                           sc.cntH, sc.offH);
-      cs_hat_fill_kernel<<<(unsigned)sc.waves, 64, 0, s>>>(a.N, sc.chunk, a.seed, a.r,
-                                                           ilog2_ceil(a.r), sc.cntW, sc.listH);
+      cs_hat_fill_kernel<<<(unsigned)sc.waves, 64, sizeof(int) * (size_t)a.r, s>>>(
+          a.N, sc.chunk, a.seed, a.r, ilog2_ceil(a.r), sc.cntW, sc.listH);
     } else {
-      cs_count_kernel<false, true, false><<<rb, kThreads, 0, s>>>(a.N, a.seed, mK_mask, a.r, nullptr,
-                                                                  sc.cntH);
+      cs_count_kernel<<<rb, kThreads, 0, s>>>(a.N, a.seed, a.r, sc.cntH);
       scan_exclusive(sc.cntH, sc.offH, a.r, sc.totals, s);
       copy_i32(sc.offH, sc.cntH, a.r, s);
-      cs_fill_kernel<true, false><<<rb, kThreads, 0, s>>>(a.N, a.seed, mK_mask, a.r, nullptr,
-                                                          nullptr, sc.cntH, sc.listH);
+      cs_fill_kernel<<<rb, kThreads, 0, s>>>(a.N, a.seed, a.r, sc.cntH, sc.listH);
       cs_sort_large_kernel<<<(unsigned)std::min<int64_t>(a.r, 65535), kSortThreads, 0, s>>>(
           a.r, sc.offH, sc.listH);
     }
