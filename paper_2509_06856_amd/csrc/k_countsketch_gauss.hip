@@ -1317,27 +1317,23 @@ __global__ void gauss_reduce_kernel(const Acc* __restrict__ part, int splits, in
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
-// 64 sketch rows x 576 columns per block (every column of a d <= 575 problem
+// 16 RT sketch rows x 64 CT columns per block (every column of a d <= 575 problem
 // in one block, so G is generated once), 64 data rows per step.  Eight
-// waves, two per SIMD: 4 MFMA waves, each all four 16-row tiles x nine
-// 16-column tiles of v_mfma_f32_16x16x32_bf16 (36 accumulators of four
-// registers; every [X|Y] element is read from LDS by one wave only), and 4
-// generator waves, two Philox blocks per thread per step with their rounds
+// waves, two per SIMD: 4 MFMA waves, each all RT 16-row tiles x CT
+// 16-column tiles of v_mfma_f32_16x16x32_bf16 (36 to 40 accumulators of four
+// registers at the widest; every [X|Y] element is read from LDS by one wave only), and 4
+// generator waves, RT / 2 Philox blocks per thread per step, two at a time with their rounds
 // interleaved (two independent chains keep one wave's VALU issue busy).
-constexpr int kMT = 64;             // sketch rows per block
-constexpr int kNT = 576;            // columns per block
+// The blocks are as wide as [X|Y] needs: with 576 columns for every d the products of
+// tiles past [X|Y] and the LDS that they fill took 5.32 ms for 2 x 1536 rows of
+// 2^20 x 256 (4.42 now), 1.41 ms for 2 x 384 rows of 2^20 x 64 (1.00 now).
+constexpr int kMT = 64;             // sketch rows that the split plan counts per block
+constexpr int kNT = 576;            // columns per column block
 constexpr int kKT = 64;             // data rows per step: 8 chunks of 8 per LDS row
 constexpr int kMW = 4;              // MFMA waves: 4 column quarters of all 64 rows
 constexpr int kGW = 4;              // generator waves
-constexpr int kRT = 4;              // 16-row tiles per MFMA wave
 constexpr int kGThreads = 64 * (kMW + kGW);
-constexpr int kRH = kMT / (16 * kRT);  // row groups of MFMA waves
-constexpr int kCQ = kMW / kRH;         // column groups of MFMA waves
-constexpr int kCT = kNT / 16 / kCQ;    // 16-column tiles per MFMA wave (9)
-constexpr int kGB = kMT / 8 * kKT / (64 * kGW);  // Philox blocks per generator thread per step
-static_assert(kRH * kCQ == kMW && kCT * 16 * kCQ == kNT, "MFMA waves tile the block");
-static_assert(kGB * 64 * kGW == kMT / 8 * kKT, "whole Philox blocks per generator thread");
-static_assert((2 * kNT + 2 * kMT) * kKT * 2 <= 163840, "two [X|Y] tiles and two G tiles fit in LDS");
+constexpr int kGroupStep = 64 * kGW / kKT;  // row groups of 8 that the generator waves fill at once
 
 // FP32 -> BF16, round to nearest even: gfx950 converts two values per
 // instruction (v_cvt_pk_bf16_f32), which the compiler forms from adjacent
@@ -1413,32 +1409,37 @@ __global__ __launch_bounds__(kStageThreads) void gauss_stage_kernel(
   }
 }
 
-// one step of the generator waves: kGB Philox blocks of 8 sketch rows at
+// one step of the generator waves: RT / 2 Philox blocks of 8 sketch rows at
 // data row j per thread, rounded to BF16 and written to the G tile (rows past
 // the split are zeros)
+template <int RT>
 __device__ __forceinline__ void gauss_gen_step(uint64_t seed, uint64_t stream, int64_t k0,
                                                int64_t j, int64_t j_end, int gt, __bf16* Gb) {
   const int kb = gt / kKT, jj = gt % kKT;
-  // the blocks' rounds side by side: independent chains for the one
-  // generator wave of a SIMD to issue back to back
-  rng::PhiloxState st[kGB];
-#pragma unroll
-  for (int b = 0; b < kGB; ++b)
-    st[b] = rng::PhiloxState{{(uint64_t)j, (uint64_t)((k0 >> 3) + kb + b * (64 * kGW / kKT)), 0, 0},
-                             seed,
-                             stream};
-#pragma unroll
-  for (int r = 0; r < 10; ++r)
-#pragma unroll
-    for (int b = 0; b < kGB; ++b) rng::philox_round(st[b], r);
   const bool live = j < j_end;
+  static_assert(RT % 4 == 0 && kGroupStep * (RT / 2) == 2 * RT, "whole pairs of Philox blocks");
 #pragma unroll
-  for (int b = 0; b < kGB; ++b) {
-    const int rb = kb + b * (64 * kGW / kKT);  // group of 8 sketch rows
-    float z[8];
-    box_muller8_words(st[b].c, z);
+  for (int h = 0; h < RT / 2; h += 2) {
+    // two blocks' rounds side by side: independent chains for the one
+    // generator wave of a SIMD to issue back to back
+    rng::PhiloxState st[2];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) Gb[swz(rb * 8 + q, jj)] = to_bf16_rne(live ? z[q] : 0.0f);
+    for (int b = 0; b < 2; ++b)
+      st[b] = rng::PhiloxState{{(uint64_t)j, (uint64_t)((k0 >> 3) + kb + (h + b) * kGroupStep), 0, 0},
+                               seed,
+                               stream};
+#pragma unroll
+    for (int r = 0; r < 10; ++r)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) rng::philox_round(st[b], r);
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const int rb = kb + (h + b) * kGroupStep;  // group of 8 sketch rows
+      float z[8];
+      box_muller8_words(st[b].c, z);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) Gb[swz(rb * 8 + q, jj)] = to_bf16_rne(live ? z[q] : 0.0f);
+    }
   }
 }
 
@@ -1459,16 +1460,19 @@ __device__ __forceinline__ void gauss_copy_step(const __bf16* tb, int wc, __bf16
   }
 }
 
+template <int CT, int RT>
 __global__ __launch_bounds__(kGThreads) void gauss_mfma_kernel(int64_t N, int d,
                                                          const __bf16* __restrict__ tiles,
                                                          int64_t nchunks, uint64_t seed,
                                                          uint64_t stream, int64_t m, int splits,
                                                          float* __restrict__ part, int64_t ldp) {
-  __shared__ __attribute__((aligned(1024))) __bf16 Ws[2][kNT * kKT];
-  __shared__ __attribute__((aligned(1024))) __bf16 Gs[2][kMT * kKT];
+  static_assert((2 * 64 * CT + 2 * 16 * RT) * kKT * 2 <= 163840,
+                "two [X|Y] tiles and two G tiles fit in LDS");
+  __shared__ __attribute__((aligned(1024))) __bf16 Ws[2][64 * CT * kKT];
+  __shared__ __attribute__((aligned(1024))) __bf16 Gs[2][16 * RT * kKT];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t k0 = (int64_t)blockIdx.x * kMT;
+  const int64_t k0 = (int64_t)blockIdx.x * 16 * RT;
   const int split = blockIdx.z;
   const int cblk = blockIdx.y;
   const int c0 = cblk * kNT;
@@ -1489,18 +1493,17 @@ __global__ __launch_bounds__(kGThreads) void gauss_mfma_kernel(int64_t N, int d,
       gauss_copy_step(tcol + (j_begin / kKT) * (wc * kKT), wc, Ws[0], wave, lane);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     } else {
-      gauss_gen_step(seed, stream, k0, j_begin + gt % kKT, j_end, gt, Gs[0]);
+      gauss_gen_step<RT>(seed, stream, k0, j_begin + gt % kKT, j_end, gt, Gs[0]);
     }
     __syncthreads();
   }
   if (mfma_wave) {
-    const int rh = wave % kRH;  // row group: kRT 16-row tiles
-    const int cq = wave / kRH;  // column group: kCT 16-column tiles
-    f32x4_t acc[kRT][kCT];
+    const int cq = wave;  // column group: CT 16-column tiles
+    f32x4_t acc[RT][CT];
 #pragma unroll
-    for (int i = 0; i < kRT; ++i)
+    for (int i = 0; i < RT; ++i)
 #pragma unroll
-      for (int q = 0; q < kCT; ++q)
+      for (int q = 0; q < CT; ++q)
 #pragma unroll
         for (int r = 0; r < 4; ++r) acc[i][q][r] = 0.0f;
     for (int64_t s = 0; s < steps; ++s) {
@@ -1513,18 +1516,18 @@ __global__ __launch_bounds__(kGThreads) void gauss_mfma_kernel(int64_t N, int d,
 #pragma unroll
       for (int ks = 0; ks < kKT / 32; ++ks) {
         const int kk = 32 * ks + 8 * (lane >> 4);
-        bf16x8_t a[kRT];
+        bf16x8_t a[RT];
 #pragma unroll
-        for (int i = 0; i < kRT; ++i)
-          a[i] = *reinterpret_cast<const bf16x8_t*>(&Gb[swz(rh * 16 * kRT + i * 16 + (lane & 15), kk)]);
+        for (int i = 0; i < RT; ++i)
+          a[i] = *reinterpret_cast<const bf16x8_t*>(&Gb[swz(i * 16 + (lane & 15), kk)]);
 #pragma unroll
-        for (int q = 0; q < kCT; ++q) {
+        for (int q = 0; q < CT; ++q) {
           // tiles past [X|Y] multiply stale LDS and are never stored (a
           // wave-uniform skip measured slower: it splits the unrolled loop)
-          const int col = (cq * kCT + q) * 16 + (lane & 15);
+          const int col = (cq * CT + q) * 16 + (lane & 15);
           const bf16x8_t bv = *reinterpret_cast<const bf16x8_t*>(&Wb[swz(col, kk)]);
 #pragma unroll
-          for (int i = 0; i < kRT; ++i)
+          for (int i = 0; i < RT; ++i)
             acc[i][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], bv, acc[i][q], 0, 0, 0);
         }
       }
@@ -1532,13 +1535,13 @@ __global__ __launch_bounds__(kGThreads) void gauss_mfma_kernel(int64_t N, int d,
       __syncthreads();
     }
 #pragma unroll
-    for (int i = 0; i < kRT; ++i)
+    for (int i = 0; i < RT; ++i)
 #pragma unroll
-      for (int q = 0; q < kCT; ++q)
+      for (int q = 0; q < CT; ++q)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int64_t k = k0 + rh * 16 * kRT + i * 16 + 4 * (lane >> 4) + r;
-          const int t = cq * kCT + q;
+          const int64_t k = k0 + i * 16 + 4 * (lane >> 4) + r;
+          const int t = cq * CT + q;
           const int col = c0 + t * 16 + (lane & 15);
           if (k < m && col <= d && t * 16 < wc)
             part[((int64_t)split * m + k) * ldp + col] = acc[i][q][r];
@@ -1547,7 +1550,7 @@ __global__ __launch_bounds__(kGThreads) void gauss_mfma_kernel(int64_t N, int d,
     for (int64_t s = 0; s < steps; ++s) {
       // G of step s + 1 (zeros after the last step: never read)
       const int64_t j = j_begin + (s + 1) * kKT + gt % kKT;
-      gauss_gen_step(seed, stream, k0, j, j_end, gt, Gs[(s + 1) & 1]);
+      gauss_gen_step<RT>(seed, stream, k0, j, j_end, gt, Gs[(s + 1) & 1]);
       __syncthreads();
     }
   }
@@ -1957,9 +1960,32 @@ void gaussian_mfma(const GaussianArgs& a, hipStream_t s) {
   // blockIdx.x is the sketch-row block: the blocks that read the same data
   // rows and columns run side by side and share them through the caches
   const int ncb = (int)ceil_div(cols, kNT);
-  dim3 grid((unsigned)ceil_div(a.m, kMT), (unsigned)ncb, (unsigned)a.splits);
-  gauss_mfma_kernel<<<grid, kGThreads, 0, s>>>(a.N, a.d, tiles, nchunks, a.seed, a.stream_id, a.m,
-                                               a.splits, part, ldp);
+  const int ct = ncb > 1 ? kNT / 64 : (int)ceil_div(cols, 64);
+  auto go = [&](auto c, auto r) {
+    constexpr int CT = decltype(c)::value, RT = decltype(r)::value;
+    dim3 grid((unsigned)ceil_div(a.m, 16 * RT), (unsigned)ncb, (unsigned)a.splits);
+    gauss_mfma_kernel<CT, RT><<<grid, kGThreads, 0, s>>>(a.N, a.d, tiles, nchunks, a.seed,
+                                                         a.stream_id, a.m, a.splits, part, ldp);
+  };
+  using std::integral_constant;
+  // 128 sketch rows per block halve the copies of [X|Y] per entry of G: taken
+  // at 193..320 columns (2^20 x 256: 4.42 ms per pair of 1536 rows against 4.70
+  // with 64 rows) where the chip stays full.  Narrower blocks fit a CU twice with
+  // 64 rows, which gains more (2^20 x 128: 2.02 against 2.19 ms); wider ones have
+  // no registers for 128 rows' accumulators.
+  const bool tall = (ct == 4 || ct == 5) && ceil_div(a.m, 128) * a.splits >= 512;
+  const integral_constant<int, 4> r4{};
+  const integral_constant<int, 8> r8{};
+  switch (ct) {
+    case 1: go(integral_constant<int, 1>{}, r4); break;
+    case 2: go(integral_constant<int, 2>{}, r4); break;
+    case 3: go(integral_constant<int, 3>{}, r4); break;
+    case 4: tall ? go(integral_constant<int, 4>{}, r8) : go(integral_constant<int, 4>{}, r4); break;
+    case 5: tall ? go(integral_constant<int, 5>{}, r8) : go(integral_constant<int, 5>{}, r4); break;
+    case 6:
+    case 7: go(integral_constant<int, 7>{}, r4); break;
+    default: go(integral_constant<int, 9>{}, r4);
+  }
   SLSE_LAUNCH_CHECK();
   gauss_reduce_kernel<float, float><<<grid1(a.m * cols), 256, 0, s>>>(
       part, a.splits, a.m, cols, ldp, static_cast<float*>(a.A), a.lda);
