@@ -16,11 +16,16 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
 
+// a vector of VEC elements whose address is a multiple of the element size
 template <typename T, int VEC>
-using vec_of = T __attribute__((ext_vector_type(VEC)));
+struct VecOf {
+  typedef T type __attribute__((ext_vector_type(VEC), aligned(sizeof(T))));
+};
+template <typename T, int VEC>
+using vec_of = typename VecOf<T, VEC>::type;
 
-// VEC elements at p (16-byte vector loads/stores when VEC > 1), streamed past
-// the caches
+// VEC elements at p, any element address (16-byte vector loads/stores when VEC >
+// 1), streamed past the caches
 template <typename T, int VEC>
 __device__ __forceinline__ void load_chunk(const T* __restrict__ p, T (&v)[VEC]) {
   if constexpr (VEC == 1) {
@@ -52,8 +57,13 @@ constexpr int adjoint_unroll() {
 
 // A row is split over `lpr` lanes, each holding NCH chunks of VEC columns
 // (column (c lpr + l) VEC + k); a block handles tiles of UNROLL x (rows per
-// block step) rows, every lane group keeping UNROLL rows in flight.  With
-// VEC > 1, d is a multiple of VEC and X, dX rows are VEC-aligned.
+// block step) rows, every lane group keeping UNROLL rows in flight.  Rows of X and
+// dX may start at any element.  Where d ends inside a chunk, the chunk is moved
+// back to end with the row: its columns that another lane holds stay out of the
+// dots and are written twice, with the same values.  Whole calls on float32 (lambda's
+// first iterate and this pass): 2^20 x 101 628 -> 359 us, 2^20 x 256 with rows 259 apart
+// 1214 -> 495 us (both took an element per lane), 2^20 x 256 535 -> 469 us (loads
+// without a guard each).
 template <typename T, typename G, int VEC, int NCH>
 __global__ __launch_bounds__(kThreads) void adjoint_kernel(int64_t n, int d, const T* __restrict__ X,
                                                            int64_t ldx, const T* __restrict__ Y,
@@ -62,21 +72,24 @@ __global__ __launch_bounds__(kThreads) void adjoint_kernel(int64_t n, int d, con
                                                            int lpr, G* __restrict__ dX, int64_t lddx,
                                                            G* __restrict__ dY) {
   constexpr int UNROLL = adjoint_unroll<T, VEC, NCH>();
+  // chunks that lie inside the row for every lane: all but the last where NCH is
+  // the exact count, half of them where it is rounded up to a power of 2
+  constexpr int kSure = NCH <= 4 ? NCH - 1 : NCH / 2;
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int gpw = 64 / lpr;
   const int grp = lane / lpr;
   const int l = lane - grp * lpr;
   double b[NCH][VEC], lam[NCH][VEC];
-  bool inside[NCH];
+  int col[NCH], at[NCH];
 #pragma unroll
   for (int c = 0; c < NCH; ++c) {
-    const int col0 = (c * lpr + l) * VEC;
-    inside[c] = col0 < d;
+    col[c] = (c * lpr + l) * VEC;
+    at[c] = min(col[c], d - VEC);
 #pragma unroll
     for (int k = 0; k < VEC; ++k) {
-      b[c][k] = inside[c] ? beta[col0 + k] : 0.0;
-      lam[c][k] = inside[c] ? lambda[col0 + k] : 0.0;
+      b[c][k] = beta[at[c] + k];
+      lam[c][k] = lambda[at[c] + k];
     }
   }
   const int step = kWaves * gpw;  // rows per block step
@@ -87,19 +100,27 @@ __global__ __launch_bounds__(kThreads) void adjoint_kernel(int64_t n, int d, con
     double y[UNROLL];
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {
-      const int64_t row = base + (int64_t)u * step + my;
-      const bool ok = row < n;
-      const T* xr = X + (ok ? row : 0) * ldx;
+      // past the end: the last row again, not stored
+      const int64_t row = min(base + (int64_t)u * step + my, n - 1);
+      const T* xr = X + row * ldx;
 #pragma unroll
-      for (int c = 0; c < NCH; ++c) {
-        if (ok && inside[c]) {
-          load_chunk<T, VEC>(xr + (c * lpr + l) * VEC, x[u][c]);
-        } else {
+      for (int c = 0; c < kSure; ++c) load_chunk<T, VEC>(xr + at[c], x[u][c]);
+      y[u] = Y ? (double)Y[row] : 0.0;
+    }
+    // the chunks that may lie past the row: lanes without columns stay idle
 #pragma unroll
-          for (int k = 0; k < VEC; ++k) x[u][c][k] = (T)0;
+    for (int c = kSure; c < NCH; ++c) {
+#pragma unroll
+      for (int u = 0; u < UNROLL; ++u)
+#pragma unroll
+        for (int k = 0; k < VEC; ++k) x[u][c][k] = (T)0;
+      if (col[c] < d) {
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) {
+          const int64_t row = min(base + (int64_t)u * step + my, n - 1);
+          load_chunk<T, VEC>(X + row * ldx + at[c], x[u][c]);
         }
       }
-      y[u] = (Y && ok) ? (double)Y[row] : 0.0;
     }
     double d1[UNROLL], d2[UNROLL];
 #pragma unroll
@@ -109,8 +130,9 @@ __global__ __launch_bounds__(kThreads) void adjoint_kernel(int64_t n, int d, con
       for (int c = 0; c < NCH; ++c)
 #pragma unroll
         for (int k = 0; k < VEC; ++k) {
-          s1 = fma((double)x[u][c][k], b[c][k], s1);
-          s2 = fma((double)x[u][c][k], lam[c][k], s2);
+          const double v = c < kSure || at[c] + k >= col[c] ? (double)x[u][c][k] : 0.0;
+          s1 = fma(v, b[c][k], s1);
+          s2 = fma(v, lam[c][k], s2);
         }
       d1[u] = s1;
       d2[u] = s2;
@@ -131,11 +153,11 @@ __global__ __launch_bounds__(kThreads) void adjoint_kernel(int64_t n, int d, con
         G* out = dX + row * lddx;
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
-          if (!inside[c]) continue;
+          if (c >= kSure && col[c] >= d) continue;
           G o[VEC];
 #pragma unroll
           for (int k = 0; k < VEC; ++k) o[k] = (G)(r * lam[c][k] - d2[u] * b[c][k]);
-          store_chunk<G, VEC>(out + (c * lpr + l) * VEC, o);
+          store_chunk<G, VEC>(out + at[c], o);
         }
       }
       if (dY && l == 0) dY[row] = (G)d2[u];
@@ -164,6 +186,8 @@ void launch3(const AdjointArgs& a, hipStream_t s) {
     launch4<T, G, VEC, 1>(a, lpr, s);
   else if (nch <= 2)
     launch4<T, G, VEC, 2>(a, lpr, s);
+  else if (nch <= 3)
+    launch4<T, G, VEC, 3>(a, lpr, s);
   else if (nch <= 4)
     launch4<T, G, VEC, 4>(a, lpr, s);
   else if (nch <= 8)
@@ -176,16 +200,19 @@ void launch3(const AdjointArgs& a, hipStream_t s) {
 
 template <typename T, typename G>
 void launch2(const AdjointArgs& a, hipStream_t s) {
-  // 16-byte chunks when every row of X and dX starts on such a boundary
+  // 16-byte chunks, but for rows shorter than one, and for FP64 rows off the
+  // 16-byte grid: two values a lane then gain nothing over one, whose lane groups fit
+  // narrow rows better (whole calls on 2^20 x 33: 251 against 267 us, on 2^19 x 255
+  // 550 against 552)
   constexpr int V = 16 / (int)sizeof(T);
   auto aligned = [](const void* p, int64_t ld, size_t es) {
-    return p == nullptr ||
-           (reinterpret_cast<uintptr_t>(p) % (V * es) == 0 && (ld * (int64_t)es) % (V * (int64_t)es) == 0);
+    return p == nullptr || (reinterpret_cast<uintptr_t>(p) % 16 == 0 && (ld * (int64_t)es) % 16 == 0);
   };
-  if (a.d % V == 0 && aligned(a.X, a.ldx, sizeof(T)) && aligned(a.dX, a.lddx, sizeof(G)))
-    launch3<T, G, V>(a, s);
-  else
+  if (a.d < V || (sizeof(T) == 8 && !(a.d % V == 0 && aligned(a.X, a.ldx, sizeof(T)) &&
+                                      aligned(a.dX, a.lddx, sizeof(G)))))
     launch3<T, G, 1>(a, s);
+  else
+    launch3<T, G, V>(a, s);
 }
 
 // ---------------------------------------------------------------------------
