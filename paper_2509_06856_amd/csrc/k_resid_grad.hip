@@ -39,6 +39,7 @@ namespace {
 #endif
 constexpr int kThreads = SLSE_RG_THREADS;
 constexpr int kWaves = kThreads / 64;
+constexpr int64_t kFewRows = int64_t(1) << 12;  // launch shapes are timed from here on
 
 // a vector of VEC elements whose address is a multiple of the element size
 template <typename T, int VEC>
@@ -362,6 +363,9 @@ ResidGradPlan plan_resid_grad(int64_t n, int d, slse_dtype storage, const void* 
   // lane groups are powers of 2 up to a wave
   int lpr = 1;
   while (lpr < 64 && lpr * 16 <= nvec) lpr *= 2;
+  // few rows (the first levels of a schedule): one or two chunks per lane, so that
+  // the chip has waves for them (256..2048 rows of 32 float64: 11..19 -> SMALLRG us)
+  while (n < kFewRows && lpr < 64 && lpr * 2 < nvec) lpr *= 2;
   if (lpr_hint > 0) lpr = lpr_hint;
   if (const char* e = std::getenv("SLSE_RG_LPR")) lpr = std::atoi(e);
   lpr = std::max(1, std::min(64, lpr));

@@ -19,11 +19,12 @@ constexpr int kThreads = 256;
 
 // Up to this many columns one block takes the whole step: it sums the pass's
 // partial rows itself (no launch in between) and needs no hand-off between
-// blocks for the estimate (a whole solve of 16384 x 32, 40 steps: 867 -> 672 us
-// together with the passes' own hand-off gone).  One CU then reads M and the rows: at
-// 128 columns 0.4 MB, about what a launch costs; the rows and M grow with d
-// and d^2.
-constexpr int kOneBlockD = 128;
+// blocks for the estimate.  One CU then reads M and the rows, which grow with d^2
+// and d: whole solves replayed from graphs, the sum kernel and about 64 blocks
+// against one block, take 576 and 461 us at 16384 x 32, 738 and 698 us at 65536 x
+// 48, 732 and 717 us (float32) or 780 and 808 us (float64) at 65536 x 64, 766 and
+// 1000 us at 40000 x 100.
+constexpr int kOneBlockD = 48;
 constexpr int kOneThreads = 1024;
 
 // the estimate's last sums: gp = g . Mg, pp = ||Mg||^2, bb = ||beta_{t+1}||^2
