@@ -192,6 +192,34 @@ __global__ __launch_bounds__(kThreads) void iter_error_kernel(const double* __re
     rel_out[0] = s_r[0] > 0.0 ? sqrt(s_e[0] / s_r[0]) : sqrt(s_e[0]);
 }
 
+// One block, in place of up to five launches ahead of a solve (copies and fills of d
+// numbers, launch-bound).  Every input is read before an output is written, as in the
+// copies one after the other: the caller's arrays may alias each other.
+__global__ void __launch_bounds__(1024) iter_start_kernel(int d, const double* beta0,
+                                                          const double* beta_prev, double* b0,
+                                                          double* b1, double* beta_out,
+                                                          double* traj_row, int* flags) {
+  if (threadIdx.x < 4) flags[threadIdx.x] = 0;
+  for (int k = threadIdx.x; k < d; k += blockDim.x) {
+    b0[k] = beta0 ? beta0[k] : 0.0;
+    if (beta_prev) b1[k] = beta_prev[k];
+  }
+  __syncthreads();
+  for (int k = threadIdx.x; k < d; k += blockDim.x) {
+    if (beta_out) beta_out[k] = b0[k];
+    if (traj_row) traj_row[k] = b0[k];
+  }
+}
+
+__global__ void read_back_kernel(const int* __restrict__ flags, const int* __restrict__ info,
+                                 const double* __restrict__ sur, int T, double* __restrict__ out) {
+  for (int k = threadIdx.x; k < 8 + T; k += blockDim.x)
+    out[k] = k < 4 ? (flags ? (double)flags[k] : 0.0)
+             : k < 7 ? (double)info[k - 4]
+             : k < 8 ? 0.0
+                     : (sur ? sur[k - 8] : 0.0);
+}
+
 __global__ void fill_i32_kernel(int* __restrict__ p, int v, int64_t n) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x)
@@ -240,6 +268,18 @@ void launch_update(const UpdateArgs& a, hipStream_t s) {
 void launch_iter_error(const double* beta, const double* ref, int d, double* rel_out,
                        double* delta, hipStream_t s) {
   iter_error_kernel<<<1, kThreads, 0, s>>>(beta, ref, d, rel_out, delta);
+  SLSE_LAUNCH_CHECK();
+}
+
+void launch_iter_start(int d, const double* beta0, const double* beta_prev, double* b0, double* b1,
+                       double* beta_out, double* traj_row, int* flags, hipStream_t s) {
+  iter_start_kernel<<<1, 1024, 0, s>>>(d, beta0, beta_prev, b0, b1, beta_out, traj_row, flags);
+  SLSE_LAUNCH_CHECK();
+}
+
+void launch_read_back(const int* flags, const int* info, const double* sur, int T, double* out,
+                      hipStream_t s) {
+  read_back_kernel<<<1, 256, 0, s>>>(flags, info, sur, T, out);
   SLSE_LAUNCH_CHECK();
 }
 

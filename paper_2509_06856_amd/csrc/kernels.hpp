@@ -93,6 +93,14 @@ void launch_update(const UpdateArgs& a, hipStream_t s);
 // rel_out[0] = ||beta - ref|| / ||ref|| and delta = beta - ref (either may be null).
 void launch_iter_error(const double* beta, const double* ref, int d, double* rel_out,
                        double* delta, hipStream_t s);
+// b0 = beta_out = traj_row = beta0 (zeros if null), b1 = beta_prev (if given), the
+// four flags cleared (beta_out, traj_row may be null; the caller's arrays may alias)
+void launch_iter_start(int d, const double* beta0, const double* beta_prev, double* b0, double* b1,
+                       double* beta_out, double* traj_row, int* flags, hipStream_t s);
+// out[0..3] = flags, out[4..6] = info, out[8..] = the T estimates (flags or sur may be
+// null), written to pinned host memory
+void launch_read_back(const int* flags, const int* info, const double* sur, int T, double* out,
+                      hipStream_t s);
 void launch_copy_f64(const double* src, double* dst, int64_t n, hipStream_t s);
 void launch_fill_i32(int* dst, int value, int64_t n, hipStream_t s);
 void launch_fill_f64(double* dst, double value, int64_t n, hipStream_t s);

@@ -42,6 +42,7 @@ struct Arena {
   };
   std::map<std::string, Buf> bufs;
   bool grew = false;
+  uint64_t generation = 0;  // of the buffers' addresses: bumped when one is replaced or freed
 
   bool measuring = false;
   char* ext = nullptr;
@@ -94,6 +95,7 @@ struct Arena {
     }
     Buf& b = bufs[name];
     if (b.bytes >= bytes) return b.p;
+    ++generation;
     if (b.p) SLSE_HIP(hipFree(b.p));
     b.p = nullptr;
     b.bytes = 0;
@@ -113,11 +115,30 @@ struct Arena {
     return static_cast<T*>(get(name, count * sizeof(T), zero_init));
   }
   void release() {
+    ++generation;
     for (auto& kv : bufs)
       if (kv.second.p) (void)hipFree(kv.second.p);
     bufs.clear();
   }
 };
+
+// Buffers of one M-IHS iteration.
+struct IterBufs {
+  double* beta[3];
+  double* partial = nullptr;
+  double* g = nullptr;  // the summed partial rows (problems wider than the update sums itself)
+  double* sur_partial = nullptr;
+  int* sur_counter = nullptr;
+  int* flags = nullptr;  // [0] done, [1] non-finite
+  double* err_delta = nullptr;  // beta_t - beta_ref (per-iterate error accounting)
+  double* err_g = nullptr;      // discarded gradient of the prediction-error pass
+  int max_blocks = 1024;   // capacity of the partial rows
+  int grid_blocks = 512;   // grid of the residual-gradient launches (<= max_blocks)
+};
+
+// The three sets of them a context holds: of slse_fused_resid_grad, of the solves
+// and of the adjoint.
+enum IterSet { kIterGrad = 0, kIterSolve = 1, kIterAdjoint = 2, kIterSets = 3 };
 
 // Ends a borrowed (measuring or external) arena mode when it goes out of scope.
 struct BorrowScope {
@@ -150,6 +171,20 @@ struct slse_ctx {
   // by storage / accumulation / d / vector width / log2(rows), and (grid,
   // tiles per block) of batched steps, keyed by the batch shape
   std::map<std::string, std::pair<int, int>> rg_tune;
+  // the residual-gradient entries of rg_tune met so far, under a number: a call looks
+  // its shape up several times
+  mutable std::map<uint64_t, std::pair<int, int>> rg_found;
+  // the iteration buffers last reserved, valid while the arena's addresses are
+  struct {
+    uint64_t generation = 0;
+    int64_t d = -1;
+    slse::IterBufs b;
+  } iter[slse::kIterSets];
+  // what a report reads back (pinned host memory that a kernel writes) and the events
+  // of a timed call: made with the context, so that no call allocates for them
+  static constexpr int kReportSteps = 1016;  // estimates it holds
+  double* h_report = nullptr;
+  hipEvent_t timer[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
   std::string arch;  // gcnArchName of the device and its compute-unit count
   void drop_graphs() {
     for (auto& kv : graphs) (void)hipGraphExecDestroy(kv.second);
@@ -433,22 +468,13 @@ void enqueue_factor(const FactorBufs& f, int64_t rows, int d, const void* A, int
 // ---------------------------------------------------------------------------
 // The M-IHS iteration engine shared by the forward solve and the adjoint.
 // ---------------------------------------------------------------------------
-struct IterBufs {
-  double* beta[3];
-  double* partial = nullptr;
-  double* g = nullptr;  // the summed partial rows (problems wider than the update sums itself)
-  double* sur_partial = nullptr;
-  int* sur_counter = nullptr;
-  int* flags = nullptr;  // [0] done, [1] non-finite
-  double* err_delta = nullptr;  // beta_t - beta_ref (per-iterate error accounting)
-  double* err_g = nullptr;      // discarded gradient of the prediction-error pass
-  int max_blocks = 1024;   // capacity of the partial rows
-  int grid_blocks = 512;   // grid of the residual-gradient launches (<= max_blocks)
-};
-
-IterBufs reserve_iter(slse_ctx* ctx, int64_t d, const char* tag) {
+IterBufs reserve_iter(slse_ctx* ctx, int64_t d, IterSet set) {
+  auto& kept = ctx->iter[set];
+  const bool own = !ctx->arena.borrowed();
+  if (own && kept.d == d && kept.generation == ctx->arena.generation) return kept.b;
   IterBufs b;
-  std::string t(tag);
+  const char* tags[kIterSets] = {"rg", "it", "adj"};
+  std::string t(tags[set]);
   for (int i = 0; i < 3; ++i) b.beta[i] = ctx->arena.get_t<double>(t + "_beta" + char('0' + i), d);
   b.max_blocks = std::max(256, 8 * ctx->num_cus);
   b.grid_blocks = std::max(64, 2 * ctx->num_cus);
@@ -460,27 +486,49 @@ IterBufs reserve_iter(slse_ctx* ctx, int64_t d, const char* tag) {
   b.flags = ctx->arena.get_t<int>(t + "_flags", 4);
   b.err_delta = ctx->arena.get_t<double>(t + "_errd", d);
   b.err_g = ctx->arena.get_t<double>(t + "_errg", d);
+  if (own) {
+    kept.b = b;
+    kept.d = d;
+    kept.generation = ctx->arena.generation;
+  }
   return b;
 }
 
-std::string rg_key(int64_t n, int d, slse_dtype storage, slse_dtype accum, const void* X,
-                   int64_t ldx) {
-  const int es = (int)dtype_size(storage);
-  const bool vec = (reinterpret_cast<uintptr_t>(X) % 16 == 0) && ((ldx * es) % 16 == 0);
-  int lg = 0;
-  while ((int64_t(1) << (lg + 1)) <= n) ++lg;
-  return std::to_string((int)storage) + "/" + std::to_string((int)accum) + "/" +
-         std::to_string(d) + "/" + (vec ? "v" : "s") + "/" + std::to_string(lg);
+// The shape class that a launch shape is tuned for.
+struct RgClass {
+  slse_dtype storage, accum;
+  int d, lg;  // lg = floor(log2(rows))
+  bool vec;   // rows on the 16-byte grid
+  RgClass(int64_t n, int d_, slse_dtype st, slse_dtype ac, const void* X, int64_t ldx)
+      : storage(st), accum(ac), d(d_), lg(0) {
+    const int es = (int)dtype_size(st);
+    vec = (reinterpret_cast<uintptr_t>(X) % 16 == 0) && ((ldx * es) % 16 == 0);
+    while ((int64_t(1) << (lg + 1)) <= n) ++lg;
+  }
+  std::string key() const {
+    return std::to_string((int)storage) + "/" + std::to_string((int)accum) + "/" +
+           std::to_string(d) + "/" + (vec ? "v" : "s") + "/" + std::to_string(lg);
+  }
+  uint64_t number() const {
+    return (uint64_t)storage | (uint64_t)accum << 2 | (uint64_t)vec << 4 | (uint64_t)lg << 8 |
+           (uint64_t)d << 16;
+  }
+};
+
+// the tuned (grid, lanes per row) of a class, or null
+const std::pair<int, int>* tuned_shape(const slse_ctx* ctx, const RgClass& c) {
+  const uint64_t k = c.number();
+  if (auto it = ctx->rg_found.find(k); it != ctx->rg_found.end()) return &it->second;
+  if (auto it = ctx->rg_tune.find(c.key()); it != ctx->rg_tune.end())
+    return &ctx->rg_found.emplace(k, it->second).first->second;
+  return nullptr;
 }
 
 ResidGradPlan rg_plan(const slse_ctx* ctx, const IterBufs& b, int64_t n, int d,
                       slse_dtype storage, slse_dtype accum, const void* X, int64_t ldx) {
-  if (ctx) {
-    auto it = ctx->rg_tune.find(rg_key(n, d, storage, accum, X, ldx));
-    if (it != ctx->rg_tune.end())
-      return plan_resid_grad(n, d, storage, X, ldx, it->second.first, b.max_blocks,
-                             it->second.second);
-  }
+  if (ctx)
+    if (const auto* t = tuned_shape(ctx, RgClass(n, d, storage, accum, X, ldx)))
+      return plan_resid_grad(n, d, storage, X, ldx, t->first, b.max_blocks, t->second);
   return plan_resid_grad(n, d, storage, X, ldx, b.grid_blocks, b.max_blocks);
 }
 
@@ -490,10 +538,10 @@ void tune_resid_grad(slse_ctx* ctx, const IterBufs& b, int64_t n, int d, slse_dt
                      slse_dtype accum, const void* X, int64_t ldx, const void* Y, int64_t incy,
                      hipStream_t st) {
   if (n < (int64_t(1) << 12)) return;
+  const RgClass cls(n, d, storage, accum, X, ldx);
+  if (tuned_shape(ctx, cls)) return;
   if (const char* e = std::getenv("SLSE_AUTOTUNE"))
     if (std::atoi(e) == 0) return;
-  const std::string key = rg_key(n, d, storage, accum, X, ldx);
-  if (ctx->rg_tune.count(key)) return;
   const ResidGradPlan base = plan_resid_grad(n, d, storage, X, ldx, b.grid_blocks, b.max_blocks);
   std::vector<int> lprs;
   for (int l : {base.lpr / 2, base.lpr, base.lpr * 2, base.lpr * 4})
@@ -540,7 +588,7 @@ void tune_resid_grad(slse_ctx* ctx, const IterBufs& b, int64_t n, int d, slse_dt
     }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
-  ctx->rg_tune[key] = pick;
+  ctx->rg_tune[cls.key()] = pick;
 }
 
 // Per-iterate errors against a reference vector (slse_params.beta_ref):
@@ -566,6 +614,18 @@ struct Stepper {
   hipStream_t st;
   const slse_ctx* ctx = nullptr;
   ErrorSink err;
+  // the last step's launch shape and what it was made for
+  struct RowsOf {
+    int64_t n = -1;
+    const void* X = nullptr;
+    int64_t ldx = 0;
+    slse_dtype storage = SLSE_F64, accum = SLSE_F64;
+    bool operator==(const RowsOf& o) const {
+      return n == o.n && X == o.X && ldx == o.ldx && storage == o.storage && accum == o.accum;
+    }
+  };
+  ResidGradPlan plan;
+  RowsOf plan_rows;
 
   // errors of the current iterate beta_t (t = this->t)
   void record_errors() {
@@ -590,20 +650,15 @@ struct Stepper {
     launch_sum_rows(b.partial, pl.blocks, pl.ldp, d, 1.0, b.err_g, err.pred + t, st);
   }
 
-  // beta_{t0} = beta0 (zeros if NULL), beta_{t0-1} = beta_prev (beta0 if NULL)
-  void start(const double* beta0, double* traj, const double* beta_prev = nullptr, int t0 = 0) {
-    if (beta0)
-      launch_copy_f64(beta0, b.beta[0], d, st);
-    else
-      launch_fill_f64(b.beta[0], 0.0, d, st);
-    cur = prev = 0;
-    if (beta_prev) {
-      launch_copy_f64(beta_prev, b.beta[1], d, st);
-      prev = 1;
-    }
+  // beta_{t0} = beta0 (zeros if NULL), beta_{t0-1} = beta_prev (beta0 if NULL);
+  // beta_out (may be NULL) = beta_{t0}
+  void start(const double* beta0, double* traj, const double* beta_prev = nullptr, int t0 = 0,
+             double* beta_out = nullptr) {
+    launch_iter_start(d, beta0, beta_prev, b.beta[0], b.beta[1], beta_out,
+                      traj ? traj + (int64_t)t0 * d : nullptr, b.flags, st);
+    cur = 0;
+    prev = beta_prev ? 1 : 0;
     t = t0;
-    if (traj) launch_copy_f64(b.beta[0], traj + (int64_t)t0 * d, d, st);
-    launch_fill_i32(b.flags, 0, 4, st);
     record_errors();
   }
   // (beta_{t-1}, beta_t) of the current iterate
@@ -617,7 +672,12 @@ struct Stepper {
   void step(int64_t n, const void* X, int64_t ldx, const void* Y, int64_t incy, slse_dtype storage,
             slse_dtype accum, double scale, const double* w, double mu, double eta, double* beta_out,
             double* traj, double* sur, double tol, int64_t incw = 1) {
-    const ResidGradPlan pl = rg_plan(ctx, b, n, d, storage, accum, X, ldx);
+    const RowsOf rows{n, X, ldx, storage, accum};
+    if (!(rows == plan_rows)) {
+      plan = rg_plan(ctx, b, n, d, storage, accum, X, ldx);
+      plan_rows = rows;
+    }
+    const ResidGradPlan& pl = plan;
     ResidGradArgs a;
     a.n = n;
     a.d = d;
@@ -748,7 +808,7 @@ SolvePlan reserve_solve(slse_ctx* ctx, const slse_problem* p, const slse_params*
   reserve_sketch(ctx, pl.sk, pl.st_t, &pl.srht, &pl.ga, &pl.gh,
                  q->precision == SLSE_PREC_MIXED && q->kind == SLSE_GAUSSIAN, &pl.cs);
   pl.f = reserve_factor(ctx, pl.sk.r, p->d, q->factor);
-  pl.it = reserve_iter(ctx, p->d, "it");
+  pl.it = reserve_iter(ctx, p->d, kIterSolve);
   // the per-step error estimates always land somewhere: the caller's buffer or ours
   pl.sur = q->surrogate ? q->surrogate
                         : ctx->arena.get_t<double>("sur_hist", (size_t)total_steps(q) + 1);
@@ -786,8 +846,7 @@ void enqueue_solve(const slse_ctx* ctx, const SolvePlan& pl, const slse_problem*
   int t0, t1;
   step_range(q, t0, t1);
   Stepper S{pl.it, d, pl.f.M, 0, 0, 0, st, ctx, error_sink(p, q)};
-  S.start(q->beta0, q->trajectory, q->beta_prev, t0);
-  launch_copy_f64(S.b.beta[0], beta_out, d, st);
+  S.start(q->beta0, q->trajectory, q->beta_prev, t0, beta_out);
   const size_t es = dtype_size(pl.st_t);
   int g = 0;  // global index of the next step
   // stage 1: a_i steps on the prefix of m_i sketched rows (eq. (98))
@@ -852,22 +911,17 @@ void launch_cached_graph(slse_ctx* ctx, const std::string& key, hipStream_t st, 
   SLSE_HIP(hipGraphLaunch(itg->second, st));
 }
 
-// Events of a timed call: [0] start, [1..4] phase ends (the last = the end).
+// Events of a timed call (the context's own): [0] start, [1..4] phase ends (the
+// last = the end).
 struct CallTimer {
-  hipEvent_t e[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
+  hipEvent_t* e = nullptr;
   int n = 0;
-  CallTimer(bool on, bool phases, hipStream_t st) {
+  CallTimer(slse_ctx* ctx, bool on, bool phases, hipStream_t st) : e(ctx->timer) {
     if (!on) return;
     n = phases ? 5 : 2;
-    for (int i = 0; i < n; ++i) SLSE_HIP(hipEventCreate(&e[i]));
     SLSE_HIP(hipEventRecord(e[0], st));
   }
-  ~CallTimer() {
-    for (int i = 0; i < n; ++i)
-      if (e[i]) (void)hipEventDestroy(e[i]);
-  }
   hipEvent_t* phase_events() { return n == 5 ? e + 1 : nullptr; }
-  hipEvent_t end() const { return n == 5 ? e[4] : e[1]; }
   void record_end(hipStream_t st) {
     if (n == 2) SLSE_HIP(hipEventRecord(e[1], st));
   }
@@ -878,19 +932,44 @@ struct CallTimer {
   }
 };
 
-slse_status finish_report(const SolvePlan& pl, const slse_params* q, slse_report* rep,
-                          hipStream_t st, const CallTimer& tm) {
+// Waits for the stream and hands back the flags, the factorization's info and the
+// T error estimates (flags, sur may be null).  One kernel writes them to the context's
+// pinned memory, in place of up to three copies to pageable memory that each wait
+// (factor of 400 x 100, one copy: 99 -> 78 us; eager 16384 x 32 solve with its report,
+// three: 611 -> 560 us together with the one launch that starts the iteration).
+struct ReadBack {
   int flags[4] = {0, 0, 0, 0};
   int info[3] = {0, 0, 0};
-  SLSE_HIP(hipMemcpyAsync(flags, pl.it.flags, sizeof(flags), hipMemcpyDeviceToHost, st));
-  SLSE_HIP(hipMemcpyAsync(info, pl.f.info, sizeof(info), hipMemcpyDeviceToHost, st));
+  std::vector<double> sur;
+};
+ReadBack read_back(slse_ctx* ctx, const int* flags, const int* info, const double* sur, int T,
+                   hipStream_t st) {
+  const double* h = ctx->h_report;
+  const bool fits = sur && T <= slse_ctx::kReportSteps;
+  launch_read_back(flags, info, fits ? sur : nullptr, fits ? T : 0, ctx->h_report, st);
   SLSE_HIP(hipStreamSynchronize(st));
+  ReadBack r;
+  for (int i = 0; i < 4; ++i) r.flags[i] = (int)h[i];
+  for (int i = 0; i < 3; ++i) r.info[i] = (int)h[4 + i];
+  if (!sur || T <= 0) return r;
+  r.sur.assign(h + 8, h + 8 + (fits ? T : 0));
+  if (!fits) {  // more steps than it holds
+    r.sur.resize(T);
+    SLSE_HIP(hipMemcpy(r.sur.data(), sur, sizeof(double) * T, hipMemcpyDeviceToHost));
+  }
+  return r;
+}
+
+slse_status finish_report(slse_ctx* ctx, const SolvePlan& pl, const slse_params* q,
+                          slse_report* rep, hipStream_t st, const CallTimer& tm) {
+  const ReadBack rb = read_back(ctx, pl.it.flags, pl.f.info, rep ? pl.sur : nullptr,
+                                rep && pl.sur ? total_steps(q) : 0, st);
   slse_status status = SLSE_OK;
-  if (info[0] != 0 || info[1] != 0 || info[2] != 0)
+  if (rb.info[0] != 0 || rb.info[1] != 0 || rb.info[2] != 0)
     status = SLSE_ESINGULAR;
-  else if (flags[1])
+  else if (rb.flags[1])
     status = SLSE_ENONFINITE;
-  else if (q->tol > 0 && !flags[0])
+  else if (q->tol > 0 && !rb.flags[0])
     status = SLSE_ENOTCONV;
   if (rep) {
     std::memset(rep, 0, sizeof(*rep));
@@ -904,8 +983,7 @@ slse_status finish_report(const SolvePlan& pl, const slse_params* q, slse_report
     rep->stage1_steps = std::max(0, std::min(t1, s1) - t0);
     rep->stage2_steps = std::max(0, t1 - u2);
     if (t1 > t0 && pl.sur) {
-      std::vector<double> sur(T, 0.0);
-      SLSE_HIP(hipMemcpy(sur.data(), pl.sur, sizeof(double) * T, hipMemcpyDeviceToHost));
+      const std::vector<double>& sur = rb.sur;
       int taken = 0;
       for (int t = u2; t < t1; ++t) {
         ++taken;
@@ -971,7 +1049,7 @@ slse_status solve_impl(slse_ctx* ctx, const slse_problem* p, const slse_params* 
                       base + (size_t)p->d * es, pl.lda, st);
     }
   }
-  CallTimer tm(rep != nullptr, rep != nullptr && !q->use_graph, st);
+  CallTimer tm(ctx, rep != nullptr, rep != nullptr && !q->use_graph, st);
   if (q->use_graph) {
     launch_cached_graph(ctx, graph_key("solve", p, q, beta_out, ws, ws_bytes), st,
                         [&](hipStream_t cs) { enqueue_solve(ctx, pl, p, q, beta_out, cs); });
@@ -982,7 +1060,7 @@ slse_status solve_impl(slse_ctx* ctx, const slse_problem* p, const slse_params* 
   remember_preconditioner(ctx, p, q, ws == nullptr);
   tm.record_end(st);
   slse_status status = SLSE_OK;
-  if (rep || q->tol > 0) status = finish_report(pl, q, rep, st, tm);
+  if (rep || q->tol > 0) status = finish_report(ctx, pl, q, rep, st, tm);
   return status;
 }
 
@@ -1002,8 +1080,7 @@ void enqueue_ihs(const slse_ctx* ctx, const SolvePlan& pl, const slse_problem* p
   const int d = (int)p->d;
   const SketchShape& sk = pl.sk;
   Stepper S{pl.it, d, pl.f.M, 0, 0, 0, st, ctx, ErrorSink{}};
-  S.start(q->beta0, q->trajectory);
-  launch_copy_f64(S.b.beta[0], beta_out, d, st);
+  S.start(q->beta0, q->trajectory, nullptr, 0, beta_out);
   for (int t = 0; t < q->s_max; ++t) {
     enqueue_sketch(sk, q->seed + (uint64_t)t, p->X, p->ldx, p->Y, pl.st_t, pl.A, pl.lda, pl.Ahat,
                    pl.ldah, pl.srht, pl.ga, pl.gh, st, pl.cs);
@@ -1038,7 +1115,7 @@ slse_status ihs_impl(slse_ctx* ctx, const slse_problem* p, const slse_params* q,
   SolvePlan pl = reserve_solve(ctx, p, &qq);
   if (ctx->arena.grew) ctx->drop_graphs();
   tune_resid_grad(ctx, pl.it, p->N, (int)p->d, pl.st_t, SLSE_F64, p->X, p->ldx, p->Y, 1, st);
-  CallTimer tm(rep != nullptr, false, st);
+  CallTimer tm(ctx, rep != nullptr, false, st);
   if (qq.use_graph)
     launch_cached_graph(ctx, graph_key("ihs", p, &qq, beta_out, nullptr, 0), st,
                         [&](hipStream_t cs) { enqueue_ihs(ctx, pl, p, &qq, beta_out, cs); });
@@ -1049,7 +1126,7 @@ slse_status ihs_impl(slse_ctx* ctx, const slse_problem* p, const slse_params* q,
   if (!rep) return SLSE_OK;
   slse_params qr = qq;  // the report counts the s_max full-data steps
   qr.K = 0;
-  return finish_report(pl, &qr, rep, st, tm);
+  return finish_report(ctx, pl, &qr, rep, st, tm);
 }
 
 // ---------------------------------------------------------------------------
@@ -1083,7 +1160,7 @@ slse_status backward_impl(slse_ctx* ctx, const slse_problem* p, const slse_param
     reserve_sketch(ctx, pl.sk, pl.st_t, &pl.srht, &pl.ga, &pl.gh,
                    q->precision == SLSE_PREC_MIXED && q->kind == SLSE_GAUSSIAN, &pl.cs);
   }
-  IterBufs ib = reserve_iter(ctx, p->d, "adj");
+  IterBufs ib = reserve_iter(ctx, p->d, kIterAdjoint);
   double* lam0 = ctx->arena.get_t<double>("adj_lam0", d);
   double* zero = ctx->arena.get_t<double>("adj_zero", (int64_t)d * 1);
   if (ctx->arena.grew) ctx->drop_graphs();
@@ -1138,13 +1215,9 @@ slse_status backward_impl(slse_ctx* ctx, const slse_problem* p, const slse_param
   if (dX || dY) launch_adjoint(a, st);
   slse_status status = SLSE_OK;
   if (rep) {
-    int flags[4] = {0, 0, 0, 0};
-    int info[3] = {0, 0, 0};
-    SLSE_HIP(hipMemcpyAsync(flags, ib.flags, sizeof(flags), hipMemcpyDeviceToHost, st));
-    SLSE_HIP(hipMemcpyAsync(info, pl.f.info, sizeof(info), hipMemcpyDeviceToHost, st));
-    SLSE_HIP(hipStreamSynchronize(st));
-    if (info[0] || info[1] || info[2]) status = SLSE_ESINGULAR;
-    else if (flags[1]) status = SLSE_ENONFINITE;
+    const ReadBack rb = read_back(ctx, ib.flags, pl.f.info, nullptr, 0, st);
+    if (rb.info[0] || rb.info[1] || rb.info[2]) status = SLSE_ESINGULAR;
+    else if (rb.flags[1]) status = SLSE_ENONFINITE;
     std::memset(rep, 0, sizeof(*rep));
     rep->status = status;
     rep->stage2_steps = q->s_max;
@@ -2020,6 +2093,11 @@ slse_status slse_ctx_create(slse_ctx** out, int device) {
     ctx->num_cus = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
     ctx->arch = std::string(prop.gcnArchName) + "/" + std::to_string(ctx->num_cus);
     SLSE_HIP(hipStreamCreateWithFlags(&ctx->capture_stream, hipStreamNonBlocking));
+    for (hipEvent_t& e : ctx->timer) SLSE_HIP(hipEventCreate(&e));
+    void* report = nullptr;
+    SLSE_HIP(hipHostMalloc(&report, (8 + slse_ctx::kReportSteps) * sizeof(double),
+                           hipHostMallocDefault));
+    ctx->h_report = static_cast<double*>(report);
     setup_noalloc_scratch(device);
     *out = ctx.release();
     return SLSE_OK;
@@ -2034,6 +2112,9 @@ slse_status slse_ctx_destroy(slse_ctx* ctx) {
     ctx->drop_graphs();
     ctx->arena.release();
     if (ctx->batch_done) (void)hipEventDestroy(ctx->batch_done);
+    for (hipEvent_t e : ctx->timer)
+      if (e) (void)hipEventDestroy(e);
+    if (ctx->h_report) (void)hipHostFree(ctx->h_report);
     if (ctx->capture_stream) (void)hipStreamDestroy(ctx->capture_stream);
     delete ctx;
     return SLSE_OK;
@@ -2099,9 +2180,8 @@ slse_status slse_factor(slse_ctx* ctx, int64_t rows, int64_t d, const void* A, i
     if (ctx->arena.grew) ctx->drop_graphs();
     ctx->pre.valid = false;
     enqueue_factor(f, rows, (int)d, A, lda, a_t, scale, method, st, R, ldr, M, ldm);
-    int info[3] = {0, 0, 0};
-    SLSE_HIP(hipMemcpyAsync(info, f.info, sizeof(info), hipMemcpyDeviceToHost, st));
-    SLSE_HIP(hipStreamSynchronize(st));
+    const ReadBack rb = read_back(ctx, nullptr, f.info, nullptr, 0, st);
+    const int* info = rb.info;
     if (info[0] || info[1] || info[2]) {
       set_last_error("factorization: non-positive or non-finite pivot at column " +
                      std::to_string((info[0] ? info[0] : info[1] ? info[1] : info[2]) - 1));
@@ -2125,7 +2205,7 @@ slse_status slse_fused_resid_grad(slse_ctx* ctx, int64_t n, int64_t d, const voi
     DeviceGuard g(ctx->device);
     hipStream_t st = as_stream(stream);
     ctx->arena.grew = false;
-    IterBufs b = reserve_iter(ctx, d, "rg");
+    IterBufs b = reserve_iter(ctx, d, kIterGrad);
     if (ctx->arena.grew) ctx->drop_graphs();
     if (n > 0) tune_resid_grad(ctx, b, n, (int)d, storage, accum, X, ldx, Y, 1, st);
     const ResidGradPlan pl = rg_plan(ctx, b, n, (int)d, storage, accum, X, ldx);
@@ -2353,6 +2433,7 @@ slse_status slse_ctx_load_tuning(slse_ctx* ctx, const char* path, int32_t* loade
     }
     int n = 0;
     if (ctx->arch == arch) {  // entries of another part or CU count are ignored
+      ctx->rg_found.clear();
       char key[256];
       int a = 0, b = 0;
       while (std::fscanf(f, "%255s %d %d", key, &a, &b) == 3) {

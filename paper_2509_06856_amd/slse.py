@@ -18,12 +18,13 @@ _FACTOR = {"chol": L.SLSE_FACTOR_CHOL, "qr": L.SLSE_FACTOR_QR}
 _PREC = {"f64": L.SLSE_PREC_F64, "mixed": L.SLSE_PREC_MIXED}
 
 
+# the declared argument types turn a plain int (or None) into a pointer
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
+    return t.data_ptr() if t is not None else None
 
 
 def _stream(device=None):
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+    return torch.cuda.current_stream(device).cuda_stream
 
 
 def _need_cuda(*ts):
@@ -148,17 +149,17 @@ class Params:
         q.fp32_sweeps = self.fp32_sweeps
         q.momentum_reset = 1 if self.momentum_reset else 0
         q.factor = _FACTOR[self.factor]
-        q.beta0 = _ptr(beta0).value
-        q.trajectory = _ptr(trajectory).value
-        q.surrogate = _ptr(surrogate).value
+        q.beta0 = _ptr(beta0)
+        q.trajectory = _ptr(trajectory)
+        q.surrogate = _ptr(surrogate)
         q.use_graph = 1 if self.use_graph else 0
-        q.beta_ref = _ptr(beta_ref).value
-        q.rel_err = _ptr(rel_err).value
-        q.pred_err = _ptr(pred_err).value
+        q.beta_ref = _ptr(beta_ref)
+        q.rel_err = _ptr(rel_err)
+        q.pred_err = _ptr(pred_err)
         q.start_step = int(start_step)
         q.stop_step = int(stop_step)
-        q.beta_prev = _ptr(beta_prev).value
-        q.state_out = _ptr(state_out).value
+        q.beta_prev = _ptr(beta_prev)
+        q.state_out = _ptr(state_out)
         return q
 
 
