@@ -39,7 +39,6 @@ namespace {
 #endif
 constexpr int kThreads = SLSE_RG_THREADS;
 constexpr int kWaves = kThreads / 64;
-constexpr int64_t kFewRows = int64_t(1) << 12;  // launch shapes are timed from here on
 
 // a vector of VEC elements whose address is a multiple of the element size
 template <typename T, int VEC>
@@ -359,13 +358,14 @@ ResidGradPlan plan_resid_grad(int64_t n, int d, slse_dtype storage, const void* 
   // vectors at any element address; rows shorter than one take an element per lane
   pl.vec = d >= vfull ? vfull : 1;
   const int nvec = (int)ceil_div(d, pl.vec);
-  // default: about eight vector chunks per lane (measured best for wide rows);
-  // lane groups are powers of 2 up to a wave
+  // Four to eight elements per lane, lane groups a power of 2 up to a wave: a wave's
+  // loads then cover whole rows side by side, and few rows still fill the chip.  Best or
+  // within 3% of it from 4096 to 16 million rows of 16 to 512 columns in both types;
+  // eight vectors per lane, in comparison: 16384 x 32 float64 11.6 -> 6.8 us (the
+  // gradient with its sum), 2^21 x 32 float32 165 -> 49 us, 2^20 x 256 float32
+  // 168 -> 162 us.
   int lpr = 1;
-  while (lpr < 64 && lpr * 16 <= nvec) lpr *= 2;
-  // few rows (the first levels of a schedule): one or two chunks per lane, so that
-  // the chip has waves for them (256..2048 rows of 32 float64: 11..19 -> SMALLRG us)
-  while (n < kFewRows && lpr < 64 && lpr * 2 < nvec) lpr *= 2;
+  while (lpr < 64 && lpr * 8 <= d) lpr *= 2;
   if (lpr_hint > 0) lpr = lpr_hint;
   if (const char* e = std::getenv("SLSE_RG_LPR")) lpr = std::atoi(e);
   lpr = std::max(1, std::min(64, lpr));

@@ -532,6 +532,8 @@ ResidGradPlan rg_plan(const slse_ctx* ctx, const IterBufs& b, int64_t n, int d,
   return plan_resid_grad(n, d, storage, X, ldx, b.grid_blocks, b.max_blocks);
 }
 
+constexpr float kBriefMs = 0.02f;  // passes shorter than this are timed in a longer queue
+
 // Time a few (grid, lane-group) shapes of the residual-gradient pass on the
 // actual data and keep the fastest for this shape (never inside a capture).
 void tune_resid_grad(slse_ctx* ctx, const IterBufs& b, int64_t n, int d, slse_dtype storage,
@@ -543,25 +545,25 @@ void tune_resid_grad(slse_ctx* ctx, const IterBufs& b, int64_t n, int d, slse_dt
   if (const char* e = std::getenv("SLSE_AUTOTUNE"))
     if (std::atoi(e) == 0) return;
   const ResidGradPlan base = plan_resid_grad(n, d, storage, X, ldx, b.grid_blocks, b.max_blocks);
-  std::vector<int> lprs;
-  for (int l : {base.lpr / 2, base.lpr, base.lpr * 2, base.lpr * 4})
-    if (l >= 1 && l <= 64) lprs.push_back(l);
-  std::vector<int> grids;
-  for (int g : {ctx->num_cus, 2 * ctx->num_cus, 4 * ctx->num_cus})
-    if (g <= b.max_blocks) grids.push_back(g);
   hipEvent_t e0, e1;
   SLSE_HIP(hipEventCreate(&e0));
   SLSE_HIP(hipEventCreate(&e1));
   float best = 1e30f;
   std::pair<int, int> pick{base.blocks, base.lpr};
-  for (int g : grids)
-    for (int l : lprs) {
+  std::vector<std::pair<int, int>> timed;  // (blocks, lanes per row) seen
+  // the rule's own shape first
+  for (int l : {base.lpr, base.lpr / 2, base.lpr * 2})
+    for (int g : {2 * ctx->num_cus, ctx->num_cus, 4 * ctx->num_cus}) {
+      if (l < 1 || l > 64 || g > b.max_blocks) continue;
       ResidGradPlan pl;
       try {
         pl = plan_resid_grad(n, d, storage, X, ldx, g, b.max_blocks, l);
       } catch (const Error&) {
         continue;
       }
+      const std::pair<int, int> shape{pl.blocks, pl.lpr};
+      if (std::find(timed.begin(), timed.end(), shape) != timed.end()) continue;
+      timed.push_back(shape);
       ResidGradArgs a;
       a.n = n;
       a.d = d;
@@ -574,14 +576,24 @@ void tune_resid_grad(slse_ctx* ctx, const IterBufs& b, int64_t n, int d, slse_dt
       a.beta = b.beta[0];
       a.partial = b.partial;
       a.capacity_blocks = b.max_blocks;
-      launch_resid_grad(pl, a, st);
-      SLSE_HIP(hipEventRecord(e0, st));
-      for (int r = 0; r < 3; ++r) launch_resid_grad(pl, a, st);
-      SLSE_HIP(hipEventRecord(e1, st));
-      SLSE_HIP(hipEventSynchronize(e1));
-      float ms = 0.f;
-      SLSE_HIP(hipEventElapsedTime(&ms, e0, e1));
-      if (ms < best) {
+      auto run = [&](int ahead, int reps) {
+        for (int r = 0; r < ahead; ++r) launch_resid_grad(pl, a, st);
+        SLSE_HIP(hipEventRecord(e0, st));
+        for (int r = 0; r < reps; ++r) launch_resid_grad(pl, a, st);
+        SLSE_HIP(hipEventRecord(e1, st));
+        SLSE_HIP(hipEventSynchronize(e1));
+        float ms = 0.f;
+        SLSE_HIP(hipEventElapsedTime(&ms, e0, e1));
+        return ms / reps;
+      };
+      // Three passes of a few microseconds end before the host has queued the next
+      // (every shape then measures the host: at 16384 x 32 float64 a shape of 10.2 us
+      // was kept where one of 5.6 was timed too).  Short passes are timed behind others
+      // in the queue, and only a clear gain moves them off the rule's shape.
+      float ms = run(1, 3);
+      const bool brief = ms < kBriefMs;
+      if (brief) ms = run(6, 12);
+      if (ms < (brief ? 0.95f : 1.f) * best) {
         best = ms;
         pick = {g, pl.lpr};
       }
