@@ -259,95 +259,195 @@ __global__ __launch_bounds__((pass_threads<CT, BB, ROUNDS>())) void fwht_pass_ba
   fwht_pass<T, CT, BA, BB, MODE, ROUNDS>(P, blockIdx.x);
 }
 
-// Position of row j in the last pass's order: group g = (hi, lo), slot pos.
-__device__ __forceinline__ int64_t last_pass_index(int64_t j, int s0, int B) {
-  const int64_t hi = j >> (s0 + B);
-  const int64_t lo = j & ((int64_t(1) << s0) - 1);
-  const int64_t pos = (j >> s0) & ((int64_t(1) << B) - 1);
-  return (hi << (s0 + B)) | (lo << B) | pos;
+// The row that position k of the last pass's order holds.
+__device__ __forceinline__ int64_t last_pass_row(int64_t k, int s0, int B) {
+  const int64_t hi = k >> (s0 + B);
+  const int64_t lo = (k >> B) & ((int64_t(1) << s0) - 1);
+  const int64_t pos = k & ((int64_t(1) << B) - 1);
+  return (hi << (s0 + B)) | (pos << s0) | lo;
 }
 
-// pi_sgn[j] = pi(j) (or ~pi(j) when D_j = -1), in row order (the first pass reads it
-// contiguously); slotA = sigma^{-1}(j) if < m_K else -1, in the last pass's order
-// The permutation of [0, 2^p) (INV: its inverse) of every index j = j0,
-// j0 + stride, .. < n, handed to emit(j, value).  Cycle walking (an odd p
-// walks twice on average) would hold a wave for its longest walk; here every
-// iteration evaluates the Feistel network once per lane, on the lane's next
-// index as soon as its current one has left the walking range.  The values
-// are those of rng::prp / rng::prp_inv.
-template <bool INV, typename Emit>
-__device__ __forceinline__ void prp_each(int64_t j0, int64_t n, int64_t stride, uint64_t seed,
-                                         uint64_t stream, int p, Emit&& emit) {
-  if (j0 >= n) return;
+// Index maps of one transform:
+//   pi_sgn[j] = pi(j), or ~pi(j) when D_j = -1, in row order (the first pass reads
+//     it contiguously), and with it, where Y is transformed on its own, Y gathered
+//     through P with D applied: yp[j] = D_j Y[pi(j)] (+0 past N), the bits that the
+//     first pass's gather would form;
+//   slotA = sigma^{-1}(j) if < m_K else -1, slotH = sigma_hat^{-1}(j) if < r else -1,
+//     in the last pass's order.
+//
+// A round of the Feistel networks behind pi, sigma and sigma_hat maps h = ceil(p / 2)
+// bits, so a network takes only 4 x 2^h different Philox values; and one Philox block
+// holds the signs of 256 rows.  A block therefore tabulates its network's rounds (16
+// bits each) and its rows' signs in LDS and then looks them up: 1/8 of the Philox work
+// of evaluating it at every row.  Each block serves one of the three networks
+// (blockIdx.y) over 8 x 2^h rows (16 x and 32 x: 16384 rows 6.6 -> 7.3, 8.9 us, 2^22 rows
+// 95 -> 97, 144 us); the slot maps are walked in the order they are stored.
+// Bound by the random reads of Y at 2^22 rows.  Before -> after, all of a transform's
+// maps: 2^22 rows with Y 196 -> 95 us, 64 transforms of 2^14 to 2^18 rows 973 -> 147 us,
+// 2^14 rows 18 -> 6.6 us (three launches -> one).
+// Networks of more than kTableBits bits (over 2^24 rows) evaluate Philox per row: their
+// tables would leave the LDS to one block.
+constexpr int kTableBits = 12;
+constexpr int kIndexThreads = 512;
+constexpr int kSignRows = 256;  // rows whose signs one Philox block holds
+
+inline int index_rows(int p) {
   const int h = (p + 1) >> 1;
-  const uint64_t lim = uint64_t(1) << p;
-  int64_t j = j0;
-  uint64_t x = (uint64_t)j;
+  // (whole Philox blocks of signs)
+  const int64_t rows = h <= kTableBits ? std::max<int64_t>(kSignRows, int64_t(8) << h) : 4096;
+  return (int)std::min<int64_t>(rows, int64_t(1) << p);
+}
+inline int index_sign_words(int p) { return (int)round_up(ceil_div(index_rows(p), 64), 4); }
+inline size_t index_lds_bytes(int p) {
+  const int h = (p + 1) >> 1;
+  return index_sign_words(p) * sizeof(uint64_t) +
+         (h <= kTableBits ? (size_t(4) << h) * sizeof(uint16_t) : 0);
+}
+
+// The value of a permutation of [0, 2^p) at start(k) for every k = k0, k0 + stride,
+// .. < n, handed to emit(k, value): `net` applied until the value is in range.  Cycle
+// walking (an odd p walks twice on average) would hold a wave for its longest walk; here
+// every iteration evaluates the network once per lane, on the lane's next index as soon
+// as its current one has left the walking range.
+template <typename Net, typename Start, typename Emit>
+__device__ __forceinline__ void walk_each(int64_t k0, int64_t n, int64_t stride, uint64_t lim,
+                                          Net&& net, Start&& start, Emit&& emit) {
+  if (k0 >= n) return;
+  int64_t k = k0;
+  uint64_t x = (uint64_t)start(k);
   while (true) {
-    const uint64_t y =
-        INV ? rng::feistel_dec(x, seed, stream, h) : rng::feistel_enc(x, seed, stream, h);
+    const uint64_t y = net(x);
     if (y < lim) {
-      emit(j, y);
-      j += stride;
-      if (j >= n) break;
-      x = (uint64_t)j;
+      emit(k, y);
+      k += stride;
+      if (k >= n) break;
+      x = (uint64_t)start(k);
     } else {
       x = y;
     }
   }
 }
 
-// pi_sgn and slotA of the indices j0, j0 + stride, .. < npad
-__device__ __forceinline__ void srht_index_range(int64_t j0, int64_t stride, int64_t npad, int p,
-                                                 uint64_t seed, int64_t mK, int s0_last, int b_last,
-                                                 int32_t* __restrict__ pi_sgn,
-                                                 int32_t* __restrict__ slotA) {
-  prp_each<false>(j0, npad, stride, seed, rng::kStreamP, p,
-                  [&](int64_t j, uint64_t src) { gptr(pi_sgn)[j] = (int32_t)src; });
-  // the signs D over the same indices (each thread rereads its own writes)
-  for (int64_t j = j0; j < npad; j += stride)
-    if (rng::rademacher(seed, (uint64_t)j) < 0) gptr(pi_sgn)[j] = ~gptr(pi_sgn)[j];
-  prp_each<true>(j0, npad, stride, seed, rng::kStreamS, p, [&](int64_t j, uint64_t t) {
-    gptr(slotA)[last_pass_index(j, s0_last, b_last)] = t < (uint64_t)mK ? (int32_t)t : -1;
-  });
+// walk_each with the network (INV: its inverse) of a stream, from the tables in LDS or
+// evaluated
+template <bool INV, typename Start, typename Emit>
+__device__ __forceinline__ void prp_each(int64_t k0, int64_t n, int64_t stride, uint64_t seed,
+                                         uint64_t stream, int p, uint16_t* tab, Start&& start,
+                                         Emit&& emit) {
+  const int h = (p + 1) >> 1;
+  const uint64_t lim = uint64_t(1) << p;
+  if (h > kTableBits) {
+    walk_each(
+        k0, n, stride, lim,
+        [&](uint64_t x) {
+          return INV ? rng::feistel_dec(x, seed, stream, h) : rng::feistel_enc(x, seed, stream, h);
+        },
+        start, emit);
+    return;
+  }
+  const uint32_t mask = (uint32_t(1) << h) - 1;
+  for (uint32_t i = threadIdx.x; i < (4u << h); i += blockDim.x)
+    tab[i] = (uint16_t)rng::feistel_round(i & mask, (int)(i >> h), seed, stream, mask);
+  __syncthreads();
+  walk_each(
+      k0, n, stride, lim,
+      [&](uint64_t x) {
+        uint32_t L = (uint32_t)(x >> h), R = (uint32_t)x & mask;
+        static_assert(rng::kFeistelRounds == 4, "the tables hold four rounds");
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          if constexpr (INV) {
+            const uint32_t f = tab[((3 - r) << h) | L];
+            const uint32_t l = R ^ f;
+            R = L;
+            L = l;
+          } else {
+            const uint32_t f = tab[(r << h) | R];
+            const uint32_t rr = L ^ f;
+            L = R;
+            R = rr;
+          }
+        }
+        return ((uint64_t)L << h) | R;
+      },
+      start, emit);
 }
 
-__global__ void srht_index_kernel(int64_t npad, int p, uint64_t seed, int64_t mK, int s0_last,
-                                  int b_last, int32_t* __restrict__ pi_sgn,
-                                  int32_t* __restrict__ slotA) {
-  srht_index_range(blockIdx.x * (int64_t)blockDim.x + threadIdx.x, (int64_t)gridDim.x * blockDim.x,
-                   npad, p, seed, mK, s0_last, b_last, pi_sgn, slotA);
-}
-
-// The same maps, and Y gathered through P with D applied, in row order:
-// yp[j] = D_j Y[pi(j)] (+0 past N), the bits the first pass's gather would
-// form; Y's own first pass then reads its rows in order, and the random reads
-// of Y overlap the Feistel arithmetic here.
+// Rows (positions) [first, first + rows) of one of a transform's maps: `part` 0 = pi_sgn
+// (and yp if Y), 1 = slotA, 2 = slotH.  Every thread of the block takes part.
 template <typename T>
-__global__ void srht_index_y_kernel(int64_t npad, int p, uint64_t seed, int64_t mK, int s0_last,
-                                    int b_last, int32_t* __restrict__ pi_sgn,
-                                    int32_t* __restrict__ slotA, const T* __restrict__ Y, int64_t N,
-                                    T* __restrict__ yp) {
-  const int64_t j0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  srht_index_range(j0, stride, npad, p, seed, mK, s0_last, b_last, pi_sgn, slotA);
-  for (int64_t j = j0; j < npad; j += stride) {
-    const int32_t ps = gptr(pi_sgn)[j];
-    const bool neg = ps < 0;
-    const int64_t src = neg ? (int64_t)(~ps) : (int64_t)ps;
-    const T v = src < N ? gptr(Y)[src] : (T)0;
-    gptr(yp)[j] = src < N ? (neg ? -v : v) : (T)0;
+__device__ __forceinline__ void srht_index_part(const SrhtIndexJob& jb, int part, int64_t first,
+                                                int64_t rows, uint64_t* lds, int sign_words,
+                                                const T* Y, int64_t N, T* yp) {
+  uint16_t* tab = reinterpret_cast<uint16_t*>(lds + sign_words);
+  const int64_t n = first + rows;
+  const int64_t k0 = first + threadIdx.x;
+  const int64_t stride = blockDim.x;
+  if (part == 0) {
+    for (int c = threadIdx.x; c < sign_words / 4; c += blockDim.x) {
+      const rng::Words w =
+          rng::philox((uint64_t)(first / kSignRows + c), 0, 0, 0, jb.seed, rng::kStreamD);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) lds[4 * c + i] = w.w[i];
+    }
+    __syncthreads();
+    prp_each<false>(
+        k0, n, stride, jb.seed, rng::kStreamP, jb.p, tab, [](int64_t j) { return j; },
+        [&](int64_t j, uint64_t src) {
+          const bool neg = (lds[(j - first) >> 6] >> (j & 63)) & 1;
+          gptr(jb.pi_sgn)[j] = neg ? ~(int32_t)src : (int32_t)src;
+        });
+    if (!Y) return;
+    // each thread rereads its own writes; eight random reads of Y in flight
+    constexpr int U = 8;
+    for (int64_t j = k0; j < n; j += U * stride) {
+      int32_t ps[U];
+      T v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t ju = j + u * stride;
+        ps[u] = gptr(jb.pi_sgn)[ju < n ? ju : j];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t src = ps[u] < 0 ? ~ps[u] : ps[u];
+        v[u] = gptr(Y)[src < N ? src : 0];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t ju = j + u * stride;
+        const int64_t src = ps[u] < 0 ? ~ps[u] : ps[u];
+        if (ju < n) gptr(yp)[ju] = src < N ? (ps[u] < 0 ? -v[u] : v[u]) : (T)0;
+      }
+    }
+  } else {
+    const bool hat = part == 2;
+    const uint64_t count = (uint64_t)(hat ? jb.r : jb.mK);
+    int32_t* slot = hat ? jb.slotH : jb.slotA;
+    prp_each<true>(
+        k0, n, stride, jb.seed, hat ? rng::kStreamShat : rng::kStreamS, jb.p, tab,
+        [&](int64_t k) { return last_pass_row(k, jb.s0_last, jb.b_last); },
+        [&](int64_t k, uint64_t t) { gptr(slot)[k] = t < count ? (int32_t)t : -1; });
   }
 }
 
-// slotH (pre-filled with -1): the row sigma_hat(t) carries slot t, for t < r
-__global__ void srht_hat_kernel(int64_t r, int p, uint64_t seed, int s0_last, int b_last,
-                                int32_t* __restrict__ slotH) {
-  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < r;
-       t += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t j = (int64_t)rng::prp((uint64_t)t, seed, rng::kStreamShat, p);
-    slotH[last_pass_index(j, s0_last, b_last)] = (int32_t)t;
-  }
+template <typename T>
+__global__ __launch_bounds__(kIndexThreads) void srht_index_kernel(SrhtIndexJob jb, int rows,
+                                                                   int sign_words, const T* Y,
+                                                                   int64_t N, T* yp) {
+  extern __shared__ uint64_t lds[];
+  srht_index_part<T>(jb, blockIdx.y, (int64_t)blockIdx.x * rows, rows, lds, sign_words, Y, N, yp);
+}
+
+// The maps of many transforms: blockIdx.z picks the job (its fields are uniform over the
+// block; blocks past a smaller job's rows return at once).
+__global__ __launch_bounds__(kIndexThreads) void srht_index_batched_kernel(
+    const SrhtIndexJob* __restrict__ jobs) {
+  extern __shared__ uint64_t lds[];
+  const SrhtIndexJob jb = jobs[blockIdx.z];
+  const int64_t first = (int64_t)blockIdx.x * jb.rows;
+  if (first >= jb.npad) return;
+  srht_index_part<float>(jb, blockIdx.y, first, jb.rows, lds, jb.sign_words, nullptr, 0, nullptr);
 }
 
 template <typename T>
@@ -664,51 +764,30 @@ size_t srht_z_bytes(const SrhtArgs& a) {
   return (size_t)(int64_t(1) << a.p) * (size_t)(a.ldz + (a.split_y ? 2 : 0)) * dtype_size(a.t);
 }
 
-namespace {
-
-// Index maps of many transforms: blockIdx.y picks the job (its fields are
-// uniform over the block), blockIdx.x and the threads stride over its rows.
-// Every row index: pi_sgn, slotA (as srht_index_kernel) and slotH = -1.
-__global__ void srht_index_batched_kernel(const SrhtIndexJob* __restrict__ jobs) {
-  const SrhtIndexJob jb = jobs[blockIdx.y];
-  const int64_t j0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  srht_index_range(j0, stride, jb.npad, jb.p, jb.seed, jb.mK, jb.s0_last, jb.b_last, jb.pi_sgn,
-                   jb.slotA);
-  for (int64_t j = j0; j < jb.npad; j += stride) gptr(jb.slotH)[j] = -1;
-}
-
-// every Hessian sample of every job (after the kernel above)
-__global__ void srht_hat_batched_kernel(const SrhtIndexJob* __restrict__ jobs) {
-  const SrhtIndexJob jb = jobs[blockIdx.y];
-  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < jb.r;
-       t += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t j = (int64_t)rng::prp((uint64_t)t, jb.seed, rng::kStreamShat, jb.p);
-    gptr(jb.slotH)[last_pass_index(j, jb.s0_last, jb.b_last)] = (int32_t)t;
-  }
-}
-
-}  // namespace
-
 void srht_last_pass(const SrhtArgs& a, int* s0_last, int* b_last) {
   const std::vector<int> bs = pass_sizes(a.p, a.bmax);
   *b_last = bs.back();
   *s0_last = a.p - bs.back();
 }
 
-void launch_srht_index_batched(const SrhtIndexJob* jobs, int B, int64_t max_npad, int64_t max_r,
+void srht_index_job(SrhtIndexJob& j, int p) {
+  j.p = p;
+  j.npad = int64_t(1) << p;
+  j.rows = index_rows(p);
+  j.sign_words = index_sign_words(p);
+}
+
+void launch_srht_index_batched(const SrhtIndexJob* jobs, const SrhtIndexJob* host_jobs, int B,
                                hipStream_t s) {
-  if (B <= 0) return;
-  const int threads = 256;
-  // about four rows per thread in the largest job; blocks past a smaller
-  // job's rows return at once
   for (int j0 = 0; j0 < B; j0 += 65535) {
     const int nb = std::min(65535, B - j0);
-    const int bx = (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(max_npad, 4 * threads), 4096));
-    srht_index_batched_kernel<<<dim3(bx, nb), threads, 0, s>>>(jobs + j0);
-    SLSE_LAUNCH_CHECK();
-    const int hx = (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(max_r, 4 * threads), 4096));
-    srht_hat_batched_kernel<<<dim3(hx, nb), threads, 0, s>>>(jobs + j0);
+    int64_t bx = 1;
+    size_t lds = 0;
+    for (int j = j0; j < j0 + nb; ++j) {
+      bx = std::max(bx, host_jobs[j].npad / host_jobs[j].rows);
+      lds = std::max(lds, index_lds_bytes(host_jobs[j].p));
+    }
+    srht_index_batched_kernel<<<dim3((unsigned)bx, 3, nb), kIndexThreads, lds, s>>>(jobs + j0);
     SLSE_LAUNCH_CHECK();
   }
 }
@@ -724,34 +803,34 @@ void launch_srht(const SrhtArgs& a, hipStream_t s) {
     return;
   }
   const int64_t npad = int64_t(1) << a.p;
-  const int threads = 256;
-  const int blocks = (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(npad, threads), 16384));
-  const std::vector<int> bs = pass_sizes(a.p, a.bmax);
-  const int b_last = bs.back();
-  const int s0_last = a.p - b_last;
   // with Y on its own, Y is gathered through P together with the maps
   // (SLSE_SRHT_Y_PREGATHER=0: in its first pass instead)
   SrhtArgs b = a;
   b.y_pregathered = a.split_y;
   if (const char* e = std::getenv("SLSE_SRHT_Y_PREGATHER"))
     if (std::atoi(e) == 0) b.y_pregathered = false;
-  if (b.y_pregathered && a.t == SLSE_F32) {
-    srht_index_y_kernel<float><<<blocks, threads, 0, s>>>(
-        npad, a.p, a.seed, a.mK, s0_last, b_last, a.pi_sgn, a.slotA, static_cast<const float*>(a.Y),
-        a.N, static_cast<float*>(a.Z) + npad * (a.ldz + 1));
-  } else if (b.y_pregathered && a.t == SLSE_F64) {
-    srht_index_y_kernel<double><<<blocks, threads, 0, s>>>(
-        npad, a.p, a.seed, a.mK, s0_last, b_last, a.pi_sgn, a.slotA, static_cast<const double*>(a.Y),
-        a.N, static_cast<double*>(a.Z) + npad * (a.ldz + 1));
+  SrhtIndexJob j{};
+  srht_index_job(j, a.p);
+  j.r = a.r;
+  j.mK = a.mK;
+  j.seed = a.seed;
+  srht_last_pass(a, &j.s0_last, &j.b_last);
+  j.pi_sgn = a.pi_sgn;
+  j.slotA = a.slotA;
+  j.slotH = a.slotH;
+  const dim3 grid((unsigned)(npad / j.rows), 3);
+  const size_t lds = index_lds_bytes(a.p);
+  if (b.y_pregathered && a.t == SLSE_F64) {
+    srht_index_kernel<double><<<grid, kIndexThreads, lds, s>>>(
+        j, j.rows, j.sign_words, static_cast<const double*>(a.Y), a.N,
+        static_cast<double*>(a.Z) + npad * (a.ldz + 1));
   } else {
-    b.y_pregathered = false;
-    srht_index_kernel<<<blocks, threads, 0, s>>>(npad, a.p, a.seed, a.mK, s0_last, b_last,
-                                                 a.pi_sgn, a.slotA);
+    const bool g = b.y_pregathered && a.t == SLSE_F32;
+    b.y_pregathered = g;
+    srht_index_kernel<float><<<grid, kIndexThreads, lds, s>>>(
+        j, j.rows, j.sign_words, g ? static_cast<const float*>(a.Y) : nullptr, a.N,
+        g ? static_cast<float*>(a.Z) + npad * (a.ldz + 1) : nullptr);
   }
-  SLSE_LAUNCH_CHECK();
-  launch_fill_i32(a.slotH, -1, npad, s);
-  srht_hat_kernel<<<(int)ceil_div(a.r, threads), threads, 0, s>>>(a.r, a.p, a.seed, s0_last,
-                                                                  b_last, a.slotH);
   SLSE_LAUNCH_CHECK();
   if (a.t == SLSE_F64)
     run_passes<double>(b, s);

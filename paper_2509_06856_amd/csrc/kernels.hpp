@@ -143,8 +143,8 @@ void srht_plan(SrhtArgs& a, int prefer_ct);
 // would hold Y and padding (no-op otherwise; SLSE_SRHT_SPLIT_Y=0 disables).
 void srht_split_y(SrhtArgs& a);
 
-// Index maps of many SRHTs in two launches (rows of every job, then the r
-// Hessian samples of every job).  base/hbase: first global index of the job.
+// Index maps of many SRHTs in one launch.  base/hbase: first global index of the
+// job; rows, sign_words: the share of a block.
 struct SrhtIndexJob {
   int64_t npad;
   int64_t r;
@@ -153,6 +153,8 @@ struct SrhtIndexJob {
   int p;
   int s0_last;
   int b_last;
+  int rows;
+  int sign_words;
   int pad_;
   int64_t base;
   int64_t hbase;
@@ -160,10 +162,12 @@ struct SrhtIndexJob {
   int32_t* slotA;
   int32_t* slotH;
 };
-// b_last / s0_last of the pass split srht_plan chooses for `a` (a.p, a.bmax set)
+
+// p, npad and a block's share of a job
+void srht_index_job(SrhtIndexJob& j, int p);
 void srht_last_pass(const SrhtArgs& a, int* s0_last, int* b_last);
-// index maps of B jobs (max_npad / max_r: the largest npad and r among them)
-void launch_srht_index_batched(const SrhtIndexJob* jobs, int B, int64_t max_npad, int64_t max_r,
+// index maps of B jobs (the same jobs on the device and on the host)
+void launch_srht_index_batched(const SrhtIndexJob* jobs, const SrhtIndexJob* host_jobs, int B,
                                hipStream_t s);
 size_t srht_z_bytes(const SrhtArgs& a);
 void launch_srht(const SrhtArgs& a, hipStream_t s);

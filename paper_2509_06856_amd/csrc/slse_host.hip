@@ -1286,7 +1286,6 @@ struct BatchPlan {
   void* d_srec = nullptr;
   std::vector<char> srht_batched;  // problem b's sketch runs in the shared launches
   int64_t s_rows = 0, s_hat = 0;          // index-map rows and Hessian samples of all jobs
-  int64_t s_max_npad = 0, s_max_r = 0;   // the largest of one job
   int32_t *s_pi = nullptr, *s_sa = nullptr, *s_sh = nullptr;
   // Cholesky route for every problem: one batched factorization
   bool batched_factor = false;
@@ -1534,7 +1533,7 @@ void enqueue_batch(const BatchPlan& bp, const slse_problem* ps, const slse_param
   launch_fill_i32(bp.flags, 0, bp.B, st);
   launch_fill_i32(bp.finfo, 0, 3 * (int64_t)bp.B, st);
   if (!bp.h_sjobs.empty())
-    launch_srht_index_batched(bp.d_sjobs, (int)bp.h_sjobs.size(), bp.s_max_npad, bp.s_max_r, st);
+    launch_srht_index_batched(bp.d_sjobs, bp.h_sjobs.data(), (int)bp.h_sjobs.size(), st);
   if (!bp.srht_launches.empty()) launch_srht_batched(bp.srht_launches, bp.d_srec, bp.t, st);
   for (int b = 0; b < bp.B; ++b)
     if (bp.srht_batched.empty() || !bp.srht_batched[b]) enqueue_batch_sketch(bp, b, ps, qs, st);
@@ -1645,19 +1644,16 @@ std::pair<std::string, bool> plan_batched(slse_ctx* ctx, int B, const slse_probl
     sa.p = sk.p;
     srht_plan(sa, 0);
     SrhtIndexJob j{};
-    j.npad = sk.n_pad;
+    srht_index_job(j, sk.p);
     j.r = sk.r;
     j.mK = sk.m[sk.K - 1];
     j.seed = qs[b].seed;
-    j.p = sk.p;
     srht_last_pass(sa, &j.s0_last, &j.b_last);
     j.base = bp.s_rows;
     j.hbase = bp.s_hat;
     bp.s_off[b] = bp.s_rows;
     bp.s_rows += sk.n_pad;
     bp.s_hat += sk.r;
-    bp.s_max_npad = std::max<int64_t>(bp.s_max_npad, sk.n_pad);
-    bp.s_max_r = std::max<int64_t>(bp.s_max_r, sk.r);
     bp.h_sjobs.push_back(j);
   }
   if (!bp.h_sjobs.empty()) {
