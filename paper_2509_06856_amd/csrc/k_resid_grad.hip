@@ -25,6 +25,7 @@
 #include <type_traits>
 
 #include "kernels.hpp"
+#include "update_step.hpp"
 
 namespace slse {
 namespace {
@@ -106,12 +107,10 @@ constexpr int unroll_for() {
 // Otherwise NCH is the exact chunk count (d > (NCH - 1) lpr VEC) and only the
 // last chunk can reach past the row.
 template <typename T, typename Acc, int VEC, int NCH, bool HAS_Y, bool FULL>
-__global__ __launch_bounds__(kThreads) void resid_grad_kernel(
-    int64_t n, int d, const T* __restrict__ X, int64_t ldx, const T* __restrict__ Y, int64_t incy,
-    const double* __restrict__ beta, int lpr, double* __restrict__ partial, int ldp,
-    const int* __restrict__ done) {
+__device__ __forceinline__ void resid_grad(int64_t n, int d, const T* __restrict__ X, int64_t ldx,
+                                           const T* __restrict__ Y, int64_t incy, const double* beta,
+                                           int lpr, double* __restrict__ partial, int ldp) {
   constexpr int UNROLL = unroll_for<T, VEC, NCH, SLSE_RG_DEPTH>();
-  if (done && *done) return;
   __shared__ double s_red[kWaves][1025];
 
   const int lane = threadIdx.x & 63;
@@ -265,6 +264,41 @@ __global__ __launch_bounds__(kThreads) void resid_grad_kernel(
   }
 }
 
+template <typename T, typename Acc, int VEC, int NCH, bool HAS_Y, bool FULL>
+__global__ __launch_bounds__(kThreads) void resid_grad_kernel(
+    int64_t n, int d, const T* __restrict__ X, int64_t ldx, const T* __restrict__ Y, int64_t incy,
+    const double* __restrict__ beta, int lpr, double* __restrict__ partial, int ldp,
+    const int* __restrict__ done) {
+  if (done && *done) return;
+  resid_grad<T, Acc, VEC, NCH, HAS_Y, FULL>(n, d, X, ldx, Y, incy, beta, lpr, partial, ldp);
+}
+
+// The pass of step t + 1 with the update of step t ahead of it: every block takes the
+// update for itself (its partial rows, M and the iterates come from the caches), and
+// block 0 writes it out, so the step is one launch.  Such a step is a chain of launches
+// and cache latencies, not of bytes: whole float64 solves from their graphs, against a
+// pass, an update and from 65 columns a sum of the rows as launches of their own:
+// 16384 x 32 472 -> 338 us, 16384 x 64 578 -> 384, 16384 x 128 608 -> 573, 2^17 x 40
+// 867 -> 716, 2^20 x 64 3800 -> 3655.
+template <typename T, typename Acc, int VEC, int NCH, bool HAS_Y, bool FULL>
+__global__ __launch_bounds__(kThreads) void step_grad_kernel(
+    UpdateArgs u, int64_t n, int d, const T* __restrict__ X, int64_t ldx, const T* __restrict__ Y,
+    int64_t incy, int lpr, double* __restrict__ partial, int ldp) {
+  static_assert(kThreads == kStepThreads, "the update's split");
+  __shared__ StepLds s_step;
+  if (u.done && u.tol2 > 0.0) {
+    // block 0 may raise it in this launch; a block that sees it has nothing left to do,
+    // and all of it has to see the same
+    __shared__ int s_done;
+    if (threadIdx.x == 0) s_done = *u.done;
+    __syncthreads();
+    if (s_done) return;
+  }
+  if (step_in_block(u, blockIdx.x == 0, s_step)) return;
+  resid_grad<T, Acc, VEC, NCH, HAS_Y, FULL>(n, d, X, ldx, Y, incy, s_step.beta, lpr,
+                                             partial, ldp);
+}
+
 // g = scale * the sum of the partial rows (columns 0..d-1), rn = scale * the
 // sum of their last column.  Sixteen columns per block: 64 row groups sum every
 // 64th row, then each wave its four groups by lane exchange, then the waves
@@ -305,10 +339,23 @@ __global__ __launch_bounds__(kSumThreads) void sum_rows_kernel(
   }
 }
 
+constexpr int kStepChunks = 4;  // chunks per lane that a pass of at most kStepD columns takes
+
 template <typename T, typename Acc, int VEC, int NCH, bool FULL>
 void launch_t(const ResidGradPlan& pl, const ResidGradArgs& a, hipStream_t s) {
   const T* X = static_cast<const T*>(a.X);
   const T* Y = static_cast<const T*>(a.Y);
+  if constexpr (NCH <= kStepChunks) {
+    if (a.step) {
+      if (Y)
+        step_grad_kernel<T, Acc, VEC, NCH, true, FULL><<<pl.blocks, kThreads, 0, s>>>(
+            *a.step, a.n, a.d, X, a.ldx, Y, a.incy, pl.lpr, a.partial, pl.ldp);
+      else
+        step_grad_kernel<T, Acc, VEC, NCH, false, FULL><<<pl.blocks, kThreads, 0, s>>>(
+            *a.step, a.n, a.d, X, a.ldx, Y, a.incy, pl.lpr, a.partial, pl.ldp);
+      return;
+    }
+  }
   if (Y) {
     resid_grad_kernel<T, Acc, VEC, NCH, true, FULL><<<pl.blocks, kThreads, 0, s>>>(
         a.n, a.d, X, a.ldx, Y, a.incy, a.beta, pl.lpr, a.partial, pl.ldp, a.done);
@@ -394,9 +441,15 @@ ResidGradPlan plan_resid_grad(int64_t n, int d, slse_dtype storage, const void* 
   return pl;
 }
 
+bool resid_grad_takes_step(const ResidGradPlan& pl, const UpdateArgs& u) {
+  return step_fits(u.d, u.rows) && pl.blocks <= 512 && pl.nch <= kStepChunks;
+}
+
 void launch_resid_grad(const ResidGradPlan& pl, const ResidGradArgs& a, hipStream_t s) {
   if (pl.blocks > a.capacity_blocks)
     fail(SLSE_EINVAL, "resid_grad: plan exceeds the scratch capacity");
+  if (a.step && (!resid_grad_takes_step(pl, *a.step) || a.step->d != a.d))
+    fail(SLSE_EINVAL, "resid_grad: the update does not fit the pass");
   if (a.storage == SLSE_F64) {
     if (a.accum == SLSE_F64)
       launch_vec<double, double>(pl, a, s);

@@ -2,8 +2,10 @@
 //   beta_{t+1} = beta_t + mu * H_hat^{-1} g_t + eta * (beta_t - beta_{t-1}),
 // g_t = c X^T (Y - X beta_t) being the negative gradient produced by the fused
 // residual-gradient pass (its partial rows, summed here in a fixed order for
-// narrow problems and by their own kernel for wider ones).  H_hat^{-1} is applied as the dense symmetric matrix
-// M = R^{-1} R^{-T} (a GEMV spread over blocks).  The step also reduces
+// narrow problems and by their own kernel for wider ones).  H_hat^{-1} is
+// applied as the dense symmetric matrix M = R^{-1} R^{-T}: by one block up to
+// 128 columns (there the next pass takes it first, and this kernel only the
+// last one), as a GEMV spread over blocks beyond.  The step also reduces
 //   ||M g_t||^2 and ||beta_{t+1}||^2,
 // whose ratio estimates the relative error of beta_t against the fixed point
 // (beta_hat - beta_t = H^{-1} g_t and M ~ H^{-1}); the last block to finish
@@ -11,77 +13,25 @@
 #include <algorithm>
 
 #include "kernels.hpp"
+#include "update_step.hpp"
 
 namespace slse {
 namespace {
 
 constexpr int kThreads = 256;
 
-// Up to this many columns one block takes the whole step: it sums the pass's
-// partial rows itself (no launch in between) and needs no hand-off between
-// blocks for the estimate.  One CU then reads M and the rows, which grow with d^2
-// and d: whole solves replayed from graphs, the sum kernel and about 64 blocks
-// against one block, take 576 and 461 us at 16384 x 32, 738 and 698 us at 65536 x
-// 48, 732 and 717 us (float32) or 780 and 808 us (float64) at 65536 x 64, 766 and
-// 1000 us at 40000 x 100.
-constexpr int kOneBlockD = 48;
-constexpr int kOneThreads = 1024;
-
-// the estimate's last sums: gp = g . Mg, pp = ||Mg||^2, bb = ||beta_{t+1}||^2
-__device__ __forceinline__ void finish_step(const UpdateArgs& a, double gp, double pp, double bb) {
-  const double est = bb > 0.0 ? sqrt(pp / bb) : sqrt(pp);
-  if (a.sur_out) a.sur_out[0] = est;
-  const bool finite = isfinite(gp) && isfinite(pp) && isfinite(bb);
-  if (!finite && a.status) atomicExch(a.status, 1);
-  if (a.done && a.tol2 > 0.0 && (!finite || est * est <= a.tol2)) atomicExch(a.done, 1);
-}
-
-// THREADS = kOneThreads: one block (d <= kOneBlockD); kThreads: rows_per_block
-// rows of M per block, the partial rows already summed (a.rows <= 1)
-template <int THREADS>
-__global__ __launch_bounds__(THREADS) void mihs_update_kernel(UpdateArgs a, int rows_per_block) {
-  constexpr bool ONE = THREADS == kOneThreads;
-  constexpr int WAVES = THREADS / 64;
+// rows_per_block rows of M per block; the partial rows come summed (a.rows <= 1)
+__global__ __launch_bounds__(kThreads) void mihs_update_kernel(UpdateArgs a, int rows_per_block) {
+  constexpr int WAVES = kThreads / 64;
   if (a.done && *a.done) return;
   extern __shared__ double s_g[];
   __shared__ double s_red[3][WAVES];
   __shared__ int s_ticket;
   const int d = a.d;
-  if constexpr (ONE) {
-    // 2^lc columns x THREADS / 2^lc row groups, each summing every such row
-    // (eight loads in flight), then the groups in order
-    __shared__ double s_p[kOneThreads];
-    int lc = 0;
-    while ((1 << lc) < d) ++lc;
-    const int groups = THREADS >> lc;
-    const int c = threadIdx.x & ((1 << lc) - 1), rg = threadIdx.x >> lc;
-    double t = 0.0;
-    if (c < d) {
-      int k = rg;
-      for (; k + 7 * groups < a.rows; k += 8 * groups) {
-        double v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = a.part[(int64_t)(k + u * groups) * a.ldp + c];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) t += v[u];
-      }
-      for (; k < a.rows; k += groups) t += a.part[(int64_t)k * a.ldp + c];
-    }
-    s_p[threadIdx.x] = t;
-    __syncthreads();
-    if ((int)threadIdx.x < d) {
-      double v = 0.0;
-      for (int q = 0; q < groups; ++q) v += s_p[(q << lc) + threadIdx.x];
-      double g = a.scale * v;
-      if (a.w) g += a.w[threadIdx.x * a.incw];
-      s_g[threadIdx.x] = g;
-    }
-  } else {
-    for (int k = threadIdx.x; k < d; k += THREADS) {
-      double g = a.rows ? a.scale * a.part[k] : 0.0;
-      if (a.w) g += a.w[k * a.incw];
-      s_g[k] = g;
-    }
+  for (int k = threadIdx.x; k < d; k += kThreads) {
+    double g = a.rows ? a.scale * a.part[k] : 0.0;
+    if (a.w) g += a.w[k * a.incw];
+    s_g[k] = g;
   }
   __syncthreads();
 
@@ -114,53 +64,49 @@ __global__ __launch_bounds__(THREADS) void mihs_update_kernel(UpdateArgs a, int 
     s_red[2][wave] = bb;
   }
   __syncthreads();
-  if constexpr (ONE) {
-    if (threadIdx.x == 0) {
-      gp = pp = bb = 0.0;
-      for (int w = 0; w < WAVES; ++w) {
-        gp += s_red[0][w];
-        pp += s_red[1][w];
-        bb += s_red[2][w];
-      }
-      finish_step(a, gp, pp, bb);
-    }
-  } else {
-    if (threadIdx.x < 3) {
-      double t = 0.0;
-      for (int w = 0; w < WAVES; ++w) t += s_red[threadIdx.x][w];
-      store_device(a.sur_partial + 3 * blockIdx.x + threadIdx.x, t);
-    }
-    wait_memory();
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      s_ticket = take_ticket(a.sur_counter);
-      if (s_ticket == (int)gridDim.x - 1) acquire_partials();
-    }
-    __syncthreads();
-    if (s_ticket != (int)gridDim.x - 1) return;
-    // the last block: every thread sums a fixed subset of the block partials,
-    // then a fixed tree over the threads (deterministic)
-    __shared__ double s_tail[3][THREADS];
-    double tgp = 0.0, tpp = 0.0, tbb = 0.0;
-    for (int b = threadIdx.x; b < (int)gridDim.x; b += THREADS) {
-      tgp += load_device(a.sur_partial + 3 * b + 0);
-      tpp += load_device(a.sur_partial + 3 * b + 1);
-      tbb += load_device(a.sur_partial + 3 * b + 2);
-    }
-    s_tail[0][threadIdx.x] = tgp;
-    s_tail[1][threadIdx.x] = tpp;
-    s_tail[2][threadIdx.x] = tbb;
-    __syncthreads();
-    for (int h = THREADS / 2; h > 0; h >>= 1) {
-      if ((int)threadIdx.x < h)
-        for (int c = 0; c < 3; ++c) s_tail[c][threadIdx.x] += s_tail[c][threadIdx.x + h];
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-      finish_step(a, s_tail[0][0], s_tail[1][0], s_tail[2][0]);
-      atomicExch(a.sur_counter, 0);
-    }
+  if (threadIdx.x < 3) {
+    double t = 0.0;
+    for (int w = 0; w < WAVES; ++w) t += s_red[threadIdx.x][w];
+    store_device(a.sur_partial + 3 * blockIdx.x + threadIdx.x, t);
   }
+  wait_memory();
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    s_ticket = take_ticket(a.sur_counter);
+    if (s_ticket == (int)gridDim.x - 1) acquire_partials();
+  }
+  __syncthreads();
+  if (s_ticket != (int)gridDim.x - 1) return;
+  // the last block: every thread sums a fixed subset of the block partials,
+  // then a fixed tree over the threads (deterministic)
+  __shared__ double s_tail[3][kThreads];
+  double tgp = 0.0, tpp = 0.0, tbb = 0.0;
+  for (int b = threadIdx.x; b < (int)gridDim.x; b += kThreads) {
+    tgp += load_device(a.sur_partial + 3 * b + 0);
+    tpp += load_device(a.sur_partial + 3 * b + 1);
+    tbb += load_device(a.sur_partial + 3 * b + 2);
+  }
+  s_tail[0][threadIdx.x] = tgp;
+  s_tail[1][threadIdx.x] = tpp;
+  s_tail[2][threadIdx.x] = tbb;
+  __syncthreads();
+  for (int h = kThreads / 2; h > 0; h >>= 1) {
+    if ((int)threadIdx.x < h)
+      for (int c = 0; c < 3; ++c) s_tail[c][threadIdx.x] += s_tail[c][threadIdx.x + h];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) {
+    finish_step(a, s_tail[0][0], s_tail[1][0], s_tail[2][0]);
+    atomicExch(a.sur_counter, 0);
+  }
+}
+
+// The update of a narrow problem on its own: the sums of the pass that takes it first,
+// so that a step gives the same bits either way.
+__global__ __launch_bounds__(kStepThreads) void step_update_kernel(UpdateArgs a) {
+  __shared__ StepLds s;
+  if (a.done && *a.done) return;
+  step_in_block(a, true, s);
 }
 
 // Per-iterate error accounting: rel_out[0] = ||beta - ref|| / ||ref|| (||beta - ref||
@@ -248,19 +194,19 @@ int rows_per_block_for(int d) {
 
 }  // namespace
 
-bool update_sums_rows(int d) { return d <= kOneBlockD; }
+bool update_sums_rows(int d, int rows) { return step_fits(d, rows); }
 
 int update_blocks(int d) { return (int)ceil_div(d, rows_per_block_for(d)); }
 
 void launch_update(const UpdateArgs& a, hipStream_t s) {
   const size_t shm = (size_t)a.d * sizeof(double);
   if (shm > 64 * 1024) fail(SLSE_EUNSUPPORTED, "update: d too large for this library");
-  if (update_sums_rows(a.d)) {
-    mihs_update_kernel<kOneThreads><<<1, kOneThreads, shm, s>>>(a, a.d);
+  if (step_fits(a.d, a.rows)) {
+    step_update_kernel<<<1, kStepThreads, 0, s>>>(a);
   } else {
     if (a.rows > 1) fail(SLSE_EINVAL, "update: the partial rows of a wide problem come summed");
     const int rpb = rows_per_block_for(a.d);
-    mihs_update_kernel<kThreads><<<(int)ceil_div(a.d, rpb), kThreads, shm, s>>>(a, rpb);
+    mihs_update_kernel<<<(int)ceil_div(a.d, rpb), kThreads, shm, s>>>(a, rpb);
   }
   SLSE_LAUNCH_CHECK();
 }

@@ -28,6 +28,8 @@ struct ResidGradPlan {
 ResidGradPlan plan_resid_grad(int64_t n, int d, slse_dtype storage, const void* X, int64_t ldx,
                               int grid_blocks, int capacity, int lpr_hint = 0);
 
+struct UpdateArgs;
+
 struct ResidGradArgs {
   int64_t n = 0;
   int d = 0;
@@ -41,8 +43,13 @@ struct ResidGradArgs {
   double* partial = nullptr;  // [blocks][ldp]
   int capacity_blocks = 0;    // rows allocated in `partial`
   const int* done = nullptr;  // optional early-exit flag
+  // an update that the pass takes first (its beta_next is then the pass's beta; `beta`
+  // and `done` are not read); its partial rows are others than `partial`
+  const UpdateArgs* step = nullptr;
 };
 
+// whether a pass of this shape can take the update u first
+bool resid_grad_takes_step(const ResidGradPlan& pl, const UpdateArgs& u);
 void launch_resid_grad(const ResidGradPlan& pl, const ResidGradArgs& a, hipStream_t s);
 
 // g = scale * sum_r part[r][0..d) and, if given, rnorm2 = scale * sum_r part[r][d].
@@ -85,9 +92,9 @@ struct UpdateArgs {
 };
 
 int update_blocks(int d);
-// whether the update of d columns sums the pass's partial rows itself (wider ones
-// take the sum of launch_sum_rows)
-bool update_sums_rows(int d);
+// whether the update of d columns sums a pass's partial rows itself (else it takes the
+// sum of launch_sum_rows)
+bool update_sums_rows(int d, int rows);
 void launch_update(const UpdateArgs& a, hipStream_t s);
 
 // rel_out[0] = ||beta - ref|| / ||ref|| and delta = beta - ref (either may be null).

@@ -554,7 +554,8 @@ void tune_resid_grad(slse_ctx* ctx, const IterBufs& b, int64_t n, int d, slse_dt
   // the rule's own shape first
   for (int l : {base.lpr, base.lpr / 2, base.lpr * 2})
     for (int g : {2 * ctx->num_cus, ctx->num_cus, 4 * ctx->num_cus}) {
-      if (l < 1 || l > 64 || g > b.max_blocks) continue;
+      // (partial rows that every block of the next pass may sum: no more than the rule's)
+      if (l < 1 || l > 64 || g > b.max_blocks || (update_sums_rows(d, 1) && g > b.grid_blocks)) continue;
       ResidGradPlan pl;
       try {
         pl = plan_resid_grad(n, d, storage, X, ldx, g, b.max_blocks, l);
@@ -638,6 +639,12 @@ struct Stepper {
   };
   ResidGradPlan plan;
   RowsOf plan_rows;
+  // Narrow problems: a step's update is left to the next step's pass, which takes it
+  // first (one launch per step), or to flush().  `one_launch` is set where nothing else
+  // reads the iterate or changes M between steps.
+  bool one_launch = false;
+  bool pending = false;
+  UpdateArgs update;  // the last step's
 
   // errors of the current iterate beta_t (t = this->t)
   void record_errors() {
@@ -674,11 +681,23 @@ struct Stepper {
     record_errors();
   }
   // (beta_{t-1}, beta_t) of the current iterate
-  void save_state(double* out) const {
+  void save_state(double* out) {
+    flush();
     launch_copy_f64(b.beta[prev], out, d, st);
     launch_copy_f64(b.beta[cur], out + d, d, st);
   }
   void reset_momentum() { prev = cur; }
+  void flush() {
+    if (pending) launch_update(update, st);
+    pending = false;
+  }
+  // whether the update may be taken by the next pass: its blocks read w while block 0
+  // writes beta_out
+  bool may_wait(const UpdateArgs& u) const {
+    if (!one_launch || err.on() || !update_sums_rows(d, u.rows)) return false;
+    if (!u.w || !u.beta_out) return true;
+    return u.w + (int64_t)(d - 1) * u.incw < u.beta_out || u.beta_out + d <= u.w;
+  }
 
   // one M-IHS step on rows [0, n) of (X, Y)
   void step(int64_t n, const void* X, int64_t ldx, const void* Y, int64_t incy, slse_dtype storage,
@@ -703,13 +722,24 @@ struct Stepper {
     a.partial = b.partial;
     a.capacity_blocks = b.max_blocks;
     a.done = b.flags;
+    const UpdateArgs before = update;
+    const int half = b.max_blocks / 2;
+    if (pending && resid_grad_takes_step(pl, before) && std::max(pl.blocks, before.rows) <= half) {
+      a.step = &before;
+      // the other half of the partial rows than the pending update reads
+      a.capacity_blocks = half;
+      if (before.part == b.partial) a.partial += (int64_t)a.capacity_blocks * pl.ldp;
+      pending = false;
+    }
+    flush();
     launch_resid_grad(pl, a, st);
     const int next = (cur + 1) % 3 == prev ? (cur + 2) % 3 : (cur + 1) % 3;
-    UpdateArgs u;
-    u.part = b.partial;
+    UpdateArgs& u = update;
+    u = UpdateArgs();
+    u.part = a.partial;
     u.rows = pl.blocks;
-    if (!update_sums_rows(d)) {
-      launch_sum_rows(b.partial, pl.blocks, pl.ldp, d, 1.0, b.g, nullptr, st);
+    if (!update_sums_rows(d, pl.blocks)) {
+      launch_sum_rows(a.partial, pl.blocks, pl.ldp, d, 1.0, b.g, nullptr, st);
       u.part = b.g;
       u.rows = 1;
     }
@@ -733,7 +763,8 @@ struct Stepper {
     u.tol2 = tol > 0 ? tol * tol : 0.0;
     u.done = b.flags;
     u.status = b.flags + 1;
-    launch_update(u, st);
+    pending = true;
+    if (!may_wait(u)) flush();
     prev = cur;
     cur = next;
     ++t;
@@ -858,6 +889,7 @@ void enqueue_solve(const slse_ctx* ctx, const SolvePlan& pl, const slse_problem*
   int t0, t1;
   step_range(q, t0, t1);
   Stepper S{pl.it, d, pl.f.M, 0, 0, 0, st, ctx, error_sink(p, q)};
+  S.one_launch = true;
   S.start(q->beta0, q->trajectory, q->beta_prev, t0, beta_out);
   const size_t es = dtype_size(pl.st_t);
   int g = 0;  // global index of the next step
@@ -881,6 +913,7 @@ void enqueue_solve(const slse_ctx* ctx, const SolvePlan& pl, const slse_problem*
     S.step(p->N, p->X, p->ldx, p->Y, 1, pl.st_t, acc, 1.0, nullptr, q->mu, q->eta, beta_out,
            q->trajectory, pl.sur, q->tol);
   }
+  S.flush();
   if (q->state_out) S.save_state(q->state_out);
   mark(3);
 }
@@ -1184,6 +1217,7 @@ slse_status backward_impl(slse_ctx* ctx, const slse_problem* p, const slse_param
   }
   // lambda_0 = M w: one update step with g = w from a zero gradient and beta = 0
   Stepper S{ib, d, pl.f.M, 0, 0, 0, st, ctx, ErrorSink{}};
+  S.one_launch = true;
   S.start(nullptr, nullptr);
   launch_fill_f64(zero, 0.0, d, st);
   {
@@ -1209,6 +1243,7 @@ slse_status backward_impl(slse_ctx* ctx, const slse_problem* p, const slse_param
     S.step(p->N, p->X, p->ldx, nullptr, 1, p->dtype, SLSE_F64, 1.0, w, q->mu, q->eta, lambda_out,
            nullptr, nullptr, 0.0, incw);
   }
+  S.flush();
   const double* lam = ib.beta[S.cur];
   if (lambda_out && q->s_max == 0) launch_copy_f64(lam, lambda_out, d, st);
   AdjointArgs a;
