@@ -271,7 +271,7 @@ def paper_rows(G, torch, dev, keys):
         XB = torch.from_numpy(prob.X @ prob.beta_true).to(dev) if "ihs" in methods else None
         del prob
         log(f"paper N={N} d={d} kappa={kappa:g}: generated in {time.perf_counter() - t0:.1f}s")
-        # the Gram route (Gauss-Jordan inverse) is scale-invariant for X = G D; the
+        # the Gram route (Cholesky) is scale-invariant for X = G D; the
         # QR route (shifted CholeskyQR3) is used at kappa = 1e8 where d allows it
         factor = "qr" if kappa > 1e6 and d <= 512 else "chol"
         m = G.paper_schedule(N, d)

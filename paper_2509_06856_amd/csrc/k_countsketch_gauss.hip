@@ -4,14 +4,14 @@
 // CountSketch: column j of S_K has the single entry s(j) in row h(j), so
 // S_K [X|Y] adds s(j) [x_j | y_j] into bucket h(j).  Instead of scattering
 // rows with float atomics, the rows are first listed per bucket (integer
-// counts, an exclusive scan, a fill that writes each row's index with its
-// sign folded in), and each output row is then gathered: one wave per bucket
-// of the largest level (m_K buckets, a few rows each) and several waves per
-// bucket of the Hessian sketch (r buckets, about N/r rows each; their partial
-// rows are added in a fixed order).  Smaller levels use the bucket h(j) mod
-// m_i, so level i is level i+1 folded in halves: A_i[k] = sum_{t = k mod m_i}
-// A_{i+1}[t].  The order of the rows inside a bucket list is set by the fill's
-// atomics, so sums agree with any other order to rounding, not bit for bit.
+// counts that give each row its rank, an exclusive scan, each row's index with
+// its sign folded in placed by rank), and each output row is then gathered: a
+// lane group per bucket of the largest level (m_K buckets, a few rows each) and
+// several waves per bucket of the Hessian sketch (r buckets, about N/r rows
+// each; their partial rows are added in a fixed order).  Smaller levels use the
+// bucket h(j) mod m_i, so level i is level i+1 folded in halves: A_i[k] =
+// sum_{t = k mod m_i} A_{i+1}[t].  Lists are put in increasing row order, so a
+// sketch has the same bits on every run.
 //
 // Gaussian: A = G [X|Y] with G_kj iid N(0, 1) drawn on the fly (Philox block
 // (j, k >> 3) -> four Box-Muller pairs), multiplied on the matrix cores with
