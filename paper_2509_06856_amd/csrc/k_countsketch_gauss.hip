@@ -1145,12 +1145,18 @@ __device__ __forceinline__ int acc_row(int lane, int r) {
 // FP32, the type that it is drawn in) and [X|Y] are double-buffered in LDS, the
 // rows of X copied straight into it a dword per lane (any alignment), one
 // barrier per step.  Row strides of an odd number of 16-value groups keep the
-// four k of an operand read in distinct banks.
+// four k of an operand read in distinct banks.  YV: Y's column is formed on the VALU
+// from the operand of G that a lane holds anyway (one multiply-add per four rows), else
+// it is a column of the tiles; it would take a tile of its own wherever d is a multiple
+// of 16.  The two units add up more than they overlap (2^17 x 64 FP64, 1024 rows, with
+// that tile: the matrix cores busy 48% of 612 us, about a third for the draw), so what
+// either does not do is gained: FP64 2^17 x 64 945 -> 852 us, 2^20 x 16 1210 -> 1057,
+// 16384 x 256 1468 -> 1349; FP32 670 -> 600, 1020 -> 940, 773 -> 756.
 // Measured (S of 16 d rows and S_hat of 6 d; 64 x 64 tiles of VALU products,
 // G drawn again per 64 columns, before): FP64 2^17 x 64 2.70 -> 0.99 ms, 65536 x 128
 // 3.63 -> 1.48 ms, 16384 x 32 1.68 -> 0.10 ms; FP32 the same shapes 2.04 -> 0.69,
 // 2.42 -> 0.85, 1.42 -> 0.09 ms.
-template <typename T, int NT, int NW>
+template <typename T, int NT, int NW, bool YV>
 __global__ __launch_bounds__(64 * NW) void gauss_kernel(int64_t N, int d, const T* __restrict__ X,
                                                         int64_t ldx, const T* __restrict__ Y,
                                                         uint64_t seed, uint64_t stream, int64_t m,
@@ -1164,6 +1170,7 @@ __global__ __launch_bounds__(64 * NW) void gauss_kernel(int64_t N, int d, const 
   static_assert(MT / 8 * kGK == 64 * NW, "one Philox block per thread per step");
   __shared__ __attribute__((aligned(16))) float Gs[2][kGK * GS];
   __shared__ __attribute__((aligned(16))) T Ws[2][kGK * WS];
+  __shared__ T Ys[2][YV ? kGK : 1];
   const int t = threadIdx.x;
   const int lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -1171,7 +1178,7 @@ __global__ __launch_bounds__(64 * NW) void gauss_kernel(int64_t N, int d, const 
   const int c0 = blockIdx.y * 16 * NT;          // columns of [X|Y]
   const int nx = min(16 * NT, d - c0);          // columns of X in this block (can be 0)
   const int yc = d - c0;                        // Y's column in the tile
-  const bool has_y = yc < 16 * NT;
+  const bool has_y = YV ? yc <= 16 * NT : yc < 16 * NT;
   const int split = blockIdx.z / sub, q = blockIdx.z % sub;
   const int64_t s_end = min(N, (split + 1) * per);
   const int64_t j_begin = min(split * per + q * sub_per, s_end);
@@ -1179,6 +1186,7 @@ __global__ __launch_bounds__(64 * NW) void gauss_kernel(int64_t N, int d, const 
   const int steps = (int)ceil_div(j_end - j_begin, (int64_t)kGK);
   // columns past [X|Y] stay zero, and so do the rows past the range
   for (int e = t; e < 2 * kGK * WS; e += 64 * NW) Ws[0][e] = (T)0;
+  if (YV && t < 2 * kGK) Ys[0][t] = (T)0;
   __syncthreads();
 
   const int kb = t % (MT / 8), jj = t / (MT / 8);  // this thread's Philox block of a step
@@ -1224,15 +1232,22 @@ __global__ __launch_bounds__(64 * NW) void gauss_kernel(int64_t N, int d, const 
   for (int u = 0; u < NT; ++u)
 #pragma unroll
     for (int r = 0; r < 4; ++r) acc[u][r] = (T)0;
+  T acc_y = 0;  // sketch row lane % 16, the rows k with k % 4 = lane / 16
   const bool mine = k0 + 16 * wave < m;
   auto multiply = [&](int s) {
     if (!mine) return;
     const float* Gb = &Gs[s & 1][16 * wave + (lane & 15)];
     const T* Wb = &Ws[s & 1][lane & 15];
-#pragma unroll 2
+    T yv[YV ? kGK / 4 : 1];
+    if constexpr (YV) {
+#pragma unroll
+      for (int ks = 0; ks < kGK; ks += 4) yv[ks / 4] = Ys[s & 1][ks + (lane >> 4)];
+    }
+#pragma unroll(YV ? kGK / 4 : 2)
     for (int ks = 0; ks < kGK; ks += 4) {
       const int k = ks + (lane >> 4);
       const T a = (T)Gb[k * GS];
+      if constexpr (YV) acc_y = fma(a, yv[ks / 4], acc_y);
 #pragma unroll
       for (int u = 0; u < NT; ++u) acc[u] = mfma16(a, Wb[k * WS + 16 * u], acc[u]);
     }
@@ -1243,7 +1258,7 @@ __global__ __launch_bounds__(64 * NW) void gauss_kernel(int64_t N, int d, const 
   if (steps > 0) {
     copy(0);
     draw(0);
-    if (y_thread) Ws[0][t * WS + yc] = j_begin + t < j_end ? Y[j_begin + t] : (T)0;
+    if (y_thread) (YV ? Ys[0][t] : Ws[0][t * WS + yc]) = j_begin + t < j_end ? Y[j_begin + t] : (T)0;
   }
   for (int s = 0; s < steps; ++s) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this step's rows of X are in LDS
@@ -1258,7 +1273,7 @@ __global__ __launch_bounds__(64 * NW) void gauss_kernel(int64_t N, int d, const 
     if (more && draws_first) draw(s + 1);
     multiply(s);
     if (more && !draws_first) draw(s + 1);
-    if (more && y_thread) Ws[(s + 1) & 1][t * WS + yc] = y;
+    if (more && y_thread) (YV ? Ys[(s + 1) & 1][t] : Ws[(s + 1) & 1][t * WS + yc]) = y;
   }
   if (!mine) return;
 #pragma unroll
@@ -1267,8 +1282,13 @@ __global__ __launch_bounds__(64 * NW) void gauss_kernel(int64_t N, int d, const 
     for (int r = 0; r < 4; ++r) {
       const int64_t k = k0 + 16 * wave + acc_row<T>(lane, r);
       const int col = c0 + 16 * u + (lane & 15);
-      if (k < m && col <= d) part[((int64_t)blockIdx.z * m + k) * ldp + col] = acc[u][r];
+      if (k < m && col < d + !YV) part[((int64_t)blockIdx.z * m + k) * ldp + col] = acc[u][r];
     }
+  if (!YV || !has_y) return;
+  acc_y += wave_xor(acc_y, 16);
+  acc_y += wave_xor(acc_y, 32);
+  const int64_t k = k0 + 16 * wave + lane;
+  if (lane < 16 && k < m) part[((int64_t)blockIdx.z * m + k) * ldp + d] = acc_y;
 }
 
 template <typename T, typename Acc>
@@ -1993,39 +2013,64 @@ void gaussian_mfma(const GaussianArgs& a, hipStream_t s) {
 }
 
 // Column tiles of 16 per block of the FP32 / FP64 kernel: every column in one
-// block while the two [X|Y] tiles fit in LDS beside those of G (17 tiles in
+// block while the two tiles of their rows fit in LDS beside those of G (17 tiles in
 // FP32, 13 in FP64: 160 KB), else the least number of equal blocks; then the next
-// width that is built.  Products of tiles past [X|Y] are wasted, so the widths lie
-// close together.
-constexpr int kGaussTiles[] = {1, 2, 3, 4, 5, 7, 9, 11, 13, 17};
-int gauss_tiles(int d, slse_dtype t) {
-  const int nt = (int)ceil_div(d + 1, 16);
-  const int most = t == SLSE_F64 ? 13 : 17;
-  const int want = (int)ceil_div(nt, ceil_div(nt, most));
-  for (int w : kGaussTiles)
-    if (w >= want) return w;
-  return most;
+// width that is built.  Products of tiles past the columns are wasted, so the widths
+// lie close together.
+constexpr int kGaussTiles[] = {1, 2, 3, 4, 5, 6, 7, 8, 9, 11, 13, 16, 17};
+struct GaussCols {
+  int tiles;   // per block
+  int blocks;
+  bool y_apart;
+};
+GaussCols gauss_cols(int d, slse_dtype t) {
+  auto split = [t](int cols) {
+    const int nt = (int)ceil_div(cols, 16);
+    const int most = t == SLSE_F64 ? 13 : 17;
+    const int want = (int)ceil_div(nt, ceil_div(nt, most));
+    GaussCols g{most, 0, false};
+    for (int w : kGaussTiles)
+      if (w >= want) {
+        g.tiles = std::min(w, most);
+        break;
+      }
+    g.blocks = (int)ceil_div(cols, 16 * g.tiles);
+    return g;
+  };
+  const GaussCols with_y = split(d + 1);
+  GaussCols g = split(d);
+  // Y apart only where that leaves fewer tiles to multiply (elsewhere it costs up to
+  // 2.5%: 30000 x 17 FP64 138 and 142 us, 16384 x 512 5990 and 6075)
+  g.y_apart = g.blocks * g.tiles < with_y.blocks * with_y.tiles;
+  return g.y_apart ? g : with_y;
 }
 // Sketch rows per block: 128, or 64 where that leaves less of the last block
 // empty (few rows: what is drawn past m is skipped, but its waves idle)
 int gauss_waves(int64_t m) { return ceil_div(m, 64) % 2 == 1 && m < 512 ? 4 : 8; }
 
-template <typename T, int NT>
-void gauss_launch(const GaussianArgs& a, T* part, int64_t ldp, hipStream_t s) {
+template <typename T, int NT, bool YV>
+void gauss_launch(const GaussianArgs& a, const GaussCols& g, T* part, int64_t ldp, hipStream_t s) {
   const int nw = gauss_waves(a.m);
   const int64_t per = ceil_div(a.N, (int64_t)a.splits);
   const int64_t sub_per = round_up(ceil_div(per, (int64_t)a.sub), kGK);
-  const dim3 grid((unsigned)ceil_div(a.m, 16 * nw), (unsigned)ceil_div(a.d + 1, 16 * NT),
-                  (unsigned)(a.splits * a.sub));
+  const dim3 grid((unsigned)ceil_div(a.m, 16 * nw), (unsigned)g.blocks, (unsigned)(a.splits * a.sub));
   const T* X = static_cast<const T*>(a.X);
   const T* Y = static_cast<const T*>(a.Y);
   if (nw == 8)
-    gauss_kernel<T, NT, 8><<<grid, 512, 0, s>>>(a.N, a.d, X, a.ldx, Y, a.seed, a.stream_id, a.m,
-                                               a.splits, a.sub, per, sub_per, part, ldp);
+    gauss_kernel<T, NT, 8, YV><<<grid, 512, 0, s>>>(a.N, a.d, X, a.ldx, Y, a.seed, a.stream_id, a.m,
+                                                   a.splits, a.sub, per, sub_per, part, ldp);
   else
-    gauss_kernel<T, NT, 4><<<grid, 256, 0, s>>>(a.N, a.d, X, a.ldx, Y, a.seed, a.stream_id, a.m,
-                                               a.splits, a.sub, per, sub_per, part, ldp);
+    gauss_kernel<T, NT, 4, YV><<<grid, 256, 0, s>>>(a.N, a.d, X, a.ldx, Y, a.seed, a.stream_id, a.m,
+                                                   a.splits, a.sub, per, sub_per, part, ldp);
   SLSE_LAUNCH_CHECK();
+}
+
+template <typename T, int NT>
+void gauss_launch_y(const GaussianArgs& a, const GaussCols& g, T* part, int64_t ldp, hipStream_t s) {
+  if (g.y_apart)
+    gauss_launch<T, NT, true>(a, g, part, ldp, s);
+  else
+    gauss_launch<T, NT, false>(a, g, part, ldp, s);
 }
 
 template <typename T>
@@ -2033,18 +2078,29 @@ void gaussian_t(const GaussianArgs& a, hipStream_t s) {
   const int cols = a.d + 1;
   const int64_t ldp = round_up(cols, 4);
   T* part = sizeof(T) == 8 ? reinterpret_cast<T*>(a.partial64) : reinterpret_cast<T*>(a.partial);
-  switch (gauss_tiles(a.d, a.t)) {
-    case 1: gauss_launch<T, 1>(a, part, ldp, s); break;
-    case 2: gauss_launch<T, 2>(a, part, ldp, s); break;
-    case 3: gauss_launch<T, 3>(a, part, ldp, s); break;
-    case 4: gauss_launch<T, 4>(a, part, ldp, s); break;
-    case 5: gauss_launch<T, 5>(a, part, ldp, s); break;
-    case 7: gauss_launch<T, 7>(a, part, ldp, s); break;
-    case 9: gauss_launch<T, 9>(a, part, ldp, s); break;
-    case 11: gauss_launch<T, 11>(a, part, ldp, s); break;
-    case 13: gauss_launch<T, 13>(a, part, ldp, s); break;
+  const GaussCols g = gauss_cols(a.d, a.t);
+  switch (g.tiles) {
+#define SLSE_TILES(W) \
+  case W: gauss_launch_y<T, W>(a, g, part, ldp, s); break;
+    SLSE_TILES(1)
+    SLSE_TILES(2)
+    SLSE_TILES(3)
+    SLSE_TILES(4)
+    SLSE_TILES(5)
+    SLSE_TILES(6)
+    SLSE_TILES(7)
+    SLSE_TILES(8)
+    SLSE_TILES(9)
+    SLSE_TILES(11)
+    SLSE_TILES(13)
+#undef SLSE_TILES
     default:
-      if constexpr (sizeof(T) == 4) gauss_launch<T, 17>(a, part, ldp, s);
+      if constexpr (sizeof(T) == 4) {
+        if (g.tiles == 16)
+          gauss_launch_y<T, 16>(a, g, part, ldp, s);
+        else
+          gauss_launch_y<T, 17>(a, g, part, ldp, s);
+      }
   }
   gauss_reduce_kernel<T, T><<<grid1(a.m * cols), 256, 0, s>>>(part, a.splits * a.sub, a.m, cols, ldp,
                                                                static_cast<T*>(a.A), a.lda);
@@ -2076,7 +2132,7 @@ void gaussian_plan(GaussianArgs& a) {
   if (!a.bf16) {
     // the FP32 / FP64 kernel's blocks are large: sub-ranges of a split (at least
     // 256 rows) until there are two per CU
-    const int64_t blocks = ceil_div(a.d + 1, 16 * gauss_tiles(a.d, a.t)) *
+    const int64_t blocks = (int64_t)gauss_cols(a.d, a.t).blocks *
                            ceil_div(a.m, 16 * gauss_waves(a.m)) * splits;
     const int64_t rows = ceil_div(std::max<int64_t>(a.N, 1), splits);
     a.sub = (int)std::max<int64_t>(

@@ -62,3 +62,22 @@ def test_gaussian_of_rows_at_any_element(G, dtype, u):
         tol += 2.0 ** -16 * (1 + np.abs(g64)) @ np.abs(W[:, keep])
         assert np.all(np.abs(out[:, keep] - ref) <= tol)
         assert np.array_equal(out[:, 7], np.sign(g64[:, N - 1]) * np.inf)
+
+
+@pytest.mark.parametrize("form", ["f32", "f64"])
+@pytest.mark.parametrize("d", [16, 17, 32, 48, 64, 80, 81, 96, 97, 112, 128, 129, 176, 208, 209, 256, 257])
+def test_y_beside_the_column_tiles(G, form, d):
+    # Y's column is formed beside the tiles of X: widths that fill their tiles, and one more
+    _case(G, 530, d, [72], d + 9, form, check_drop=False)
+
+
+def test_an_infinite_y_stays_in_its_column(G):
+    N, d, m, r = 700, 32, 40, 48
+    g = np.random.default_rng(4)
+    X, Y = dev(g.standard_normal((N, d))), dev(g.standard_normal(N))
+    A0, H0, _ = G.sketch_apply(X, Y, "gaussian", 12, [m], r)
+    Y[N - 1] = float("inf")
+    A, H, _ = G.sketch_apply(X, Y, "gaussian", 12, [m], r)
+    for new, old in ((A, A0), (H, H0)):
+        assert torch.equal(new[:, :d], old[:, :d])
+        assert not torch.isfinite(new[:, d]).any()
