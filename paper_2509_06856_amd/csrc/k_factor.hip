@@ -274,18 +274,29 @@ __device__ __forceinline__ void tile_product(const double* X, int sxm, int sxk, 
 // is the chain from one pivot to the next, so the steps eliminate without
 // square roots (row b loses A[a][b] / p_a times row a: a broadcast, a reciprocal and
 // two products per step) and the rows are scaled by p_a^{-1/2} afterwards.
-// Returns c0 + a + 1 of the first bad pivot a, else 0.
+// Returns c0 + a + 1 of the first bad pivot a (not positive and finite), else 0.  After
+// a bad pivot the columns hold nothing useful, unless SUBST: it then counts as 1, so that
+// the rows and columns it does not touch are factored as without it.  Guarding every
+// pivot would lengthen the chain, so the caller runs the SUBST form on the columns
+// again where the plain one met a bad pivot.
+template <bool SUBST>
 __device__ __forceinline__ int eliminate16(double (&col)[16], int c0) {
   const int lane = threadIdx.x & 63;
+  auto good = [](double p) { return p > 0.0 && p <= 1.7976931348623157e308; };
 #pragma unroll
   for (int a = 0; a < 16; ++a) {
     const double p = readlane_f64(col[a], a);
     double m[16];
 #pragma unroll
     for (int b = a + 1; b < 16; ++b) m[b] = readlane_f64(col[a], b);
-    double inv = __builtin_amdgcn_rcp(p);  // 24 bits; one step of order three
-    const double e = fma(-p, inv, 1.0);
-    inv = fma(inv, fma(e, e, e), inv);
+    double inv;
+    if constexpr (SUBST) {
+      inv = good(p) ? 1.0 / p : 1.0;
+    } else {
+      inv = __builtin_amdgcn_rcp(p);  // 24 bits; one step of order three
+      const double e = fma(-p, inv, 1.0);
+      inv = fma(inv, fma(e, e, e), inv);
+    }
     const double w = col[a] * inv;
 #pragma unroll
     for (int b = a + 1; b < 16; ++b) col[b] = fma(-m[b], w, col[b]);
@@ -294,13 +305,16 @@ __device__ __forceinline__ int eliminate16(double (&col)[16], int c0) {
   double p = 1.0;
 #pragma unroll
   for (int a = 0; a < 16; ++a) p = lane == a ? col[a] : p;
-  const uint64_t ok = __ballot(p > 0.0 && p <= 1.7976931348623157e308) | ~uint64_t(0xffff);
+  const uint64_t ok = __ballot(good(p)) | ~uint64_t(0xffff);
+  const int bad = ok == ~uint64_t(0) ? 0 : c0 + __builtin_ctzll(~ok) + 1;
+  if (!SUBST && bad) return bad;
+  if (SUBST) p = good(p) ? p : 1.0;
   const double y = rsqrt_f64(p);
   const double h = p * y;
   const double root = fma(0.5 * y, fma(-h, h, p), h);
 #pragma unroll
   for (int a = 0; a < 16; ++a) col[a] = lane == a ? root : col[a] * readlane_f64(y, a);
-  return ok == ~uint64_t(0) ? 0 : c0 + __builtin_ctzll(~ok) + 1;
+  return bad;
 }
 
 // One wave factors the 32 x 32 pivot tile D (rows of kCBs doubles in LDS): R_KK
@@ -324,16 +338,24 @@ __device__ __forceinline__ int pivot_tile(double* D, double* Rs, int k0) {
                                  : 0u;
   double col[16];
   // the lanes past 32 read a valid column and replace it
+  auto load = [&](const double* from) {
 #pragma unroll
-  for (int a = 0; a < 16; ++a) {
-    const double v = D[a * kCBs + (lane & 31)];
-    const double id = a == one ? 1.0 : 0.0;
-    col[a] = data ? v : id;
-  }
+    for (int a = 0; a < 16; ++a) {
+      const double v = from[a * kCBs];
+      const double id = a == one ? 1.0 : 0.0;
+      col[a] = data ? v : id;
+    }
+  };
+  auto eliminate = [&](const double* from, int c0) {
+    load(from);
+    if (eliminate16<false>(col, c0) == 0) return 0;
+    load(from);
+    return eliminate16<true>(col, c0);
+  };
   f64x4 T;  // A22 in the accumulator layout
 #pragma unroll
   for (int r = 0; r < 4; ++r) T[r] = D[(16 + 4 * r + q) * kCBs + 16 + c];
-  const int bad0 = eliminate16(col, k0);
+  const int bad0 = eliminate(D + (lane & 31), k0);
   // R11 | R12 to Rs, Z11 to the upper left of D, zeros to its upper right
   {
     double* out = data ? Rs + lane : D + (lane - 32);
@@ -356,13 +378,7 @@ __device__ __forceinline__ int pivot_tile(double* D, double* Rs, int k0) {
     D[(16 + 4 * r + q) * kCBs + 16 + c] = T[r];
   }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-#pragma unroll
-  for (int a = 0; a < 16; ++a) {
-    const double v = D[(16 + a) * kCBs + (q == 0 ? 16 + c : c)];
-    const double id = a == one ? 1.0 : 0.0;
-    col[a] = data ? v : id;
-  }
-  const int bad1 = eliminate16(col, k0 + 16);
+  const int bad1 = eliminate(D + 16 * kCBs + (q == 0 ? 16 + c : c), k0 + 16);
   // R22 to Rs (zeros left of it), Z21 | Z22 to the lower half of D
   {
     double* out = q == 0 ? Rs + 16 + c : q == 1 ? D + c : q == 2 ? D + 16 + c : Rs + c;
