@@ -7,6 +7,7 @@
 //  gemm        Q = alpha A Z^T (a CholeskyQR pass) and small d x d products
 // and M = (R^T R)^{-1} = Z^T Z, once more the Gram kernel.
 #include <algorithm>
+#include <cmath>
 
 #include "kernels.hpp"
 
@@ -43,14 +44,14 @@ struct GemmLds {
   double b[kKS][32 * MT + 16];
 };
 
-// acc += op(A)[i0 .., k] op(B)[k, j0 ..] over k in [kb0, kend).
+// acc += op(pre A)[i0 .., k] op(pre B)[k, j0 ..] over k in [kb0, kend).
 // TRA: A is stored k-major (A[k][i]), else i-major; TRB: B is stored j-major
 // (B[j][k]), else k-major.
 template <int MT, bool TRA, bool TRB, typename AP, typename BP>
 __device__ __forceinline__ void mfma_tile(GemmLds<MT>& lds, AP __restrict__ A, int64_t lda,
                                           BP __restrict__ B, int64_t ldb, int64_t M, int64_t N,
                                           int64_t i0, int64_t j0, int64_t kb0, int64_t kend,
-                                          f64x4 (&acc)[MT][MT]) {
+                                          double pre, f64x4 (&acc)[MT][MT]) {
   constexpr int S = 32 * MT;
   constexpr int kL = kKS * S / 256;  // entries of A and of B per thread per step
   const int t = threadIdx.x;
@@ -79,6 +80,13 @@ __device__ __forceinline__ void mfma_tile(GemmLds<MT>& lds, AP __restrict__ A, i
   };
   if (kb0 < kend) fetch(kb0);
   for (int64_t k0 = kb0; k0 < kend; k0 += kKS) {
+    if (pre != 1.0) {
+#pragma unroll
+      for (int u = 0; u < kL; ++u) {
+        va[u] *= pre;
+        vb[u] *= pre;
+      }
+    }
 #pragma unroll
     for (int u = 0; u < kL; ++u) {
       const int e = t + 256 * u;
@@ -138,10 +146,10 @@ __device__ __forceinline__ void upper_tile(int t, int& ti, int& tj) {
   ti = t - tj * (tj + 1) / 2;
 }
 
-// One upper tile of G = alpha A^T A over the rows [kb0, kend): written to both
-// triangles of G, or raw to split slot `zpart` of `part` when there are several.
+// One upper tile of G = alpha (pre A)^T (pre A) over the rows [kb0, kend): written to both
+// triangles of G, or without alpha to split slot `zpart` of `part` when there are several.
 template <int MT, typename AP, typename GP, typename PP>
-__device__ __forceinline__ void gram_tile(int d, double alpha, AP __restrict__ A, int64_t lda,
+__device__ __forceinline__ void gram_tile(int d, double pre, double alpha, AP __restrict__ A, int64_t lda,
                                           GP __restrict__ G, int64_t ldg, PP __restrict__ part,
                                           int zpart, int tile, int64_t kb0, int64_t kend) {
   __shared__ GemmLds<MT> lds;
@@ -150,7 +158,7 @@ __device__ __forceinline__ void gram_tile(int d, double alpha, AP __restrict__ A
   const int i0 = ti * 32 * MT, j0 = tj * 32 * MT;
   f64x4 acc[MT][MT];
   clear_acc(acc);
-  mfma_tile<MT, true, false>(lds, A, lda, A, lda, d, d, i0, j0, kb0, kend, acc);
+  mfma_tile<MT, true, false>(lds, A, lda, A, lda, d, d, i0, j0, kb0, kend, pre, acc);
   for_acc(acc, [&](int r, int c, double v) {
     const int i = i0 + r, j = j0 + c;
     if (i >= d || j >= d) return;
@@ -164,12 +172,12 @@ __device__ __forceinline__ void gram_tile(int d, double alpha, AP __restrict__ A
 }
 
 template <int MT, typename T>
-__global__ __launch_bounds__(256) void gram_kernel(int d, int64_t rows, double alpha,
-                                                   const T* __restrict__ A, int64_t lda,
-                                                   double* __restrict__ G, int64_t ldg,
+__global__ __launch_bounds__(256) void gram_kernel(int d, int64_t rows, double pre,
+                                                   double alpha, const T* __restrict__ A,
+                                                   int64_t lda, double* __restrict__ G, int64_t ldg,
                                                    double* __restrict__ part, int64_t kper) {
   const int64_t kb0 = (int64_t)blockIdx.y * kper;
-  gram_tile<MT>(d, alpha, A, lda, G, ldg, part, (int)blockIdx.y, (int)blockIdx.x, kb0,
+  gram_tile<MT>(d, pre, alpha, A, lda, G, ldg, part, (int)blockIdx.y, (int)blockIdx.x, kb0,
                 min(rows, kb0 + kper));
 }
 
@@ -215,7 +223,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(int64_t M, int64_t N, int64_t
   const int64_t ldc = p.ldc[z];
   f64x4 acc[MT][MT];
   clear_acc(acc);
-  mfma_tile<MT, false, TRB>(lds, p.A[z], lda, p.B[z], ldb, M, N, i0, j0, 0, K, acc);
+  mfma_tile<MT, false, TRB>(lds, p.A[z], lda, p.B[z], ldb, M, N, i0, j0, 0, K, 1.0, acc);
   for_acc(acc, [&](int r, int c, double v) {
     if (i0 + r < M && j0 + c < N) C[(i0 + r) * ldc + j0 + c] = alpha * v;
   });
@@ -485,7 +493,7 @@ __global__ __launch_bounds__(256) void chol_step_kernel(int d, int k, double* __
 // ---------------------------------------------------------------------------
 // The same for the jobs of a batch.
 // ---------------------------------------------------------------------------
-// G = scale^2 A^T A of every job (blockIdx.z = job x splits + split): with splits > 1
+// G = scale (pre A)^T (pre A) of every job (blockIdx.z = job x splits + split): with splits > 1
 // each split sums its share of the rows into the job's partial slot
 template <typename T>
 __global__ __launch_bounds__(256) void gram_batched_kernel(const FactorJob* __restrict__ jobs,
@@ -496,7 +504,7 @@ __global__ __launch_bounds__(256) void gram_batched_kernel(const FactorJob* __re
   if ((int)blockIdx.x >= nt * (nt + 1) / 2) return;
   const int64_t kper = round_up(ceil_div(jb.rows, (int64_t)splits), kKS);
   const int64_t kb0 = sp * kper;
-  gram_tile<1>(jb.d, jb.scale, gptr(static_cast<const T*>(jb.A)), jb.lda, gptr(jb.G), jb.d,
+  gram_tile<1>(jb.d, jb.pre, jb.scale, gptr(static_cast<const T*>(jb.A)), jb.lda, gptr(jb.G), jb.d,
                splits > 1 ? gptr(jb.part) : nullptr, sp, (int)blockIdx.x, kb0,
                min(jb.rows, kb0 + kper));
 }
@@ -520,7 +528,7 @@ __global__ __launch_bounds__(256) void inverse_batched_kernel(const FactorJob* _
   const FactorJob jb = jobs[blockIdx.z];
   const int nt = (int)ceil_div(jb.d, 32);
   if ((int)blockIdx.x >= nt * (nt + 1) / 2) return;
-  gram_tile<1>(jb.d, 1.0, gptr((const double*)jb.Z), jb.d, gptr(jb.M), jb.d,
+  gram_tile<1>(jb.d, 1.0, 1.0, gptr((const double*)jb.Z), jb.d, gptr(jb.M), jb.d,
                (SLSE_GLOBAL double*)nullptr, 0, (int)blockIdx.x, 0, jb.d);
 }
 
@@ -564,6 +572,17 @@ GramShape gram_shape(int64_t rows, int64_t d) {
   return g;
 }
 
+void gram_scale(double scale, slse_dtype at, double* pre, double* rest) {
+  *pre = 1.0;
+  *rest = scale;
+  if (at == SLSE_F32 || !(scale > 0.0) || !std::isfinite(scale)) return;
+  int e;
+  const double f = std::frexp(scale, &e);  // scale = f 2^e, f in [1/2, 1)
+  const int k = (e - 1) >> 1;              // scale / 4^k in [1, 4)
+  *pre = std::ldexp(1.0, k);
+  *rest = std::ldexp(f, e - 2 * k);
+}
+
 size_t gram_scratch_doubles(int64_t rows, int64_t d) {
   const GramShape g = gram_shape(rows, d);
   return g.splits > 1 ? (size_t)g.splits * d * d : 0;
@@ -578,12 +597,14 @@ void launch_gram(int64_t rows, int d, double alpha, const void* A, int64_t lda, 
     g.kper = rows;
   }
   double* part = g.splits > 1 ? scratch : nullptr;
+  double pre;
+  gram_scale(alpha, at, &pre, &alpha);
   const dim3 grid((unsigned)g.tiles, (unsigned)g.splits);
   auto go = [&](auto* a) {
     if (g.wide)
-      gram_kernel<2><<<grid, 256, 0, s>>>(d, rows, alpha, a, lda, G, ldg, part, g.kper);
+      gram_kernel<2><<<grid, 256, 0, s>>>(d, rows, pre, alpha, a, lda, G, ldg, part, g.kper);
     else
-      gram_kernel<1><<<grid, 256, 0, s>>>(d, rows, alpha, a, lda, G, ldg, part, g.kper);
+      gram_kernel<1><<<grid, 256, 0, s>>>(d, rows, pre, alpha, a, lda, G, ldg, part, g.kper);
   };
   if (at == SLSE_F32)
     go(static_cast<const float*>(A));

@@ -252,7 +252,12 @@ void launch_gauss_generate(uint64_t seed, uint64_t stream_id, int64_t m, int64_t
 // G = alpha A^T A (both triangles, ld ldg) for A rows x d in F32 or F64, summed in
 // FP64.  Long A are split over rows into `scratch` (gram_scratch_doubles
 // entries) and summed in split order.
+// (FP64: A's entries are first scaled by a power of 2 near sqrt(alpha), so that only
+// squares that alpha A^T A itself cannot hold leave the range; exact otherwise)
 size_t gram_scratch_doubles(int64_t rows, int64_t d);
+// scale = pre^2 rest, pre a power of 2 and rest in [1, 4) (FP32 data, whose squares FP64
+// holds: pre = 1)
+void gram_scale(double scale, slse_dtype at, double* pre, double* rest);
 void launch_gram(int64_t rows, int d, double alpha, const void* A, int64_t lda, slse_dtype at,
                  double* G, int64_t ldg, double* scratch, size_t scratch_doubles, hipStream_t s);
 // Q = alpha A Z^T (rows x d, ld d): A R^{-1} for Z = R^{-T}
@@ -271,7 +276,7 @@ void launch_cholesky(int d, double* G, double* R, int64_t ldr, double* Z, int* i
 // G += coef * trace(G) * I (d x d, ld = d).
 void launch_shift_diag(int d, double* G, double coef, hipStream_t s);
 
-// One Cholesky-route factorization of a batch: G = scale A^T A, Z = R^{-T} of its
+// One Cholesky-route factorization of a batch: G = scale (pre A)^T (pre A), Z = R^{-T} of its
 // Cholesky factor R, M = Z^T Z = G^{-1} (info[0]: first bad pivot + 1).  Every
 // buffer is the job's own, row-major with leading dimension d (A: lda); G is
 // destroyed and may be M.
@@ -280,7 +285,7 @@ struct FactorJob {
   int64_t lda = 0;
   int64_t rows = 0;
   int d = 0;
-  double scale = 1.0;
+  double pre = 1.0, scale = 1.0;
   double* G = nullptr;
   double* Z = nullptr;
   double* M = nullptr;

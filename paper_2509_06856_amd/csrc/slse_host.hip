@@ -1773,7 +1773,7 @@ std::pair<std::string, bool> plan_batched(slse_ctx* ctx, int B, const slse_probl
       j.lda = bp.lda[b];
       j.rows = bp.sk[b].r;
       j.d = (int)d;
-      j.scale = bp.sk[b].hat_scale;
+      gram_scale(bp.sk[b].hat_scale, bp.t, &j.pre, &j.scale);
       j.M = bp.Mpool + bp.m_off[b];
       j.G = j.M;
       j.Z = zp + so;
