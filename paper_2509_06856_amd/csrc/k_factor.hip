@@ -282,29 +282,20 @@ __device__ __forceinline__ void tile_product(const double* X, int sxm, int sxk, 
 // is the chain from one pivot to the next, so the steps eliminate without
 // square roots (row b loses A[a][b] / p_a times row a: a broadcast, a reciprocal and
 // two products per step) and the rows are scaled by p_a^{-1/2} afterwards.
-// Returns c0 + a + 1 of the first bad pivot a (not positive and finite), else 0.  After
-// a bad pivot the columns hold nothing useful, unless SUBST: it then counts as 1, so that
-// the rows and columns it does not touch are factored as without it.  Guarding every
-// pivot would lengthen the chain, so the caller runs the SUBST form on the columns
-// again where the plain one met a bad pivot.
-template <bool SUBST>
-__device__ __forceinline__ int eliminate16(double (&col)[16], int c0) {
+// Takes pivots whose reciprocal and its products stay in the normal range and returns
+// whether all were such: guarding every pivot would lengthen the chain, so where it
+// returns false, the columns of no use, the caller runs eliminate16_any on them.
+__device__ __forceinline__ bool eliminate16(double (&col)[16]) {
   const int lane = threadIdx.x & 63;
-  auto good = [](double p) { return p > 0.0 && p <= 1.7976931348623157e308; };
 #pragma unroll
   for (int a = 0; a < 16; ++a) {
     const double p = readlane_f64(col[a], a);
     double m[16];
 #pragma unroll
     for (int b = a + 1; b < 16; ++b) m[b] = readlane_f64(col[a], b);
-    double inv;
-    if constexpr (SUBST) {
-      inv = good(p) ? 1.0 / p : 1.0;
-    } else {
-      inv = __builtin_amdgcn_rcp(p);  // 24 bits; one step of order three
-      const double e = fma(-p, inv, 1.0);
-      inv = fma(inv, fma(e, e, e), inv);
-    }
+    double inv = __builtin_amdgcn_rcp(p);  // 24 bits; one step of order three
+    const double e = fma(-p, inv, 1.0);
+    inv = fma(inv, fma(e, e, e), inv);
     const double w = col[a] * inv;
 #pragma unroll
     for (int b = a + 1; b < 16; ++b) col[b] = fma(-m[b], w, col[b]);
@@ -313,15 +304,46 @@ __device__ __forceinline__ int eliminate16(double (&col)[16], int c0) {
   double p = 1.0;
 #pragma unroll
   for (int a = 0; a < 16; ++a) p = lane == a ? col[a] : p;
-  const uint64_t ok = __ballot(good(p)) | ~uint64_t(0xffff);
-  const int bad = ok == ~uint64_t(0) ? 0 : c0 + __builtin_ctzll(~ok) + 1;
-  if (!SUBST && bad) return bad;
-  if (SUBST) p = good(p) ? p : 1.0;
+  if (__ballot(!(p >= 0x1p-1000 && p <= 0x1p1000))) return false;
   const double y = rsqrt_f64(p);
   const double h = p * y;
   const double root = fma(0.5 * y, fma(-h, h, p), h);
 #pragma unroll
   for (int a = 0; a < 16; ++a) col[a] = lane == a ? root : col[a] * readlane_f64(y, a);
+  return true;
+}
+
+// The same for any pivots, on columns in LDS (column l at C[a * kCBs + l], l < 48; one
+// wave): a pivot's reciprocal is its mantissa's and two powers of 2, so that each operand
+// of a product stays near the square root of its own diagonal entry, and a bad pivot (not
+// positive and finite) counts as 1, so that what it does not touch is factored as without
+// it.  Returns c0 + a + 1 of the first bad pivot a, else 0.  Rare, so short code (a second
+// unrolled form in registers cost every step 0.3 us: 132 VGPRs, twice the code).
+__device__ __forceinline__ int eliminate16_any(double* C, int c0) {
+  const int lane = threadIdx.x & 63;
+  double* mine = C + min(lane, 47);  // the lanes past 48 repeat column 47
+  int bad = 0;
+#pragma unroll 1
+  for (int a = 0; a < 16; ++a) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    double p = C[a * kCBs + a];
+    if (!(p > 0.0 && p <= 1.7976931348623157e308)) {
+      if (!bad) bad = c0 + a + 1;
+      p = 1.0;
+    }
+    int x;
+    const double mant = frexp(p, &x);
+    const double w = ldexp(mine[a * kCBs], -(x >> 1)) / mant;
+#pragma unroll 1
+    for (int b = a + 1; b < 16; ++b)
+      mine[b * kCBs] = fma(-ldexp(C[a * kCBs + b], (x >> 1) - x), w, mine[b * kCBs]);
+    // row a is not read by the others any more
+    const double root = sqrt(p);
+    const double r = mine[a * kCBs] * (1.0 / root);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    mine[a * kCBs] = lane == a ? root : r;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   return bad;
 }
 
@@ -345,25 +367,29 @@ __device__ __forceinline__ int pivot_tile(double* D, double* Rs, int k0) {
                         : q == 2 ? 0x10000u - (1u << c)
                                  : 0u;
   double col[16];
-  // the lanes past 32 read a valid column and replace it
-  auto load = [&](const double* from) {
+  // the columns from `from`, eliminated; the lanes past 32 read a valid column and
+  // replace it.  `work`: 16 rows of LDS that hold nothing yet
+  auto eliminate = [&](const double* from, double* work, int c0) {
 #pragma unroll
     for (int a = 0; a < 16; ++a) {
       const double v = from[a * kCBs];
       const double id = a == one ? 1.0 : 0.0;
       col[a] = data ? v : id;
     }
-  };
-  auto eliminate = [&](const double* from, int c0) {
-    load(from);
-    if (eliminate16<false>(col, c0) == 0) return 0;
-    load(from);
-    return eliminate16<true>(col, c0);
+    if (eliminate16(col)) return 0;
+    if (q < 3)
+#pragma unroll 1
+      for (int a = 0; a < 16; ++a)
+        work[a * kCBs + lane] = data ? from[a * kCBs] : a == one ? 1.0 : 0.0;
+    const int bad = eliminate16_any(work, c0);
+#pragma unroll
+    for (int a = 0; a < 16; ++a) col[a] = work[a * kCBs + min(lane, 47)];
+    return bad;
   };
   f64x4 T;  // A22 in the accumulator layout
 #pragma unroll
   for (int r = 0; r < 4; ++r) T[r] = D[(16 + 4 * r + q) * kCBs + 16 + c];
-  const int bad0 = eliminate(D + (lane & 31), k0);
+  const int bad0 = eliminate(D + (lane & 31), Rs, k0);
   // R11 | R12 to Rs, Z11 to the upper left of D, zeros to its upper right
   {
     double* out = data ? Rs + lane : D + (lane - 32);
@@ -386,7 +412,7 @@ __device__ __forceinline__ int pivot_tile(double* D, double* Rs, int k0) {
     D[(16 + 4 * r + q) * kCBs + 16 + c] = T[r];
   }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  const int bad1 = eliminate(D + 16 * kCBs + (q == 0 ? 16 + c : c), k0 + 16);
+  const int bad1 = eliminate(D + 16 * kCBs + (q == 0 ? 16 + c : c), Rs + 16 * kCBs, k0 + 16);
   // R22 to Rs (zeros left of it), Z21 | Z22 to the lower half of D
   {
     double* out = q == 0 ? Rs + 16 + c : q == 1 ? D + c : q == 2 ? D + 16 + c : Rs + c;

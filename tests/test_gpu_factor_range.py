@@ -1,8 +1,10 @@
 """slse_factor on FP64 data far from 1: entries whose squares leave the range while
-those of sqrt(scale) A do not.
+those of sqrt(scale) A do not, and Gram matrices below the normal range.
 
 R against LAPACK's Householder R of sqrt(scale) A with the bounds of the other factor
-tests (c d u kappa^2 for the Cholesky route, c d u kappa for the QR route, c = 200).
+tests (c d u kappa^2 for the Cholesky route, c d u kappa for the QR route, c = 200).  A
+Gram entry below the normal range is rounded by up to 2^-1075 per row of A, which takes
+the place of u in the Cholesky route's bound there.  M is asked for where it is in range.
 """
 import ctypes
 
@@ -58,3 +60,29 @@ def test_scale_brings_the_squares_into_range(G, method, rows, d, size, scale):
     Mref = Rinv @ Rinv.T
     Mu = M * unit * unit
     assert np.linalg.norm(Mu - Mref) <= 200 * d * U64 * kappa ** 2 * np.linalg.norm(Mref)
+
+
+@pytest.mark.parametrize("method", ["chol", "qr"])
+@pytest.mark.parametrize("d", [1, 16, 20, 33, 64])
+@pytest.mark.parametrize("every", [1, 2, 7])
+def test_pivots_below_the_normal_range(G, method, d, every):
+    # every such column 2^-515 times standard normals, the others of size 1
+    rows = 2 * d + 30
+    small = np.arange(d) % every == 0
+    A = np.random.default_rng(d + every).standard_normal((rows, d))
+    A[:, small] *= 2.0 ** -515
+    R, _ = _factor(G, A, 1.0, method, False)
+    if every == 1:
+        Rref = O.qr_r(np.ldexp(A, 515))
+        kappa = np.linalg.cond(Rref)
+        R = np.ldexp(R, 515)
+        # 2^-1075 per row against the Gram's diagonal of rows 2^-1030
+        u = U64 if method == "qr" else 2.0 ** -45
+        tol = 200 * d * u * (kappa if method == "qr" else kappa ** 2)
+        assert np.linalg.norm(R - Rref) <= tol * np.linalg.norm(Rref)
+    elif method == "chol":
+        # a column of size 2^-515 among others: R's rows scale with the columns
+        S = np.where(small, 2.0 ** 515, 1.0)
+        Rref = O.qr_r(A * S)
+        tol = 200 * d * 2.0 ** -45 * np.linalg.cond(Rref) ** 2
+        assert np.linalg.norm(R * S - Rref) <= tol * np.linalg.norm(Rref)
