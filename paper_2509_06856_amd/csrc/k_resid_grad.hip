@@ -147,7 +147,8 @@ __device__ __forceinline__ void resid_grad(int64_t n, int d, const T* __restrict
   const int64_t r1 = min(n, r0 + chunk);
 
   // UNROLL rows per lane group, from `row0` every rs rows.  PART: some of them
-  // may lie past r1; those read row r1 - 1 and count as zeros.
+  // may lie past r1; those read row r1 - 1 and count as zeros (their residuals too:
+  // the dot of zeros with an infinite beta is NaN).
   auto step = [&](int64_t row0, auto part) {
     constexpr bool PART = decltype(part)::value;
     T x[UNROLL][NCH][VEC];
@@ -175,7 +176,6 @@ __device__ __forceinline__ void resid_grad(int64_t n, int d, const T* __restrict
 #pragma unroll
       for (int u = 0; u < UNROLL; ++u) {
         const bool in = row0 + (int64_t)u * rs < r1;
-        y[u] = in ? y[u] : (T)0;
 #pragma unroll
         for (int c = 0; c < NCH; ++c)
 #pragma unroll
@@ -210,7 +210,8 @@ __device__ __forceinline__ void resid_grad(int64_t n, int d, const T* __restrict
     }
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {
-      const Acc r = (Acc)y[u] - dot[u];
+      Acc r = (Acc)y[u] - dot[u];
+      if constexpr (PART) r = row0 + (int64_t)u * rs < r1 ? r : (Acc)0;
 #pragma unroll
       for (int c = 0; c < NCH; ++c)
 #pragma unroll
