@@ -130,9 +130,11 @@ __global__ __launch_bounds__(kThreads) void adjoint_kernel(int64_t n, int d, con
       for (int c = 0; c < NCH; ++c)
 #pragma unroll
         for (int k = 0; k < VEC; ++k) {
-          const double v = c < kSure || at[c] + k >= col[c] ? (double)x[u][c][k] : 0.0;
-          s1 = fma(v, b[c][k], s1);
-          s2 = fma(v, lam[c][k], s2);
+          // (a sum kept, not a zero added: 0 times an infinite coefficient is NaN)
+          const bool own = c < kSure || at[c] + k >= col[c];
+          const double v = (double)x[u][c][k];
+          s1 = own ? fma(v, b[c][k], s1) : s1;
+          s2 = own ? fma(v, lam[c][k], s2) : s2;
         }
       d1[u] = s1;
       d2[u] = s2;

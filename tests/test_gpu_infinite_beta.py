@@ -1,13 +1,16 @@
 """An infinite coefficient gives infinite gradients, not NaN: rows past a block's share
-add nothing, not 0 * inf.
+and columns past a lane's add nothing, not 0 * inf.
 
 X > 0 and beta > 0 with one entry +inf: every residual is -inf, so every entry of
-X^T (Y - X beta) is -inf and the residual norm +inf.
+X^T (Y - X beta) is -inf and the residual norm +inf; in the adjoint, dY does not
+depend on beta and dX's columns of finite coefficients are r lambda_k = -inf lambda_k.
 """
 import pytest
 import torch
 
 pytestmark = pytest.mark.gpu
+
+U64 = 2.0 ** -53
 
 
 @pytest.fixture(scope="module")
@@ -37,3 +40,21 @@ def test_gradient(G, dtype, d, n):
         for call in (G.fused_resid_grad, G.fused_resid_grad_noalloc):
             g, rn = call(X, Y, beta)
             assert torch.all(g == -float("inf")) and rn.item() == float("inf")
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("d", [2, 5, 16, 33, 64, 100, 101, 130, 330, 512])
+def test_adjoint(G, dtype, d):
+    n = 2531
+    for col in (0, d - 2, d - 1):
+        X, Y, beta = _data(n, d, dtype, col)
+        w = torch.randn(d, device="cuda", dtype=torch.float64)
+        p = G.Params(kind="srht", seed=2, m=[d + 1], a=[0], r=d + 40, s_max=0,
+                     precision="mixed" if dtype == torch.float32 else "f64")
+        dX, dY, lam = G.backward(X, Y, p, beta, w, grad_dtype=torch.float64)
+        ref = X.double().cpu() @ lam.cpu()
+        tol = (d + 3) * U64 * (X.double().cpu() @ lam.cpu().abs())
+        assert torch.all((dY.cpu() - ref).abs() <= tol)
+        keep = torch.arange(d, device="cuda") != col
+        want = (-float("inf") * lam.sign()).expand(n, d)
+        assert torch.equal(dX[:, keep], want[:, keep])
