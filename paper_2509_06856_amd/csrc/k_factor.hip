@@ -203,8 +203,9 @@ __global__ void gram_reduce_kernel(int d, int S, int splits, double alpha,
   gram_reduce(d, S, splits, alpha, part, G, ldg);
 }
 
-// C = alpha A op(B), one S x S tile per block; blockIdx.z picks one of two products
-// of the same shape.
+// C = alpha A op(B), one S x S tile per block, the column tiles of a row side by side on
+// blockIdx.x (the other dimensions of a grid end at 65536 blocks: 2^21 rows of A);
+// blockIdx.z picks one of two products of the same shape.
 template <typename T>
 struct GemmPair {
   const T* A[2];
@@ -218,7 +219,8 @@ __global__ __launch_bounds__(256) void gemm_kernel(int64_t M, int64_t N, int64_t
                                                    GemmPair<T> p, int64_t lda, int64_t ldb) {
   __shared__ GemmLds<MT> lds;
   const int z = blockIdx.z;
-  const int64_t i0 = (int64_t)blockIdx.y * 32 * MT, j0 = (int64_t)blockIdx.x * 32 * MT;
+  const unsigned nt = (unsigned)ceil_div(N, 32 * MT);
+  const int64_t i0 = (int64_t)(blockIdx.x / nt) * 32 * MT, j0 = (int64_t)(blockIdx.x % nt) * 32 * MT;
   double* __restrict__ C = p.C[z];
   const int64_t ldc = p.ldc[z];
   f64x4 acc[MT][MT];
@@ -647,7 +649,7 @@ void launch_gram(int64_t rows, int d, double alpha, const void* A, int64_t lda, 
 void launch_times_inverse(int64_t rows, int d, double alpha, const void* A, int64_t lda,
                           slse_dtype at, const double* Z, double* Q, hipStream_t s) {
   if (rows <= 0 || d <= 0) return;
-  const dim3 grid((unsigned)ceil_div(d, 32), (unsigned)ceil_div(rows, 32));
+  const dim3 grid((unsigned)(ceil_div(d, 32) * ceil_div(rows, 32)));
   if (at == SLSE_F32) {
     const GemmPair<float> p{{static_cast<const float*>(A), nullptr}, {Z, nullptr}, {Q, nullptr},
                               {d, d}};
@@ -666,7 +668,7 @@ void launch_two_products(int d, const double* A0, const double* B0, double* C0, 
   if (d <= 0) return;
   const GemmPair<double> p{{A0, A1}, {B0, B1}, {C0, C1}, {ldc0, ldc1}};
   const unsigned nt = (unsigned)ceil_div(d, 32);
-  gemm_kernel<1, false><<<dim3(nt, nt, 2), 256, 0, s>>>(d, d, d, 1.0, p, d, d);
+  gemm_kernel<1, false><<<dim3(nt * nt, 1, 2), 256, 0, s>>>(d, d, d, 1.0, p, d, d);
   SLSE_LAUNCH_CHECK();
 }
 
