@@ -903,6 +903,8 @@ void enqueue_solve(const slse_ctx* ctx, const SolvePlan& pl, const slse_problem*
              nullptr, q->mu, q->eta, beta_out, q->trajectory, pl.sur, 0.0);
     }
   }
+  // an update left to the next pass is stage 1's, not stage 2's, where both are timed
+  if (ev && ev[2]) S.flush();
   mark(2);
   // stage 2: full-data steps (eq. (99))
   for (int j = 0; j < q->s_max; ++j, ++g) {
