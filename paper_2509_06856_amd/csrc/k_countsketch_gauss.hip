@@ -107,14 +107,30 @@ int cs_count_waves(int64_t buckets) {
   while (w > 1 && w * buckets * (int64_t)sizeof(int) > 65536) w /= 2;
   return w;
 }
-// totals += the block's counts of n buckets (hist: one row of n per wave)
-__device__ __forceinline__ void add_block_counts(const int* hist, int64_t n, int* __restrict__ tot) {
-  const int nw = blockDim.x >> 6;
-  for (int k = threadIdx.x; k < n; k += blockDim.x) {
-    int c = 0;
-    for (int q = 0; q < nw; ++q) c += hist[q * n + k];
-    if (c) atomicAdd(tot + k, c);
-  }
+// the block's counts of n buckets (hist: one row of n per wave, the first the launch's
+// wave w0) to the waves' rows of cntW, and totals += their sums
+__device__ __forceinline__ void put_block_counts(const int* hist, int64_t n, int64_t w0, int waves,
+                                                 int* __restrict__ cntW, int* __restrict__ tot) {
+  const int nw = (int)min((int64_t)(blockDim.x >> 6), waves - w0);
+  auto put = [&](auto waves_here) {
+    constexpr int W = decltype(waves_here)::value;
+#pragma unroll 4
+    for (int k = threadIdx.x; k < n; k += blockDim.x) {
+      int c = 0;
+#pragma unroll
+      for (int q = 0; q < W; ++q) {
+        const int v = hist[q * n + k];
+        cntW[(w0 + q) * n + k] = v;
+        c += v;
+      }
+      if (c) atomicAdd(tot + k, c);
+    }
+  };
+  static_assert(kCountWaves == 4, "one form per number of waves");
+  if (nw == 4) put(std::integral_constant<int, 4>{});
+  if (nw == 3) put(std::integral_constant<int, 3>{});
+  if (nw == 2) put(std::integral_constant<int, 2>{});
+  if (nw == 1) put(std::integral_constant<int, 1>{});
 }
 __global__ __launch_bounds__(64 * kCountWaves) void cs_hat_count_kernel(
     int64_t n, int64_t chunk, int waves, uint64_t seed, int64_t r, int* __restrict__ cntW,
@@ -133,9 +149,7 @@ __global__ __launch_bounds__(64 * kCountWaves) void cs_hat_count_kernel(
     atomicAdd(hist + hh, 1);
   }
   __syncthreads();
-  if (w < waves)
-    for (int k = lane; k < r; k += 64) cntW[w * r + k] = hist[k];
-  add_block_counts(s_hist, r, cntH);
+  put_block_counts(s_hist, r, w - wave, waves, cntW, cntH);
 }
 
 // per bucket: the exclusive scan of the bucket totals (written to off, with
@@ -276,9 +290,7 @@ __global__ __launch_bounds__(64 * kCountWaves) void cs_digit_count_kernel(
     }
   }
   __syncthreads();
-  if (w < waves)
-    for (int k = lane; k < nd; k += 64) cntW[w * nd + k] = hist[k];
-  add_block_counts(s_hist, nd, tot);
+  put_block_counts(s_hist, nd, w - wave, waves, cntW, tot);
 }
 
 // PASS 0: writes (bucket, entry) of every row in low-digit order; PASS 1:
@@ -405,12 +417,8 @@ __global__ __launch_bounds__(64 * kCountWaves) void cs_lists_count_kernel(
     atomicAdd(histd + ((int)h & (nd - 1)), 1);
   }
   __syncthreads();
-  if (w < waves) {
-    for (int k = lane; k < r; k += 64) cntW[w * r + k] = hist[k];
-    for (int k = lane; k < nd; k += 64) cntWd[w * nd + k] = histd[k];
-  }
-  add_block_counts(s_hist, r, cntH);
-  add_block_counts(s_histd, nd, dtot);
+  put_block_counts(s_hist, r, w - wave, waves, cntW, cntH);
+  put_block_counts(s_histd, nd, w - wave, waves, cntWd, dtot);
 }
 
 // Fill: every row into its Hessian bucket's list (listH) and, by its low
