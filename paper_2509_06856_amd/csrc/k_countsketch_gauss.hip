@@ -765,8 +765,12 @@ struct FamilyTargets {
   int64_t off[4];  // off[l]: first row (in A) of level K - l, l = 0..L
 };
 
+// Rows wider than a wave (CH > 1): at most six waves per SIMD, which has fewer of their
+// runs open at once (one level of 2^20 buckets, 2.5 10^6 x 512 float32: 2548 us with the
+// seven that the registers allow, 2498 with six; 1.5 10^6 x 1000 2857 and 2852).
 template <typename T, int VEC, int L, int CH>
-__global__ __launch_bounds__(kThreads) void cs_gather_family_kernel(
+__global__ __launch_bounds__(kThreads)
+__attribute__((amdgpu_waves_per_eu(1, CH > 1 ? 6 : 8))) void cs_gather_family_kernel(
     int64_t mf, int d, int lanes, const T* __restrict__ X, int64_t ldx, const T* __restrict__ Y,
     const int* __restrict__ off, const int* __restrict__ list, T* __restrict__ A, int64_t lda,
     FamilyTargets tg, bool a_vec) {
