@@ -47,8 +47,7 @@ typedef enum { SLSE_F32 = 0, SLSE_F64 = 1, SLSE_BF16 = 2 } slse_dtype;
 typedef enum { SLSE_SRHT = 0, SLSE_COUNTSKETCH = 1, SLSE_GAUSSIAN = 2 } slse_sketch_kind;
 
 /* Factorization of the Hessian sketch (implementation-details appendix):
- *  SLSE_FACTOR_CHOL  through the Gram matrix (Cholesky; inside the solve the
- *                    Gram matrix is inverted directly).  Fine while the
+ *  SLSE_FACTOR_CHOL  the Cholesky factor of the Gram matrix.  Fine while the
  *                    sketch's condition number is well below u^{-1/2} ~ 1e8.
  *  SLSE_FACTOR_QR    the R factor of the QR of the sketch by shifted
  *                    CholeskyQR3 (Fukaya et al., SIAM J. Sci. Comput. 2020),
@@ -147,7 +146,7 @@ slse_status slse_sketch_apply(slse_ctx* ctx, slse_sketch_kind kind, uint64_t see
  *             matrix M = (R^T R)^{-1}, d x d, symmetric.
  * Errors: EINVAL; ESINGULAR when a pivot is zero, negative or non-finite
  * (the status is read back from the device, so this call synchronizes the
- * stream).
+ * stream; R and M then hold the factorization with such pivots replaced by 1).
  */
 slse_status slse_factor(slse_ctx* ctx, int64_t rows, int64_t d, const void* A, int64_t lda,
                         slse_dtype a_t, double scale, slse_factor_method method, double* R,
@@ -267,7 +266,9 @@ typedef struct {
  * carries across subproblems unless momentum_reset.
  *  beta_out   device FP64, length d: beta_T.
  *  rep        host report or NULL.  When non-NULL the call synchronizes the
- *             stream to fill it.
+ *             stream to fill it.  With rep = NULL and tol = 0 the call does not
+ *             wait and reports no bad pivot: it counts as 1, so a column of zeros
+ *             keeps the coefficient 0 and leaves the others as without it.
  * Errors: EINVAL (see slse_sketch_apply for the sizes; also start_step or
  * stop_step outside 0..T, or start_step > stop), ESINGULAR from the
  * factorization, ENOTCONV when tol > 0 was not met (beta_out still holds
@@ -449,8 +450,9 @@ slse_status slse_debug_gaussian_generate(slse_ctx* ctx, uint64_t seed, int32_t s
                                         int64_t m, int64_t N, int32_t blocks, uint32_t* sink,
                                         void* stream);
 /* Data-row splits the Gaussian sketch of N x (d+1) data into m sketch rows uses (host only):
- * bf16 = 1 for the matrix-core form on F32 data, 0 for the FP32/FP64 form.  Each split sums
- * its own contiguous range of data rows; the ranges are added in split order. */
+ * bf16 = 1 for the BF16 form on F32 data, 0 for the FP32/FP64 form.  Each split sums
+ * its own contiguous range of data rows (the FP32/FP64 form where few blocks would run in
+ * equal parts of it); the ranges are added in split order, the parts of one in row order. */
 slse_status slse_debug_gaussian_plan(int64_t N, int64_t d, int64_t m, int32_t bf16,
                                      int32_t* splits);
 

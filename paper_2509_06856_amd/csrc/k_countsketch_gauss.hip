@@ -241,7 +241,10 @@ __global__ __launch_bounds__(1024) void cs_colscan_kernel(int64_t r, int waves,
 // no atomic slot claims.
 constexpr int kDigitBits = 11;
 constexpr int kDigits = 1 << kDigitBits;
-constexpr int64_t kRadixRows = int64_t(1) << 21;  // the sort pays off from here (measured)
+// From here the sort is faster than placing the rows by rank and sorting each list: float64
+// x 64 in five levels (rank, sort) 2^17 rows 140, 161 us; 2^20 614, 627; 2^21 1171, 1168;
+// 2^22 2423, 2327; float32 x 8 100, 124; 273, 288; 498, 488; 999, 893.
+constexpr int64_t kRadixRows = int64_t(1) << 21;
 
 // the rank of this lane among the batch's lanes with the same digit, and
 // whether it is the last of them (one ballot per digit bit)
@@ -1856,7 +1859,7 @@ void countsketch_t(const CountSketchArgs& a, hipStream_t s) {
   const unsigned rb = (unsigned)grid1(a.N);
   const uint64_t mK_mask = (uint64_t)mK - 1;
   // 1. the largest level's lists, every bucket's rows in increasing row order:
-  // by the counting sort from 2^21 rows, below that by atomic slot claims and
+  // by the counting sort from 2^21 rows, below that placed by arrival number with
   // a sort of each list (fewer launches; the two give the same lists).
   // SLSE_CS_SORT=1 / 0 forces one of them, for measurement and tests.
   bool radix = sc.radix && a.N >= kRadixRows;
@@ -2027,10 +2030,13 @@ void gaussian_mfma(const GaussianArgs& a, hipStream_t s) {
 }
 
 // Column tiles of 16 per block of the FP32 / FP64 kernel: every column in one
-// block while the two tiles of their rows fit in LDS beside those of G (17 tiles in
-// FP32, 13 in FP64: 160 KB), else the least number of equal blocks; then the next
-// width that is built.  Products of tiles past the columns are wasted, so the widths
-// lie close together.
+// block up to 17 tiles in FP32 and 13 in FP64, the widest that are built, else the least
+// number of equal blocks; then the next width that is built.  LDS does not set these
+// limits (two tiles of the data beside those of G take 104 and 140 KB of 160; 29 and 15
+// tiles would fit), and beyond them G is drawn again for every column block: with widths of
+// 21, 25 and 29 (FP32) and 15 (FP64) built as well, 4096 rows of 16384 x 400 float32 took
+// 1212 us against 1483, 3584 of 65536 x 239 float64 3.89 ms against 4.50.  Products of
+// tiles past the columns are wasted, so the widths lie close together.
 constexpr int kGaussTiles[] = {1, 2, 3, 4, 5, 6, 7, 8, 9, 11, 13, 16, 17};
 struct GaussCols {
   int tiles;   // per block

@@ -249,8 +249,8 @@ __global__ __launch_bounds__(256) void gemm_kernel(int64_t M, int64_t N, int64_t
 // A step is latency: 9.8 us at d = 512, of which 2.6 the launch and the loads,
 // 4.3 the pivot tile and 2.9 the three products with their LDS round trips.  The
 // 16 steps take 0.157 ms, against 2.37 + 0.69 ms of a one-block Cholesky and a
-// row-wise inverse (slse_factor, 3072 x 512: 3.24 -> 0.26 ms; CholeskyQR3 of
-// 1536 x 256: 3.09 -> 0.43 ms) and 0.37 ms of a blocked Gauss-Jordan inverse with
+// row-wise inverse (slse_factor, 3072 x 512: 3.24 -> 0.24 ms; CholeskyQR3 of
+// 1536 x 256: 3.08 -> 0.40 ms) and 0.37 ms of a blocked Gauss-Jordan inverse with
 // two launches per 32 columns, which the solves took.
 // ---------------------------------------------------------------------------
 constexpr int kCB = 32;       // columns per step

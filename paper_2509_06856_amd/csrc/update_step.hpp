@@ -24,8 +24,8 @@ __device__ __forceinline__ void finish_step(const UpdateArgs& a, double gp, doub
 }
 
 // The updates that every block of a pass takes for itself: d columns and a sum of `rows`
-// partial rows.  Each block reads M and the rows, up to 288 KB here; twice the width
-// would be 1 MB, more than the launches that it saves.  Of 48 columns and 512 rows, 256
+// partial rows.  Each block reads M and the rows, up to 384 KB here (128 columns; 288 KB
+// at 64); twice the width would be 1 MB, more than the launches that it saves.  Of 48 columns and 512 rows, 256
 // rows as the limit was slower (2^18 x 48 float64 solve 1191 and 1227 us); wider problems
 // have their rows summed first from 257 on.
 constexpr int kStepD = 128;
