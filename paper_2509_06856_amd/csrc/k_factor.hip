@@ -8,6 +8,7 @@
 // and M = (R^T R)^{-1} = Z^T Z, once more the Gram kernel.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "kernels.hpp"
 
@@ -44,10 +45,12 @@ struct GemmLds {
   double b[kKS][32 * MT + 16];
 };
 
-// acc += op(pre A)[i0 .., k] op(pre B)[k, j0 ..] over k in [kb0, kend).
+// acc += op(A)[i0 .., k] op(B)[k, j0 ..] over k in [kb0, kend), for PRE of pre A and pre B.
 // TRA: A is stored k-major (A[k][i]), else i-major; TRB: B is stored j-major
-// (B[j][k]), else k-major.
-template <int MT, bool TRA, bool TRB, typename AP, typename BP>
+// (B[j][k]), else k-major.  (PRE at compile time: behind a branch every thread waited for all
+// its loads there, 300000 x 1 float32 306 -> 318 us; on the operands, among the products,
+// 300000 x 200 float64 1030 -> 1165 us, on their way to LDS 1021.)
+template <int MT, bool TRA, bool TRB, bool PRE, typename AP, typename BP>
 __device__ __forceinline__ void mfma_tile(GemmLds<MT>& lds, AP __restrict__ A, int64_t lda,
                                           BP __restrict__ B, int64_t ldb, int64_t M, int64_t N,
                                           int64_t i0, int64_t j0, int64_t kb0, int64_t kend,
@@ -80,20 +83,13 @@ __device__ __forceinline__ void mfma_tile(GemmLds<MT>& lds, AP __restrict__ A, i
   };
   if (kb0 < kend) fetch(kb0);
   for (int64_t k0 = kb0; k0 < kend; k0 += kKS) {
-    if (pre != 1.0) {
-#pragma unroll
-      for (int u = 0; u < kL; ++u) {
-        va[u] *= pre;
-        vb[u] *= pre;
-      }
-    }
 #pragma unroll
     for (int u = 0; u < kL; ++u) {
       const int e = t + 256 * u;
       const int ia = TRA ? e % S : e / kKS, ka = TRA ? e / S : e % kKS;
-      lds.a[ka][ia] = ((oka >> u) & 1) ? va[u] : 0.0;
+      lds.a[ka][ia] = ((oka >> u) & 1) ? (PRE ? va[u] * pre : va[u]) : 0.0;
       const int jb = TRB ? e / kKS : e % S, kb = TRB ? e % kKS : e / S;
-      lds.b[kb][jb] = ((okb >> u) & 1) ? vb[u] : 0.0;
+      lds.b[kb][jb] = ((okb >> u) & 1) ? (PRE ? vb[u] * pre : vb[u]) : 0.0;
     }
     __syncthreads();
     if (k0 + kKS < kend) fetch(k0 + kKS);
@@ -146,9 +142,10 @@ __device__ __forceinline__ void upper_tile(int t, int& ti, int& tj) {
   ti = t - tj * (tj + 1) / 2;
 }
 
-// One upper tile of G = alpha (pre A)^T (pre A) over the rows [kb0, kend): written to both
-// triangles of G, or without alpha to split slot `zpart` of `part` when there are several.
-template <int MT, typename AP, typename GP, typename PP>
+// One upper tile of G = alpha (pre A)^T (pre A) over the rows [kb0, kend) (pre = 1 unless
+// PRE): written to both triangles of G, or without alpha to split slot `zpart` of `part`
+// when there are several.
+template <int MT, bool PRE, typename AP, typename GP, typename PP>
 __device__ __forceinline__ void gram_tile(int d, double pre, double alpha, AP __restrict__ A, int64_t lda,
                                           GP __restrict__ G, int64_t ldg, PP __restrict__ part,
                                           int zpart, int tile, int64_t kb0, int64_t kend) {
@@ -158,7 +155,7 @@ __device__ __forceinline__ void gram_tile(int d, double pre, double alpha, AP __
   const int i0 = ti * 32 * MT, j0 = tj * 32 * MT;
   f64x4 acc[MT][MT];
   clear_acc(acc);
-  mfma_tile<MT, true, false>(lds, A, lda, A, lda, d, d, i0, j0, kb0, kend, pre, acc);
+  mfma_tile<MT, true, false, PRE>(lds, A, lda, A, lda, d, d, i0, j0, kb0, kend, pre, acc);
   for_acc(acc, [&](int r, int c, double v) {
     const int i = i0 + r, j = j0 + c;
     if (i >= d || j >= d) return;
@@ -171,13 +168,13 @@ __device__ __forceinline__ void gram_tile(int d, double pre, double alpha, AP __
   });
 }
 
-template <int MT, typename T>
+template <int MT, bool PRE, typename T>
 __global__ __launch_bounds__(256) void gram_kernel(int d, int64_t rows, double pre,
                                                    double alpha, const T* __restrict__ A,
                                                    int64_t lda, double* __restrict__ G, int64_t ldg,
                                                    double* __restrict__ part, int64_t kper) {
   const int64_t kb0 = (int64_t)blockIdx.y * kper;
-  gram_tile<MT>(d, pre, alpha, A, lda, G, ldg, part, (int)blockIdx.y, (int)blockIdx.x, kb0,
+  gram_tile<MT, PRE>(d, pre, alpha, A, lda, G, ldg, part, (int)blockIdx.y, (int)blockIdx.x, kb0,
                 min(rows, kb0 + kper));
 }
 
@@ -225,7 +222,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(int64_t M, int64_t N, int64_t
   const int64_t ldc = p.ldc[z];
   f64x4 acc[MT][MT];
   clear_acc(acc);
-  mfma_tile<MT, false, TRB>(lds, p.A[z], lda, p.B[z], ldb, M, N, i0, j0, 0, K, 1.0, acc);
+  mfma_tile<MT, false, TRB, false>(lds, p.A[z], lda, p.B[z], ldb, M, N, i0, j0, 0, K, 1.0, acc);
   for_acc(acc, [&](int r, int c, double v) {
     if (i0 + r < M && j0 + c < N) C[(i0 + r) * ldc + j0 + c] = alpha * v;
   });
@@ -532,7 +529,7 @@ __global__ __launch_bounds__(256) void gram_batched_kernel(const FactorJob* __re
   if ((int)blockIdx.x >= nt * (nt + 1) / 2) return;
   const int64_t kper = round_up(ceil_div(jb.rows, (int64_t)splits), kKS);
   const int64_t kb0 = sp * kper;
-  gram_tile<1>(jb.d, jb.pre, jb.scale, gptr(static_cast<const T*>(jb.A)), jb.lda, gptr(jb.G), jb.d,
+  gram_tile<1, sizeof(T) == 8>(jb.d, jb.pre, jb.scale, gptr(static_cast<const T*>(jb.A)), jb.lda, gptr(jb.G), jb.d,
                splits > 1 ? gptr(jb.part) : nullptr, sp, (int)blockIdx.x, kb0,
                min(jb.rows, kb0 + kper));
 }
@@ -556,7 +553,7 @@ __global__ __launch_bounds__(256) void inverse_batched_kernel(const FactorJob* _
   const FactorJob jb = jobs[blockIdx.z];
   const int nt = (int)ceil_div(jb.d, 32);
   if ((int)blockIdx.x >= nt * (nt + 1) / 2) return;
-  gram_tile<1>(jb.d, 1.0, 1.0, gptr((const double*)jb.Z), jb.d, gptr(jb.M), jb.d,
+  gram_tile<1, false>(jb.d, 1.0, 1.0, gptr((const double*)jb.Z), jb.d, gptr(jb.M), jb.d,
                (SLSE_GLOBAL double*)nullptr, 0, (int)blockIdx.x, 0, jb.d);
 }
 
@@ -628,16 +625,19 @@ void launch_gram(int64_t rows, int d, double alpha, const void* A, int64_t lda, 
   double pre;
   gram_scale(alpha, at, &pre, &alpha);
   const dim3 grid((unsigned)g.tiles, (unsigned)g.splits);
-  auto go = [&](auto* a) {
+  auto go = [&](auto* a, auto scaled) {
+    constexpr bool PRE = decltype(scaled)::value;
     if (g.wide)
-      gram_kernel<2><<<grid, 256, 0, s>>>(d, rows, pre, alpha, a, lda, G, ldg, part, g.kper);
+      gram_kernel<2, PRE><<<grid, 256, 0, s>>>(d, rows, pre, alpha, a, lda, G, ldg, part, g.kper);
     else
-      gram_kernel<1><<<grid, 256, 0, s>>>(d, rows, pre, alpha, a, lda, G, ldg, part, g.kper);
+      gram_kernel<1, PRE><<<grid, 256, 0, s>>>(d, rows, pre, alpha, a, lda, G, ldg, part, g.kper);
   };
   if (at == SLSE_F32)
-    go(static_cast<const float*>(A));
+    go(static_cast<const float*>(A), std::false_type{});
+  else if (pre == 1.0)
+    go(static_cast<const double*>(A), std::false_type{});
   else
-    go(static_cast<const double*>(A));
+    go(static_cast<const double*>(A), std::true_type{});
   SLSE_LAUNCH_CHECK();
   if (g.splits > 1) {
     const int blocks = (int)std::min<int64_t>(ceil_div((int64_t)d * d, 256), 4096);
