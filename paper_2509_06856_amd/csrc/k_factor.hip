@@ -243,7 +243,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(int64_t M, int64_t N, int64_t
 // a virtual one) write row K of R and of Z; nothing of row K of G is written
 // during step k, and every trailing tile belongs to one block.
 //
-// A step is latency: 9.8 us at d = 512, of which 2.6 the launch and the loads,
+// A step is latency: 9.6 us at d = 512, of which (taken apart) 2.6 the launch and the loads,
 // 4.3 the pivot tile and 2.9 the three products with their LDS round trips.  The
 // 16 steps take 0.157 ms, against 2.37 + 0.69 ms of a one-block Cholesky and a
 // row-wise inverse (slse_factor, 3072 x 512: 3.24 -> 0.24 ms; CholeskyQR3 of
